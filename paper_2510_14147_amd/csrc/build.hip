@@ -499,6 +499,36 @@ __device__ __forceinline__ void upd_lane(const float *__restrict__ X, int o, flo
         }
 }
 
+// The chunk's R farthest uncovered points (dv, id of each lane; dv < 0:
+// covered), farthest first.  Called by a whole wave.
+__device__ __forceinline__ void report_chunk(int c, int R, float dv, int id,
+                                             float *__restrict__ cb_D,
+                                             int32_t *__restrict__ cb_id)
+{
+    const int lane = threadIdx.x % CH;
+    for (int r = 0; r < R; ++r) {
+        float bd = dv;
+        int bi = id;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            float d2 = __shfl_xor(bd, off, WAVE);
+            int i2 = __shfl_xor(bi, off, WAVE);
+            if (better(d2, i2, bd, bi)) {
+                bd = d2;
+                bi = i2;
+            }
+        }
+        if (lane == 0) {
+            cb_D[(size_t)c * CAND_R + r] = bd;
+            cb_id[(size_t)c * CAND_R + r] = bi;
+        }
+        if (id == bi && bd >= 0.f) {  // the winner leaves the race
+            dv = -1.f;
+            id = INT_MAX;
+        }
+    }
+}
+
 template <int M>
 __global__ void __launch_bounds__(CH * UPD_W)
 k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
@@ -655,32 +685,96 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
         }
     }
     if (act) {
-        // the chunk's R farthest uncovered points, farthest first
-        const int R = cand_per_chunk(hb.ce[h] - hb.cb[h], kmax);
-        for (int r = 0; r < R; ++r) {
-            float bd = dv;
-            int bi = id;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                float d2 = __shfl_xor(bd, off, WAVE);
-                int i2 = __shfl_xor(bi, off, WAVE);
-                if (better(d2, i2, bd, bi)) {
-                    bd = d2;
-                    bi = i2;
-                }
-            }
-            if (lane == 0) {
-                cb_D[(size_t)c * CAND_R + r] = bd;
-                cb_id[(size_t)c * CAND_R + r] = bi;
-            }
-            if (id == bi && bd >= 0.f) {  // the winner leaves the race
-                dv = -1.f;
-                id = INT_MAX;
-            }
-        }
+        report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
         if (lane == 0 && j1 > j0)
             atomicAdd(cnt, (unsigned long long)(j1 - j0) * (unsigned)(e - s));
     }
+    }
+}
+
+// k_update for strings.  A distance is some five thousand instructions, so
+// the work-group's waves share one chunk's new centres (wave w takes every
+// LEV_W-th; 50K strings are 782 chunks, under one wave per SIMD otherwise)
+// and the nearest of them meet in LDS, the earliest centre winning ties as
+// in a scan in order.  The point is the pattern (its planes loaded once per
+// pass), the centre the text: every lane reads the same symbol.  A centre
+// whose length differs by D or more cannot come nearer than D.
+constexpr int LEV_W = 8;
+template <int NW, int NB>
+__global__ void __launch_bounds__(CH *LEV_W)
+k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
+             const int32_t *__restrict__ ch_e, const int32_t *__restrict__ queue,
+             const int32_t *__restrict__ qlen, Hubs hb, const int32_t *__restrict__ cent,
+             const int32_t *__restrict__ perm, float *__restrict__ D,
+             int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
+             float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax,
+             unsigned long long *__restrict__ cnt)
+{
+    __shared__ int sd[LEV_W][CH], sj[LEV_W][CH];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CH));
+    const int lane = threadIdx.x % CH;
+    const int nq = *qlen;
+    for (int t = blockIdx.x; t < nq; t += gridDim.x) {
+        const int c = queue[t], h = ch_hub[c];
+        if (!hb.act[h])
+            continue;  // the same for the whole work-group
+        const int s = ch_s[c], e = ch_e[c], p = s + lane;
+        const bool valid = p < e;
+        const int b = hb.b[h], j0 = hb.ma[h], j1 = hb.m[h];
+        const int o = valid ? perm[p] : perm[s];
+        float dcur = valid ? D[p] : 0.f;
+        int lcur = valid ? L[p] : 0;
+        if (j1 > j0) {
+            int bd = INT_MAX, bj = INT_MAX;
+            LevPat<NW, NB> q;
+            lev_load(q, P.peq + (size_t)o * P.sigma * P.W, P.sigma, P.W, P.len[o]);
+            for (int j = j0 + w; j < j1; j += LEV_W) {
+                const int cj = __builtin_amdgcn_readfirstlane(cent[b + j]);
+                const int lc = __builtin_amdgcn_readfirstlane(P.len[cj]);
+                if (!__any(valid && (float)abs(q.m - lc) < dcur))
+                    continue;
+                const int d = lev_run(q, P.s + (size_t)cj * P.dp, lc);
+                if (d < bd) {
+                    bd = d;
+                    bj = j;
+                }
+            }
+            __syncthreads();  // the previous chunk's values are consumed
+            sd[w][lane] = bd;
+            sj[w][lane] = bj;
+            __syncthreads();
+        }
+        if (w != 0)
+            continue;
+        float dv = -1.f;
+        int id = INT_MAX;
+        if (valid) {
+            if (j1 > j0) {
+                int bd = INT_MAX, bj = INT_MAX;
+#pragma unroll
+                for (int k = 0; k < LEV_W; ++k) {
+                    const int d = sd[k][lane], j = sj[k][lane];
+                    if (d < bd || (d == bd && j < bj)) {
+                        bd = d;
+                        bj = j;
+                    }
+                }
+                if (bj != INT_MAX && (float)bd < dcur) {
+                    dcur = (float)bd;
+                    lcur = bj;
+                }
+                D[p] = dcur;
+                L[p] = lcur;
+            }
+            const Thr T = tab->t[hb.lvl[h] - 1 + LOFF];
+            if (!within<M_LEV>(P, o, cent[b + lcur], dcur, T, cnt + 1)) {
+                dv = dcur;
+                id = o;
+            }
+        }
+        report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
+        if (lane == 0 && j1 > j0)
+            atomicAdd(cnt, (unsigned long long)(j1 - j0) * (unsigned)(e - s));
     }
 }
 
@@ -966,12 +1060,56 @@ k_select_pre(Hubs hb, int H, float *__restrict__ cb_D, int32_t *__restrict__ cb_
 // candidate accepted before them in this pass.  The pairwise conflicts of
 // the candidates are evaluated in parallel, then the greedy scan runs on
 // bit masks.
-template <int M>
+// With PH = SEL_TOP and SEL_TAKE the three parts are kernels of their own
+// (strings at levels of few hubs): SEL_TOP leaves the candidates in the
+// hub's part of sp, k_conflicts fills their conflicts in, SEL_TAKE goes on
+// from there.
+enum { SEL_ALL = 0, SEL_TOP = 1, SEL_TAKE = 2 };
+struct SelPart {
+    unsigned long long key[MAX_K];
+    unsigned long long conf[MAX_K][SEL_W];
+    int nk;
+};
+
+// Conflicts of strings, one pair per lane over the whole chip: within a
+// hub's own work-group the 2016 pairs of 64 candidates are eight distances
+// per thread one after another, 0.27 ms a pass while the other CUs idle
+// (as kernels of their own, top-K, conflicts and acceptance: 0.04 ms).
+// nt work-groups per hub.
+__global__ void __launch_bounds__(WAVE)
+k_conflicts(Pts P, Hubs hb, int nt, SelPart *__restrict__ sp,
+            const LevelTab *__restrict__ tab, unsigned long long *__restrict__ cnt)
+{
+    const int h = blockIdx.x / nt, q = (blockIdx.x % nt) * WAVE + threadIdx.x;
+    if (!hb.act[h])
+        return;
+    SelPart &s = sp[h];
+    const bool in = q < s.nk * (s.nk - 1) / 2;
+    if (in) {
+        int i = (int)((1.0f + sqrtf(1.0f + 8.0f * (float)q)) * 0.5f);
+        while (i * (i - 1) / 2 > q)
+            --i;
+        while ((i + 1) * i / 2 <= q)
+            ++i;
+        const int j = q - i * (i - 1) / 2;
+        const int a = 0x7FFFFFFF - (int)(uint32_t)s.key[i];
+        const int c = 0x7FFFFFFF - (int)(uint32_t)s.key[j];
+        const Thr T = tab->t[hb.lvl[h] - 1 + LOFF];
+        if (within<M_LEV>(P, a, c, key32<M_LEV>(P, a, c), T, cnt + 1))
+            atomicOr(&s.conf[i][j >> 6], 1ull << (j & 63));
+    }
+    const int tests = __popcll(__ballot(in));
+    if (threadIdx.x == 0 && tests)
+        atomicAdd(cnt, (unsigned long long)tests);
+}
+
+template <int M, int PH>
 __global__ void __launch_bounds__(SEL_T)
 k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
          const float *__restrict__ cb_D, const int32_t *__restrict__ cb_id,
          const LevelTab *__restrict__ tab, int kmax, int32_t *__restrict__ qnext,
-         int32_t *__restrict__ qnext_len, unsigned long long *__restrict__ cnt)
+         int32_t *__restrict__ qnext_len, unsigned long long *__restrict__ cnt,
+         SelPart *__restrict__ sp)
 {
     __shared__ unsigned long long buf[SEL_BUF], out[MAX_K];
     __shared__ unsigned long long conf[MAX_K][SEL_W];
@@ -987,6 +1125,15 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
     const int b = hb.b[h], m0 = hb.m[h];
     const Thr T = tab->t[hb.lvl[h] - 1 + LOFF];
 
+    int nk;
+    unsigned long long tests = 0;
+    if constexpr (PH == SEL_TAKE) {
+        nk = sp[h].nk;
+        for (int i = threadIdx.x; i < nk; i += SEL_T)
+            buf[i] = sp[h].key[i];
+        for (int i = threadIdx.x; i < MAX_K * SEL_W; i += SEL_T)
+            conf[i / SEL_W][i % SEL_W] = sp[h].conf[i / SEL_W][i % SEL_W];
+    } else {
     // ---- top-K candidates ------------------------------------------------
     // (a hub with many candidates streams its slices' pre-selected K each)
     int nsl;
@@ -1000,7 +1147,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
         const size_t a = (size_t)(q / R) * CAND_R + (size_t)(q % R);
         return cand_key(cb_D[a], cb_id[a]);
     };
-    int nk = nv <= SEL_RANK ? topk_rank((int)nv, K, ckey, buf, out, &fill_s)
+    nk = nv <= SEL_RANK ? topk_rank((int)nv, K, ckey, buf, out, &fill_s)
                             : topk_stream(nv, K, ckey, buf, &fill_s, out);
     if (threadIdx.x == 0)
         nk_s = nk;
@@ -1008,12 +1155,21 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
         conf[i / SEL_W][i % SEL_W] = 0ull;
     __syncthreads();
     nk = nk_s;
+    if constexpr (PH == SEL_TOP) {
+        for (int i = threadIdx.x; i < nk; i += SEL_T)
+            sp[h].key[i] = buf[i];
+        for (int i = threadIdx.x; i < MAX_K * SEL_W; i += SEL_T)
+            sp[h].conf[i / SEL_W][i % SEL_W] = 0ull;
+        if (threadIdx.x == 0)
+            sp[h].nk = nk;
+        __syncthreads();  // buf is reused by the next hub
+        continue;
+    }
 
     // ---- pairwise conflicts (j < i): within 2^{l-1} ----------------------
     // Vector rows of up to SEL_CR candidates are staged in LDS first (rows
     // padded by 4 floats: neighbouring rows start in different banks) and
     // tested in 2 x 2 blocks; the FP32 key is that of sqdiff_key either way.
-    unsigned long long tests = 0;
     const bool lds_rows = (M == M_L2 || M == M_ANG) && P.dp <= UPD_D && nk <= SEL_CR;
     const int ldr = P.dp + 4;
     if (lds_rows) {
@@ -1103,6 +1259,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
             if (within<M>(P, a, c, key32<M>(P, a, c), T, cnt + 1))
                 atomicOr(&conf[i][j >> 6], 1ull << (j & 63));
         }
+    }
     }
     __syncthreads();
 
@@ -1670,6 +1827,40 @@ Pts ingest_input(fnn_tree *T, const void *points, Scratch &S)
     }
 }
 
+// k_update_lev for the words and planes of the set's strings.
+template <class... A>
+static void launch_update_lev(dim3 g, hipStream_t s, const Pts &P, A... a)
+{
+    auto words = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        switch (lev_planes(P.sigma)) {
+        case 2:
+            FNN_LAUNCH((k_update_lev<NW, 2>), g, dim3(CH * LEV_W), 0, s, P, a...);
+            break;
+        case 5:
+            FNN_LAUNCH((k_update_lev<NW, 5>), g, dim3(CH * LEV_W), 0, s, P, a...);
+            break;
+        default:
+            FNN_LAUNCH((k_update_lev<NW, 8>), g, dim3(CH * LEV_W), 0, s, P, a...);
+            break;
+        }
+    };
+    switch (P.W) {
+    case 1:
+        words(std::integral_constant<int, 2>{});
+        break;
+    case 2:
+        words(std::integral_constant<int, 4>{});
+        break;
+    case 3:
+        words(std::integral_constant<int, 6>{});
+        break;
+    default:
+        words(std::integral_constant<int, 8>{});
+        break;
+    }
+}
+
 template <int M>
 static void build_impl(fnn_tree *T, const void *points, Scratch &S)
 {
@@ -1855,17 +2046,41 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
         const size_t upd_lds =
             (M == M_L2 || M == M_ANG) && T->dp <= UPD_D ? sizeof(float) * UPD_K * (T->dp + 4)
                                                         : 16;
+        // strings: a level of fewer hubs than CUs spreads its conflict tests;
+        // from there on the hubs' own work-groups fill the chip
+        SelPart *sp = nullptr;
+        if (M == M_LEV && H < num_cus())
+            sp = S.get<SelPart>(H);
         auto pass = [&](hipStream_t s, int k) {
             int32_t *qc = k ? qb : qa, *qx = k ? qa : qb;
             fill(qlen + (1 - k), 0, 1, s);
-            FNN_LAUNCH((k_update<M>), dim3(gu), dim3(CH * UPD_W), upd_lds, s, P, ch_hub, ch_s,
-                       ch_e, qc, qlen + k, hubs, cent, perm, D, L, tab, cb_D,
-                       cb_id, T->opt.kmax, cnt);
+            if constexpr (M == M_LEV)
+                launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, ch_s, ch_e, qc,
+                                  qlen + k, hubs, cent, perm, D, L, tab, cb_D, cb_id,
+                                  T->opt.kmax, cnt);
+            else
+                FNN_LAUNCH((k_update<M>), dim3(gu), dim3(CH * UPD_W), upd_lds, s, P, ch_hub,
+                           ch_s, ch_e, qc, qlen + k, hubs, cent, perm, D, L, tab, cb_D,
+                           cb_id, T->opt.kmax, cnt);
             FNN_LAUNCH(k_select_pre, dim3(grid_cap((int64_t)H * SEL_SL, 1, 8192)),
                        dim3(SEL_T), 0, s, hubs, H, cb_D, cb_id, T->opt.kmax);
-            FNN_LAUNCH((k_select<M>), dim3(grid_cap(H, 1, 4096)), dim3(SEL_T), 0, s, P,
-                       hubs, H, cent, cb_D, cb_id, tab, T->opt.kmax, qx,
-                       qlen + (1 - k), cnt);
+            const dim3 gs(grid_cap(H, 1, 4096));
+            if constexpr (M == M_LEV) {
+                if (sp) {
+                    const int K = std::min(T->opt.kmax, MAX_K);
+                    const int nt = (int)cdiv(std::max(1, K * (K - 1) / 2), WAVE);
+                    FNN_LAUNCH((k_select<M, SEL_TOP>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent,
+                               cb_D, cb_id, tab, T->opt.kmax, qx, qlen + (1 - k), cnt, sp);
+                    FNN_LAUNCH(k_conflicts, dim3((unsigned)(H * nt)), dim3(WAVE), 0, s, P,
+                               hubs, nt, sp, tab, cnt);
+                    FNN_LAUNCH((k_select<M, SEL_TAKE>), gs, dim3(SEL_T), 0, s, P, hubs, H,
+                               cent, cb_D, cb_id, tab, T->opt.kmax, qx, qlen + (1 - k), cnt,
+                               sp);
+                    return;
+                }
+            }
+            FNN_LAUNCH((k_select<M, SEL_ALL>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent, cb_D,
+                       cb_id, tab, T->opt.kmax, qx, qlen + (1 - k), cnt, nullptr);
         };
         if (GP <= 1) {
             for (int k = 0;; k ^= 1) {

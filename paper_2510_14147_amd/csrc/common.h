@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace fnn {
 
 enum { M_L2 = 0, M_ANG = 1, M_HAM = 2, M_LEV = 3 };
@@ -99,118 +101,82 @@ __device__ __forceinline__ int ham_words(const uint64_t *__restrict__ a,
 // Unit-cost edit distance by the bit-parallel dynamic programme of Myers
 // (1999) in Hyyro's formulation for whole-string distance: the pattern's
 // vertical deltas live in bit vectors, one text symbol is consumed per
-// step, the top row's horizontal delta is always +1.  Multi-word: the
-// addition carries and the shifts carry between 64-bit words.
-template <int W>
-__device__ inline int lev_bitpar(const uint64_t *__restrict__ peq, int m,
-                                 const uint8_t *__restrict__ text, int tl)
+// step, the top row's horizontal delta is always +1.
+//
+// The vectors are NW 32-bit words (the hardware's add with carry and its
+// funnel shift chain them: 10 instructions per word and symbol, against
+// about 25 with 64-bit words, whose carries are compares).  The match mask
+// of a text symbol comes from NB bit planes of the pattern held in registers
+// (plane b, bit i: bit b of symbol i), NB more instructions per word, instead
+// of a table indexed by the symbol, which is a memory round trip per step.
+// The last column's deltas add up to the distance (D[m][n] = n + sum of the
+// vertical deltas), so no score is kept.  Bits past the pattern's end only
+// ever carry upwards and are masked off at the end.  50K strings of 80..120
+// symbols: BUILDLEV.
+template <int NW, int NB>
+struct LevPat {
+    uint32_t p[NB][NW];
+    int m;
+};
+
+template <int NW, int NB>
+__device__ __forceinline__ void lev_load(LevPat<NW, NB> &q, const uint64_t *__restrict__ peq,
+                                         int sigma, int W, int m)
 {
-    if (m == 0)
-        return tl;
-    if (tl == 0)
-        return m;
-    uint64_t pv[W], mv[W];
+    q.m = m;
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-        pv[w] = ~0ull;
-        mv[w] = 0ull;
-    }
-    const int lastw = (m - 1) >> 6;
-    const uint64_t lastbit = 1ull << ((m - 1) & 63);
-    int score = m;
-    for (int j = 0; j < tl; ++j) {
-        const uint64_t *eqv = peq + (int)text[j] * W;
-        uint64_t cadd = 0ull, cph = 1ull, cmh = 0ull;
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            if (w <= lastw) {
-                uint64_t eq = eqv[w];
-                uint64_t xv = eq | mv[w];
-                uint64_t t = eq & pv[w];
-                uint64_t s1 = t + pv[w];
-                uint64_t c1 = s1 < t ? 1ull : 0ull;
-                uint64_t s2 = s1 + cadd;
-                uint64_t c2 = s2 < s1 ? 1ull : 0ull;
-                cadd = c1 | c2;
-                uint64_t xh = (s2 ^ pv[w]) | eq;
-                uint64_t ph = mv[w] | ~(xh | pv[w]);
-                uint64_t mh = pv[w] & xh;
-                if (w == lastw) {
-                    if (ph & lastbit)
-                        ++score;
-                    else if (mh & lastbit)
-                        --score;
+        for (int w = 0; w < NW; ++w)
+            q.p[b][w] = 0u;
+    for (int c = 1; c < sigma; ++c) {
+#pragma unroll
+        for (int w2 = 0; w2 < NW / 2; ++w2) {
+            const uint64_t v = w2 < W ? peq[c * W + w2] : 0ull;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                if ((c >> b) & 1) {
+                    q.p[b][2 * w2] |= (uint32_t)v;
+                    q.p[b][2 * w2 + 1] |= (uint32_t)(v >> 32);
                 }
-                uint64_t phs = (ph << 1) | cph;
-                uint64_t mhs = (mh << 1) | cmh;
-                cph = ph >> 63;
-                cmh = mh >> 63;
-                pv[w] = mhs | ~(xv | phs);
-                mv[w] = phs & xv;
-            }
         }
     }
-    return score;
 }
 
-// The same recurrence for alphabets of at most 4 symbols: the pattern's
-// match masks sit in registers and the text is read four symbols per load,
-// so a step waits on no memory (the per-symbol loads of lev_bitpar make a
-// single distance a chain of dependent memory round trips).
-template <int W>
-__device__ inline int lev_bitpar4(const uint64_t *__restrict__ peq, int sigma, int m,
-                                  const uint8_t *__restrict__ text, int tl)
+template <int NW, int NB>
+__device__ __forceinline__ int lev_run(const LevPat<NW, NB> &q, const uint8_t *__restrict__ text,
+                                       int tl)
 {
-    if (m == 0)
-        return tl;
-    if (tl == 0)
-        return m;
-    uint64_t eqr[4][W], pv[W], mv[W];
+    uint32_t pv[NW], mv[NW];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int w = 0; w < W; ++w)
-            eqr[c][w] = c < sigma ? peq[c * W + w] : 0ull;  // the table holds sigma rows
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        pv[w] = ~0ull;
-        mv[w] = 0ull;
+    for (int w = 0; w < NW; ++w) {
+        pv[w] = ~0u;
+        mv[w] = 0u;
     }
-    const int lastw = (m - 1) >> 6;
-    const uint64_t lastbit = 1ull << ((m - 1) & 63);
-    int score = m;
     auto step = [&](unsigned ch) {
-        uint64_t cadd = 0ull, cph = 1ull, cmh = 0ull;
+        uint32_t s[NB];  // all ones where the symbol's bit is set
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            if (w <= lastw) {
-                const uint64_t eq = ch == 0 ? eqr[0][w]
-                                    : ch == 1 ? eqr[1][w]
-                                    : ch == 2 ? eqr[2][w]
-                                              : eqr[3][w];
-                uint64_t xv = eq | mv[w];
-                uint64_t t = eq & pv[w];
-                uint64_t s1 = t + pv[w];
-                uint64_t c1 = s1 < t ? 1ull : 0ull;
-                uint64_t s2 = s1 + cadd;
-                uint64_t c2 = s2 < s1 ? 1ull : 0ull;
-                cadd = c1 | c2;
-                uint64_t xh = (s2 ^ pv[w]) | eq;
-                uint64_t ph = mv[w] | ~(xh | pv[w]);
-                uint64_t mh = pv[w] & xh;
-                if (w == lastw) {
-                    if (ph & lastbit)
-                        ++score;
-                    else if (mh & lastbit)
-                        --score;
-                }
-                uint64_t phs = (ph << 1) | cph;
-                uint64_t mhs = (mh << 1) | cmh;
-                cph = ph >> 63;
-                cmh = mh >> 63;
-                pv[w] = mhs | ~(xv | phs);
-                mv[w] = phs & xv;
-            }
+        for (int b = 0; b < NB; ++b)
+            s[b] = (uint32_t)((int)(ch << (31 - b)) >> 31);
+        unsigned carry = 0u;
+        uint32_t ph1 = 0x80000000u, mh1 = 0u;  // the word below's deltas
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            uint32_t eq = ~(q.p[0][w] ^ s[0]);
+#pragma unroll
+            for (int b = 1; b < NB; ++b)
+                eq &= ~(q.p[b][w] ^ s[b]);
+            const uint32_t xv = eq | mv[w];
+            const uint32_t t = __builtin_addc(eq & pv[w], pv[w], carry, &carry);
+            const uint32_t xh = (t ^ pv[w]) | eq;
+            const uint32_t ph = mv[w] | ~(xh | pv[w]);
+            const uint32_t mh = pv[w] & xh;
+            const uint32_t phs = __builtin_amdgcn_alignbit(ph, ph1, 31);
+            const uint32_t mhs = __builtin_amdgcn_alignbit(mh, mh1, 31);
+            ph1 = ph;
+            mh1 = mh;
+            pv[w] = mhs | ~(xv | phs);
+            mv[w] = phs & xv;
         }
     };
     int j = 0;
@@ -224,31 +190,53 @@ __device__ inline int lev_bitpar4(const uint64_t *__restrict__ peq, int sigma, i
         }
     for (; j < tl; ++j)
         step(text[j]);
-    return score;
+    int d = tl;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int r = min(max(q.m - 32 * w, 0), 32);  // pattern bits in this word
+        const uint32_t k = r == 32 ? ~0u : (1u << r) - 1u;
+        d += __popc(pv[w] & k) - __popc(mv[w] & k);
+    }
+    return d;
+}
+
+// Planes needed for an alphabet: 2, 5 or 8.
+__host__ __device__ __forceinline__ int lev_planes(int sigma)
+{
+    return sigma <= 4 ? 2 : sigma <= 32 ? 5 : 8;
+}
+
+template <int NW>
+__device__ inline int lev_one(const uint64_t *peq, int m, const uint8_t *text, int tl, int W,
+                              int sigma)
+{
+    auto go = [&](auto nb) {
+        LevPat<NW, decltype(nb)::value> q;
+        lev_load(q, peq, sigma, W, m);
+        return lev_run(q, text, tl);
+    };
+    switch (lev_planes(sigma)) {
+    case 2:
+        return go(std::integral_constant<int, 2>{});
+    case 5:
+        return go(std::integral_constant<int, 5>{});
+    default:
+        return go(std::integral_constant<int, 8>{});
+    }
 }
 
 __device__ inline int lev_dispatch(const uint64_t *peq, int m,
                                    const uint8_t *text, int tl, int W, int sigma)
 {
-    if (sigma <= 4) {
-        switch (W) {
-        case 1:
-            return lev_bitpar4<1>(peq, sigma, m, text, tl);
-        case 2:
-            return lev_bitpar4<2>(peq, sigma, m, text, tl);
-        default:
-            break;  // longer patterns: the general form
-        }
-    }
     switch (W) {
     case 1:
-        return lev_bitpar<1>(peq, m, text, tl);
+        return lev_one<2>(peq, m, text, tl, W, sigma);
     case 2:
-        return lev_bitpar<2>(peq, m, text, tl);
+        return lev_one<4>(peq, m, text, tl, W, sigma);
     case 3:
-        return lev_bitpar<3>(peq, m, text, tl);
+        return lev_one<6>(peq, m, text, tl, W, sigma);
     default:
-        return lev_bitpar<4>(peq, m, text, tl);
+        return lev_one<8>(peq, m, text, tl, W, sigma);
     }
 }
 

@@ -671,23 +671,34 @@ k_tile(Pts P, const int2 *__restrict__ inter, long long ninter,
                     for (int j = 0; j < 4; ++j)
                         acc[i][j] = (float)hc[i][j];
                 __syncthreads();
-            } else {  // Levenshtein: one bit-parallel DP per pair
+            } else {
+                // Levenshtein: one bit-parallel DP per pair, the tile's pairs
+                // dealt out to the threads in order (string packs are single
+                // leaf blocks, a third of a tile's side on average: fixed
+                // 4 x 4 blocks left most threads idle).  Edges are marked
+                // here; the guard below finds none in acc.
                 __syncthreads();
                 const int kk = (int)E.lo;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int ri = ty * 4 + i, cj = tx * 4 + j;
-                        float v = FLT_MAX;
-                        if (ri < ra && cj < rb && (!sdiag || ri < cj)) {
-                            const int p = pa + ri, q = pb + cj;
-                            const int lp = P.len[p], lq = P.len[q];
-                            if (abs(lp - lq) <= kk)
-                                v = (float)key32<M_LEV>(P, p, q);
-                        }
-                        acc[i][j] = v;
+                    for (int j = 0; j < 4; ++j)
+                        acc[i][j] = FLT_MAX;
+                for (int f = t; f < ra * rb; f += TT) {
+                    const int ri = f / rb, cj = f - ri * rb;
+                    if (sdiag && ri >= cj)
+                        continue;
+                    const int p = pa + ri, q = pb + cj;
+                    if (abs(P.len[p] - P.len[q]) > kk)
+                        continue;
+                    const float v = key32<M_LEV>(P, p, q);
+                    if (v <= E.lo) {
+                        atomicOr(&mask[ri], 1ull << cj);
+                        atomicOr(&cmask[cj], 1ull << ri);
+                        if constexpr (DIST)
+                            dt[ri * (TS + 1) + cj] = v;
                     }
+                }
             }
 
             // ---- exactness guard and edge bits ----------------------------
