@@ -32,7 +32,7 @@ PEAK_HBM_GBS = 8000.0
 PEAK_FP32_VEC_TFLOPS = 157.3
 PEAK_BF16_TFLOPS = 2500.0
 PEAK_FP8_TFLOPS = 5000.0
-PEAK_INT8_TOPS = 5000.0
+PEAK_FP4_TFLOPS = 10000.0
 
 
 def workload(name: str):
@@ -213,18 +213,19 @@ def measured_traffic(kernel: str, workload: str):
 def roofline(dim, precision, tq, workload=""):
     """Roofline of the dominant kernel of one query: the leaf-tile count pass
     (plain FP32: 3*d flops per pair -- difference, square, accumulate) or the
-    MFMA Gram filter (2*k flops per screened pair, k = padded dim; on Hamming
-    codes 2*k integer ops, k = code bits), timed with HIP events inside the
+    MFMA filter (2*k flops per screened pair, k = padded dim; on Hamming
+    codes k = the bits every pair takes), timed with HIP events inside the
     library on the stream it runs on."""
     if tq["count_ms"] <= 0:
         return None
     if precision == "i8":
-        ops = 2.0 * dim * tq["filter_pairs"]
+        # every pair's first (at most) 128 bits; the rest only where needed
+        ops = 2.0 * min(dim, 128) * tq["filter_pairs"]
         kms = tq["filter_ms"] if tq.get("filter_ms", 0) > 0 else tq["count_ms"]
         ach = ops / (kms / 1e3) / 1e12
-        kname = f"k_gram<HAM,i8,k{dim}>"
-        return {"bound": "mfma", "achieved": round(ach, 3), "peak": PEAK_INT8_TOPS,
-                "unit": "TOP/s", "frac": round(ach / PEAK_INT8_TOPS, 4),
+        kname = f"k_ham_direct<fp4,k{dim}>"
+        return {"bound": "mfma", "achieved": round(ach, 3), "peak": PEAK_FP4_TFLOPS,
+                "unit": "TFLOP/s", "frac": round(ach / PEAK_FP4_TFLOPS, 4),
                 "traffic": measured_traffic(kname, workload),
                 "kernel": kname, "kernel_ms": round(kms, 3),
                 "ops_per_launch": ops}
@@ -492,7 +493,7 @@ def main():
                     "fp8": "fp8 filter + f32"}.get(
         "+".join(precs), "+".join(precs))
     if metric == "hamming":
-        out["dtype"] = ("i8 MFMA (exact integer Gram)" if "i8" in precs
+        out["dtype"] = ("fp4 +-1 MFMA (exact integer Gram)" if "i8" in precs
                         else "u64 (xor + popcount)")
     elif metric == "levenshtein":
         out["dtype"] = "u64 (bit-parallel edit distance)"

@@ -64,8 +64,8 @@ typedef enum {
     FNN_PREC_FP32 = 0,   /* direct-difference FP32 tiles (the plain path)      */
     FNN_PREC_BF16 = 1,   /* MFMA BF16 Gram filter, FP32 recompute of survivors */
     FNN_PREC_FP8 = 2,    /* MFMA FP8 (E4M3) Gram filter, FP32 recompute        */
-    FNN_PREC_I8 = 3,     /* Hamming codes of <= 256 bits: exact int8 MFMA Gram */
-                         /* (bits as +-1 bytes: s.t = K - 2 d over K bits)     */
+    FNN_PREC_I8 = 3,     /* Hamming codes of <= 256 bits: exact MFMA Gram of   */
+                         /* the bits as +-1 (s.t = K - 2 d over K bits)       */
     FNN_PREC_AUTO = 4,   /* chosen per query: I8 for Hamming codes of <= 256  */
                          /* bits; FP16 for L2 / angular with 16 <= dim <= 128 */
                          /* when the filter's margin is small against eps^2   */

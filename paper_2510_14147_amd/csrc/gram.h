@@ -61,10 +61,6 @@ struct GramArgs {
     int2 *surv;
     unsigned long long *nsurv;     // running count (may exceed cap)
     long long surv_cap;
-    // exact integer filter (Hamming codes, not validating): the survivors
-    // are the edges, and degp counts the edges of each tree position; null
-    // otherwise
-    int32_t *degp;
     // screened pairs when the work list is every pair of one cloud
     // (n (n - 1) / 2, known in closed form); -1 otherwise (counted on the
     // device)
@@ -86,10 +82,12 @@ struct GramArgs {
     // staged kernel runs
     const void *qp;
     const float *ayp;
-    // uniform packs over one cloud: pack k holds tree positions GP k ..
-    // min(GP k + GP, upk) - 1 and a work unit's B packs are consecutive;
-    // 0: packs from q_pb / q_pe and the list
-    int upk;
+    // uniform packs: B pack k holds tree positions GP k + uoff ..
+    // min(GP k + uoff + GP, upk) - 1 and a work unit's B packs are
+    // consecutive; upk 0: packs from q_pb / q_pe and the list
+    int upk, uoff;
+    int nq;    // rows of q
+    int kmax;  // Hamming codes: the largest floor(eps) of the query
 };
 
 // Per-pack copies of the quantised rows and column terms for the narrow
@@ -113,14 +111,6 @@ void edges_scatter(const int2 *edges, const float *edist, long long ne, bool bot
 // fill exactly); a rank past its row sets ERR_INDEX.
 void edges_place(const int2 *edges, const float *edist, const int2 *erank, long long ne,
                  const int64_t *row_ptr, const TileOut &o, hipStream_t s);
-// Survivors of the exact integer filter (tree positions) into the CSR, with
-// their Hamming distances.
-void edges_scatter_ham(const int2 *surv, long long ne, const Pts &P,
-                       const int32_t *perm, const TileOut &o, hipStream_t s);
-// deg[perm[p]] += degp[p] for every tree position p; *dsum += sum degp.
-void degrees_from_positions(const int32_t *degp, const int32_t *perm, int n,
-                            int32_t *deg, unsigned long long *dsum, hipStream_t s);
-
 // 2 c1 mean|x - mu|^2 / t2min for the BF16 filter (mu per cloud): how much
 // its rounding margin widens the test against the smallest squared
 // threshold; small values mean a selective filter.

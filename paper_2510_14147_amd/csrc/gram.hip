@@ -542,20 +542,37 @@ __global__ void k_sqdev(const float *__restrict__ x, int n, int dp, Centre C,
         atomicMax(amax, __float_as_uint(m));
 }
 
-// Hamming codes as signed bytes for the integer Gram: bit b of a code
-// becomes byte b, +1 if set and -1 if not.  Over K = 64 W bits the product
-// of two such rows is s.t = K - 2 d_H, so d_H <= k exactly when
-// s.t >= K - 2k: one integer threshold, no per-point terms.
+// Hamming codes as 4-bit floats for the matrix cores: bit b of a code becomes
+// +1 if set and -1 if not (sign and 1.0 in E2M1: exact, and so are their
+// products and sums in FP32).  Over K = 64 W bits the product of two such
+// rows is s.t = K - 2 d_H, so d_H <= k exactly when s.t >= K - 2k: one
+// threshold, no per-point terms.  Word t of a code is 32 bytes; plane t / 2
+// holds words 2 t' and 2 t' + 1 of every row side by side ([n + GP][64]
+// bytes, zero past n), so a test of the first words alone reads only them.
+__device__ __forceinline__ size_t ham_plane(int n) { return (size_t)(n + GP) * 64; }
+
 __global__ void k_quant_ham(const uint64_t *__restrict__ h, int n, int W,
-                            int8_t *__restrict__ q)
+                            unsigned char *__restrict__ q)
 {
-    const int kq = 64 * W;
     for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-         e < (long long)n * kq; e += (long long)gridDim.x * blockDim.x) {
-        const long long i = e / kq;
-        const int k = (int)(e - i * kq);
-        const int bit = (int)((h[i * W + (k >> 6)] >> (k & 63)) & 1ull);
-        q[e] = (int8_t)(2 * bit - 1);
+         e < (long long)(n + GP) * W; e += (long long)gridDim.x * blockDim.x) {
+        const long long i = e / W;
+        const int t = (int)(e - i * W);
+        unsigned v[8];
+        const uint64_t c = i < n ? h[i * W + t] : 0ull;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            // the byte's bits to the nibbles' lowest, then clear bits to signs
+            unsigned x = (unsigned)(c >> (8 * b)) & 0xFFu;
+            x = (x | (x << 12)) & 0x000F000Fu;
+            x = (x | (x << 6)) & 0x03030303u;
+            x = (x | (x << 3)) & 0x11111111u;
+            v[b] = i < n ? 0x22222222u | ((~x & 0x11111111u) << 3) : 0u;
+        }
+        int4 *o = reinterpret_cast<int4 *>(q + (size_t)(t >> 1) * ham_plane(n) +
+                                           (size_t)i * 64 + (t & 1) * 32);
+        o[0] = make_int4((int)v[0], (int)v[1], (int)v[2], (int)v[3]);
+        o[1] = make_int4((int)v[4], (int)v[5], (int)v[6], (int)v[7]);
     }
 }
 
@@ -755,11 +772,6 @@ struct GramCfg<FNN_PREC_FP8> {
     static constexpr int KSTEP = 64;
     static constexpr int EB = 1;
 };
-template <>
-struct GramCfg<FNN_PREC_I8> {
-    static constexpr int KSTEP = 32;  // code bits (one signed byte each) per MFMA
-    static constexpr int EB = 1;
-};
 
 // The 16-bit formats share the operand layout of the 32 x 32 x 16 products
 // (eight elements per lane); only the instruction differs.
@@ -779,9 +791,6 @@ __device__ __forceinline__ f32x16 mfma16(const int4 &a, const int4 &b, const f32
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0);
     }
 }
-
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((ext_vector_type(16))) int i32x16;
 
 // OR of v over the wave, in every lane (DPP within rows of 16 lanes, then
 // row broadcasts; no LDS round trips).
@@ -831,8 +840,7 @@ __device__ __forceinline__ void pad_surv(const GramArgs &G, unsigned long long c
 // End of one 64-row x 32-column block (column block cb) of a wave's tile:
 // the pairs that pass the filter (all valid pairs with their pass flag when
 // validating) go to the survivor list through the wave's reserved slots
-// [cpos, cend); the exact integer filter also counts degrees; npairs counts
-// the screened pairs.  mx is the lane's largest accumulator (scaled) and ay
+// [cpos, cend); npairs counts the screened pairs.  mx is the lane's largest accumulator (scaled) and ay
 // its column term.
 template <int PREC, typename V, typename ACC>
 __device__ __forceinline__ void block_finish(const GramArgs &G, const ACC (&accb)[2], V ay,
@@ -868,8 +876,8 @@ __device__ __forceinline__ void block_finish(const GramArgs &G, const ACC (&accb
     // r0(i) < rl, looked up per tile), bit i of pm whether it also passes.
     const int rl = (col < nb ? (self ? min(na, col) : na) : 0) - 4 * hi;
     const unsigned om = rmS[min(max(rl + 4, 0), 68)];
-    // Fails as sign bits: gq < ay exactly when gq - ay is negative (integer
-    // codes: no overflow; floats: x - y rounds to +0 when x == y), shifted
+    // Fails as sign bits: gq < ay exactly when gq - ay is negative (x - y
+    // rounds to +0 when x == y), shifted
     // in from the top position down, one funnel shift per position.  (A
     // float tie -0 against +0 counts as a fail; the real filters keep a
     // positive slack above every true edge, so a tie is never one.)
@@ -878,9 +886,7 @@ __device__ __forceinline__ void block_finish(const GramArgs &G, const ACC (&accb
     for (int i = 31; i >= 0; --i) {
         const int rb = i >> 4, q = i & 15;
         unsigned d;
-        if constexpr (PREC == FNN_PREC_I8)
-            d = (unsigned)((int)accb[rb][q] - (int)ay);
-        else if constexpr (PREC == FNN_PREC_FP8)
+        if constexpr (PREC == FNN_PREC_FP8)
             d = __float_as_uint(__fsub_rn(__fmul_rn(accb[rb][q], G.gscale), ay));
         else
             d = __float_as_uint(__fsub_rn((float)accb[rb][q], ay));
@@ -893,7 +899,6 @@ __device__ __forceinline__ void block_finish(const GramArgs &G, const ACC (&accb
     // of rows r0 (lanes 0..31) and r0 + 4 (lanes 32..63).
     const unsigned todo = G.validate ? om : pm;
     unsigned any = wave_or_u32(todo);
-    int cdeg = 0;  // exact integer filter: edges of this lane's column
     while (any) {
         const int i = __ffs(any) - 1;
         any &= any - 1;
@@ -914,25 +919,6 @@ __device__ __forceinline__ void block_finish(const GramArgs &G, const ACC (&accb
             G.surv[o] = make_int2(pa + r0 + 4 * hi,
                                   (pb + col) | (int)(((pm >> i) & 1u) << 31));
         cpos += (unsigned long long)cnt;
-        if constexpr (PREC == FNN_PREC_I8) {
-            if (G.degp) {
-                // row degrees from the two halves of the ballot
-                const int lo = __popcll(m & 0xFFFFFFFFull);
-                const int hi2 = __popcll(m >> 32);
-                if (lane == 0 && lo)
-                    atomicAdd(&G.degp[pa + r0], lo);
-                if (lane == 32 && hi2)
-                    atomicAdd(&G.degp[pa + r0 + 4], hi2);
-                cdeg += emit;
-            }
-        }
-    }
-    if constexpr (PREC == FNN_PREC_I8) {
-        // column degrees: lanes l and l + 32 hold the two row halves
-        // of column l
-        cdeg += __shfl_xor(cdeg, 32, WAVE);
-        if (G.degp && hi == 0 && cdeg)
-            atomicAdd(&G.degp[pb + col], cdeg);
     }
 }
 
@@ -976,9 +962,8 @@ k_gram(Pts P, GramArgs G, TileOut out)
     constexpr int ldb = rowb + 16;             // LDS row stride (bytes)
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char *Bs = smem;                  // [GP][ldb]
-    // filter terms (integers on the Hamming path, where the test is exact)
-    using V = typename std::conditional<PREC == FNN_PREC_I8, int, float>::type;
-    using ACC = typename std::conditional<PREC == FNN_PREC_I8, i32x16, f32x16>::type;
+    using V = float;    // filter terms
+    using ACC = f32x16;
     V *ayS = (V *)(smem + GP * ldb);           // [GP]
     V *axS = ayS + GP;                         // [GW][GP]
     __shared__ int eB[UNIT_MAX], eP[UNIT_MAX], eN[UNIT_MAX], eC[UNIT_MAX];
@@ -1033,10 +1018,9 @@ k_gram(Pts P, GramArgs G, TileOut out)
                 if (r < na) {
                     const unsigned char *src =
                         (const unsigned char *)G.q + (size_t)(pa + r) * rowb;
-                    if constexpr (is16(PREC) || PREC == FNN_PREC_I8) {
+                    if constexpr (is16(PREC)) {
                         // k-step ks: bytes ks*32 + hi*16 .. +16 (16-bit
-                        // elements ks*16 + hi*8 .. +8, or Hamming bits
-                        // ks*32 + hi*16 .. +16 as bytes)
+                        // elements ks*16 + hi*8 .. +8)
                         #pragma unroll
                         for (int ks = 0; ks < nks; ++ks) {
                             const int4 v = *(const int4 *)(src + (ks * 16 + hi * 8) * 2);
@@ -1065,14 +1049,9 @@ k_gram(Pts P, GramArgs G, TileOut out)
         // skipped below)
         const int ca = (G.pcl && has_a) ? G.pcl[pa] : -1;
         const float e2 = ca >= 0 ? G.ct[ca].e2f : G.e2f;
-        // stored as the accumulators' start value -ax (scaled units); on
-        // the Hamming path 2k - K with k = floor(eps), K = code bits, and
-        // the pass test s.t + 2k - K >= 0 is exact
+        // stored as the accumulators' start value -ax (scaled units)
         for (int r = lane; r < GP; r += WAVE) {
-            if constexpr (PREC == FNN_PREC_I8)
-                axS[w * GP + r] = (r < na) ? 2 * (int)e2 - kq : -(1 << 29);
-            else
-                axS[w * GP + r] = (r < na) ? -0.5f * (G.hx[pa + r] - e2) * ginv : -FLT_MAX;
+            axS[w * GP + r] = (r < na) ? -0.5f * (G.hx[pa + r] - e2) * ginv : -FLT_MAX;
         }
 
         // B tiles are software-pipelined: the rows of entry e+1 are loaded
@@ -1080,7 +1059,7 @@ k_gram(Pts P, GramArgs G, TileOut out)
         constexpr int CPR = rowb / 16;                      // 16-byte chunks per row
         constexpr int NCH = (GP * CPR + GT - 1) / GT;       // chunks per thread
         int4 pre[NCH];
-        V pre_ay = PREC == FNN_PREC_I8 ? (V)(1 << 29) : (V)FLT_MAX;
+        V pre_ay = (V)FLT_MAX;
         // this unit's B packs (id, first point, size, cloud) in LDS: the
         // entry loop then never waits on a chain of dependent global loads
         for (int i = t; i < e1 - e0; i += GT) {
@@ -1105,10 +1084,7 @@ k_gram(Pts P, GramArgs G, TileOut out)
                                              (size_t)(pbb + r) * rowb + o);
             }
             if (t < GP) {
-                if constexpr (PREC == FNN_PREC_I8)
-                    pre_ay = (t < nbb) ? (V)0 : (V)(1 << 29);
-                else
-                    pre_ay = (t < nbb) ? (V)(0.5f * G.hx[pbb + t]) : (V)FLT_MAX;
+                pre_ay = (t < nbb) ? (V)(0.5f * G.hx[pbb + t]) : (V)FLT_MAX;
             }
         };
         load_b(e0);
@@ -1141,8 +1117,7 @@ k_gram(Pts P, GramArgs G, TileOut out)
             for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
-                    using V4 = typename std::conditional<PREC == FNN_PREC_I8, int4, float4>::type;
-                    const V4 a4 = *reinterpret_cast<const V4 *>(
+                    const float4 a4 = *reinterpret_cast<const float4 *>(
                         axS + w * GP + rb * 32 + 8 * q4 + 4 * hi);
 #pragma unroll
                     for (int cb = 0; cb < 2; ++cb) {
@@ -1156,7 +1131,7 @@ k_gram(Pts P, GramArgs G, TileOut out)
             const unsigned char *brow1 = Bs + (32 + l32) * ldb;
             // all of this step's B fragments, read before the matrix-core
             // chain so no k-step waits on LDS
-            constexpr bool B16 = is16(PREC) || PREC == FNN_PREC_I8;
+            constexpr bool B16 = is16(PREC);
             int4 bfrag[B16 ? nks : 1][2];
             if constexpr (B16) {
 #pragma unroll
@@ -1168,24 +1143,7 @@ k_gram(Pts P, GramArgs G, TileOut out)
             }
 #pragma unroll
             for (int ks = 0; ks < nks; ++ks) {
-                if constexpr (PREC == FNN_PREC_I8) {
-                    // 16 bytes per lane and k-step, the BF16 byte layout
-                    const int slot = ks >> 1, half = ks & 1;
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb) {
-                        i32x4 bb;
-                        __builtin_memcpy(&bb, &bfrag[ks][cb], 16);
-#pragma unroll
-                        for (int rb = 0; rb < 2; ++rb) {
-                            const i32x4 aa = (i32x4){Areg[rb][slot][half * 4 + 0],
-                                                     Areg[rb][slot][half * 4 + 1],
-                                                     Areg[rb][slot][half * 4 + 2],
-                                                     Areg[rb][slot][half * 4 + 3]};
-                            acc[cb][rb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                                aa, bb, acc[cb][rb], 0, 0, 0);
-                        }
-                    }
-                } else if constexpr (is16(PREC)) {
+                if constexpr (is16(PREC)) {
                     const int4 bv[2] = {bfrag[ks][0], bfrag[ks][1]};
                     const int slot = ks >> 1, half = ks & 1;
 #pragma unroll
@@ -1549,7 +1507,7 @@ k_gram_direct(Pts P, GramArgs G, TileOut out)
             bool skip;
             if constexpr (U) {
                 b = ub0 + (e - e0);
-                pb = b * GP;
+                pb = b * GP + G.uoff;
                 nb = min(GP, G.upk - pb);
                 skip = false;
             } else {
@@ -1615,6 +1573,211 @@ k_gram_direct(Pts P, GramArgs G, TileOut out)
                     step(uc, e + 1, BB, ayB);
                 else
                     load_b(uc, e1 - 1, BB, ayB);  // same loads in flight on both paths
+            }
+        };
+        if (uloop) {
+            // entries before the wave's own pack pair it with earlier packs
+            const int es = has_a ? e0 + max(0, a - ub0) : e1;
+            if (es < e1)
+                run(std::true_type{}, es);
+        } else {
+            run(std::false_type{}, e0);
+        }
+        __syncthreads();  // eB.. are rewritten by the next unit
+    }
+    surv_flush(G, survS[w], (unsigned)__builtin_amdgcn_readfirstlane((int)fillS[w]));
+}
+
+// The exact filter for Hamming codes of W = S1 + S2 words, the narrow
+// kernel's scheme on 32 x 32 x 64 products of 4-bit floats (one word of both
+// codes per instruction).  With S2 > 0 a block first takes only its first S1
+// = 2 words: a pair within k of each other has a product of at least
+// 128 - 2k there, which unrelated codes (64 +- 5.7 of 128 bits apart) all but
+// never reach, so the other words are read and multiplied only for blocks
+// where some pair does.  Survivors are edges already; the decision kernel
+// after it adds their distances and ranks.
+//
+// What bounds it: two products (64 cycles) and about 12 vector instructions
+// per block of 1024 pairs.  988258 codes of 256 bits, k = 24, every pair
+// (4.88e11): 27.7 ms where the products alone are 12.4; the traversal's list
+// (2.0e11 pairs) 27.4 ms, against 90.4 ms on one signed byte per bit with
+// the tiles staged in LDS.
+template <int S1, int S2>
+__global__ void __launch_bounds__(GT, S1 <= 2 ? 4 : 2)  // waves / SIMD that fit unspilled
+k_ham_direct(int n, GramArgs G, TileOut out)
+{
+    static_assert(S1 >= 1 && S1 + S2 <= 4 && (S2 == 0 || S1 == 2), "words of a code");
+    __shared__ int eB[UNIT_MAX], eP[UNIT_MAX], eN[UNIT_MAX], eC[UNIT_MAX];
+    __shared__ unsigned rmS[69];  // row-mask table
+    for (int i = threadIdx.x; i < 69; i += GT)
+        rmS[i] = c_rowmask.m[i];
+    const int t = threadIdx.x, lane = t & (WAVE - 1);
+    const int w = __builtin_amdgcn_readfirstlane(t / WAVE);  // wave-uniform
+    const bool uloop = G.upk && !G.validate;  // the uniform-pack entry loop
+    const int l32 = lane & 31, hi = lane >> 5;
+    const unsigned char *Q = (const unsigned char *)G.q;
+    const size_t plane = ham_plane(n);
+    // byte offset of this lane's part of word s of a row, within its plane
+    const int lo = hi * 16;
+    __shared__ unsigned fillS[GW];                     // each wave's buffered survivors
+    __shared__ __align__(16) int2 survS[GW][SURV_BUF];  // and the buffer
+    if (lane == 0)
+        fillS[w] = 0u;
+    auto mul = [](const int4 &a, const int4 &b, const f32x16 &c) __attribute__((always_inline)) {
+        const i32x8 x = {a.x, a.y, a.z, a.w, 0, 0, 0, 0}, y = {b.x, b.y, b.z, b.w, 0, 0, 0, 0};
+        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, c, 4, 4, 0, 0, 0, 0);
+    };
+    auto word = [&](const unsigned char *row, int s) __attribute__((always_inline)) {
+        return *(const int4 *)(row + (size_t)(s >> 1) * plane + (s & 1) * 32 + lo);
+    };
+    // XCD slices of the unit order, as in k_gram
+    const int bpx = (int)gridDim.x / 8, jb = (int)blockIdx.x / 8;
+    const int per = (G.nunits + 7) / 8;
+    const int ub = min(G.nunits, (int)(blockIdx.x % 8) * per);
+    const int ue = min(G.nunits, ub + per);
+    for (int u = ub + jb; u < ue; u += bpx) {
+        const int e0 = G.ubeg[u], e1 = min(G.ubeg[u + 1], e0 + UNIT_MAX);
+        if (G.ubeg[u + 1] - e0 > UNIT_MAX && t == 0)
+            atomicOr(out.err, ERR_INDEX);  // the list builders never do this
+        const int g = G.lg[e0];
+        const int a = G.nn + GW * g + w;
+        const bool has_a = (GW * g + w) < G.npacks && G.q_pe[a] - G.q_pb[a] <= GP;
+        const int pa = has_a ? __builtin_amdgcn_readfirstlane(G.q_pb[a]) : 0;
+        const int na = has_a ? __builtin_amdgcn_readfirstlane(G.q_pe[a]) - pa : 0;
+        const int ub0 = uloop ? __builtin_amdgcn_readfirstlane(G.lb[e0]) : 0;
+        int4 Af[2][S1];
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int s = 0; s < S1; ++s)
+                Af[rb][s] = rb * 32 + l32 < na ? word(Q + (size_t)(pa + rb * 32 + l32) * 64, s)
+                                               : make_int4(0, 0, 0, 0);
+        const int ca = (G.pcl && has_a) ? G.pcl[pa] : -1;
+        const int k = (int)(ca >= 0 ? G.ct[ca].e2f : G.e2f);
+        // pass: s.t >= K - 2k; first words: the rest adds at most 64 S2
+        const float thr = (float)(64 * (S1 + S2) - 2 * k), thr1 = thr - 64.f * S2;
+        for (int i = uloop ? e1 - e0 : t; i < e1 - e0; i += GT) {
+            const int bb = G.nn + G.lb[e0 + i];
+            const int pbb = G.q_pb[bb];
+            eB[i] = bb;
+            eP[i] = pbb;
+            eN[i] = G.q_pe[bb] - pbb;
+            eC[i] = G.pcl ? G.pcl[pbb] : -1;
+        }
+        __syncthreads();
+        int4 BA[2][S1], BB[2][S1];
+        // row of this lane's column cb * 32 + l32 of entry e (inside the rows
+        // and the zero rows after them)
+        auto brow = [&](auto uc, int e, int cb) __attribute__((always_inline)) {
+            constexpr bool U = decltype(uc)::value;
+            if constexpr (U) {
+                return Q + (size_t)((ub0 + (e - e0)) * GP + G.uoff) * 64 +
+                       (unsigned)((cb * 32 + l32) * 64);
+            } else {
+                const int p = __builtin_amdgcn_readfirstlane(eP[e - e0]);
+                const int m = __builtin_amdgcn_readfirstlane(eN[e - e0]);
+                return Q + (size_t)p * 64 + (unsigned)(min(cb * 32 + l32, max(m, 1) - 1) * 64);
+            }
+        };
+        auto load_b = [&](auto uc, int e, int4 (&B)[2][S1]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                const unsigned char *r = brow(uc, e, cb);
+#pragma unroll
+                for (int s = 0; s < S1; ++s)
+                    B[cb][s] = word(r, s);
+            }
+        };
+        auto step = [&](auto uc, int e, int4 (&B)[2][S1]) __attribute__((always_inline)) {
+            constexpr bool U = decltype(uc)::value;
+            int b, pb, nb;
+            bool skip;
+            if constexpr (U) {
+                b = ub0 + (e - e0);
+                pb = b * GP + G.uoff;
+                nb = min(GP, G.upk - pb);
+                skip = false;
+            } else {
+                b = __builtin_amdgcn_readfirstlane(eB[e - e0]);
+                pb = __builtin_amdgcn_readfirstlane(eP[e - e0]);
+                nb = __builtin_amdgcn_readfirstlane(eN[e - e0]);
+                const int cb_cl = __builtin_amdgcn_readfirstlane(eC[e - e0]);
+                skip = !has_a || b < a || (ca >= 0 && (cb_cl == ca) == (bool)G.cross);
+            }
+            if (!skip) {
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb) {
+                    f32x16 acc[2];
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        acc[cb] = (f32x16){};
+#pragma unroll
+                        for (int s = 0; s < S1; ++s)
+                            acc[cb] = mul(Af[rb][s], B[cb][s], acc[cb]);
+                    }
+                    float mx[2];
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        mx[cb] = acc[cb][0];
+#pragma unroll
+                        for (int q = 1; q < 16; ++q)
+                            mx[cb] = fmaxf(mx[cb], acc[cb][q]);
+                    }
+                    if (__ballot(fmaxf(mx[0], mx[1]) >= thr1) == 0 && (U || !G.validate))
+                        continue;
+                    // ---- the other words, and the pairs that pass ---------
+                    if constexpr (S2 > 0) {
+                        const int r = min(rb * 32 + l32, max(na, 1) - 1);
+#pragma unroll
+                        for (int s = S1; s < S1 + S2; ++s) {
+                            const int4 x = word(Q + (size_t)(pa + r) * 64, s);
+#pragma unroll
+                            for (int cb = 0; cb < 2; ++cb)
+                                acc[cb] = mul(x, word(brow(uc, e, cb), s), acc[cb]);
+                        }
+                    }
+                    // rows past na and columns past nb never pass (the row
+                    // limit hidden from the compiler, which would hold every
+                    // position's comparison over the whole unit)
+                    if (na < rb * 32 + 32) {
+                        int lim = na - 32 * rb - 4 * hi;
+                        asm volatile("" : "+v"(lim));
+#pragma unroll
+                        for (int q = 0; q < 16; ++q) {
+                            const bool in = 8 * (q >> 2) + (q & 3) < lim;
+                            acc[0][q] = in ? acc[0][q] : -FLT_MAX;
+                            acc[1][q] = in ? acc[1][q] : -FLT_MAX;
+                        }
+                    }
+                    float ay[2];
+                    uint64_t hm[2];
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        ay[cb] = cb * 32 + l32 < nb ? thr : FLT_MAX;
+                        float m = acc[cb][0];
+#pragma unroll
+                        for (int q = 1; q < 16; ++q)
+                            m = fmaxf(m, acc[cb][q]);
+                        hm[cb] = __ballot(m >= ay[cb]);
+                    }
+                    if ((hm[0] | hm[1]) != 0 || (!U && G.validate))
+                        half_finish(G, acc, ay, hm, rb, na, nb, b - a, pa, pb, &fillS[w],
+                                    survS[w], rmS);
+                }
+            }
+            // on every path: the count of loads in flight never depends on it
+            load_b(uc, min(e + 2, e1 - 1), B);
+        };
+        auto run = [&](auto uc, int es) __attribute__((always_inline)) {
+            load_b(uc, es, BA);
+            asm volatile("" ::: "memory");  // the two entries' loads in this order
+            load_b(uc, min(es + 1, e1 - 1), BB);
+            for (int e = es; e < e1; e += 2) {
+                step(uc, e, BA);
+                if (e + 1 < e1)
+                    step(uc, e + 1, BB);
+                else
+                    load_b(uc, e1 - 1, BB);
             }
         };
         if (uloop) {
@@ -1988,69 +2151,6 @@ void edges_scatter(const int2 *edges, const float *edist, long long ne, bool bot
                edist, ne, both, o);
 }
 
-// Edges of the exact integer filter (tree positions, passed flag in bit 31
-// of .y) into the CSR: distance from the codes, positions mapped to input
-// ids.
-__global__ void k_edges_scatter_ham(const int2 *__restrict__ surv, long long ne,
-                                    const uint64_t *__restrict__ h, int W,
-                                    const int32_t *__restrict__ perm, TileOut out)
-{
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < ne;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int2 e = surv[i];
-        const int oi = e.x < 0 ? -1 : perm[e.x];
-        const unsigned long long s1 = claim_run(out.cursor, oi);
-        if (e.x < 0)
-            continue;  // an unused slot
-        const int pi = e.x, pj = e.y & 0x7FFFFFFF;
-        const float d = (float)ham_words(h + (size_t)pi * W, h + (size_t)pj * W, W);
-        const int oj = perm[pj];
-        const unsigned long long s2 = atomicAdd(&out.cursor[oj], 1ull);
-        if (s1 < out.nnz && s2 < out.nnz) {
-            out.col[s1] = oj;
-            out.dist[s1] = d;
-            out.col[s2] = oi;
-            out.dist[s2] = d;
-        } else {
-            atomicOr(out.err, ERR_INDEX);
-        }
-    }
-}
-
-void edges_scatter_ham(const int2 *surv, long long ne, const Pts &P,
-                       const int32_t *perm, const TileOut &o, hipStream_t s)
-{
-    if (ne <= 0)
-        return;
-    FNN_LAUNCH(k_edges_scatter_ham, dim3(grid_cap(ne, 256, 4096)), dim3(256), 0, s, surv,
-               ne, P.h, P.dp, perm, o);
-}
-
-__global__ void k_deg_from_positions(const int32_t *__restrict__ degp,
-                                     const int32_t *__restrict__ perm, int n,
-                                     int32_t *__restrict__ deg,
-                                     unsigned long long *__restrict__ dsum)
-{
-    unsigned long long t = 0;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n;
-         p += gridDim.x * blockDim.x) {
-        deg[perm[p]] += degp[p];
-        t += (unsigned long long)degp[p];
-    }
-    t = wave_sum(t);
-    if ((threadIdx.x & (WAVE - 1)) == 0 && t)
-        atomicAdd(dsum, t);
-}
-
-void degrees_from_positions(const int32_t *degp, const int32_t *perm, int n,
-                            int32_t *deg, unsigned long long *dsum, hipStream_t s)
-{
-    if (n <= 0)
-        return;
-    FNN_LAUNCH(k_deg_from_positions, dim3(grid_cap(n, 256, 2048)), dim3(256), 0, s,
-               degp, perm, n, deg, dsum);
-}
-
 template <int M, int PREC, int NKS>
 static void launch_gram_k(bool fill_pass, const Pts &P, const GramArgs &G,
                           const TileOut &o, hipStream_t s)
@@ -2073,6 +2173,8 @@ static void launch_gram_k(bool fill_pass, const Pts &P, const GramArgs &G,
     FNN_LAUNCH((k_gram<M, PREC, NKS>), grid, dim3(GT), sh, s, P, G, o);
 }
 
+static void count_pairs(const GramArgs &G, const TileOut &o, hipStream_t s);
+
 template <int M, int PREC, int NKS>
 static void launch_gram_direct(const Pts &P, const GramArgs &G, const TileOut &o,
                                hipStream_t s)
@@ -2089,10 +2191,63 @@ static void launch_gram_direct(const Pts &P, const GramArgs &G, const TileOut &o
     const long long need = ((long long)G.nunits + 7) / 8 * 8;
     const dim3 grid((unsigned)std::max<long long>(8, std::min(want, need)));
     FNN_LAUNCH((k_gram_direct<M, PREC, NKS>), grid, dim3(GT), 0, s, P, G, o);
+    count_pairs(G, o, s);
+}
+
+// Pairs a kernel without a count of its own screens: known in closed form,
+// or counted from the lists.
+static void count_pairs(const GramArgs &G, const TileOut &o, hipStream_t s)
+{
     if (G.dense_pairs >= 0)
         fill(o.cnt + 2, (unsigned long long)G.dense_pairs, 1, s);
     else
         FNN_LAUNCH(k_gram_pairs, dim3(grid_cap(G.nlist, 256, 4096)), dim3(256), 0, s, G, o);
+}
+
+template <int S1, int S2>
+static void launch_ham_k(const GramArgs &G, const TileOut &o, hipStream_t s)
+{
+    static std::atomic<int> resident{0};  // work-groups per CU (this instance)
+    int rb = resident.load();
+    if (rb == 0) {
+        FNN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &rb, reinterpret_cast<const void *>(&k_ham_direct<S1, S2>), GT, 0));
+        rb = std::max(1, rb);
+        resident.store(rb);
+    }
+    const long long want = std::max<long long>(8, (long long)rb * num_cus() / 8 * 8);
+    const long long need = ((long long)G.nunits + 7) / 8 * 8;
+    const dim3 grid((unsigned)std::max<long long>(8, std::min(want, need)));
+    FNN_LAUNCH((k_ham_direct<S1, S2>), grid, dim3(GT), 0, s, G.nq, G, o);
+    count_pairs(G, o, s);
+}
+
+// Codes of three and four words take their first two alone first while the
+// radius is below what unrelated codes differ by in 128 bits, five standard
+// deviations under the half: 64 - 28.  (988258 codes of 256 bits: 29.4 ms
+// this way at a radius of 36, 56.3 ms with all four words at 48, where every
+// block holds a pair that passes the first two.)
+static void launch_ham(const GramArgs &G, const TileOut &o, hipStream_t s)
+{
+    if (G.nunits <= 0)
+        return;
+    const bool first = G.kmax <= 36;
+    switch (G.kq / 64) {
+    case 1: launch_ham_k<1, 0>(G, o, s); break;
+    case 2: launch_ham_k<2, 0>(G, o, s); break;
+    case 3:
+        if (first)
+            launch_ham_k<2, 1>(G, o, s);
+        else
+            launch_ham_k<3, 0>(G, o, s);
+        break;
+    default:
+        if (first)
+            launch_ham_k<2, 2>(G, o, s);
+        else
+            launch_ham_k<4, 0>(G, o, s);
+        break;
+    }
 }
 
 template <int M, int PREC>
@@ -2102,14 +2257,7 @@ static void launch_gram(bool fill_pass, const Pts &P, const GramArgs &G,
     if (G.nunits <= 0)
         return;
     const int nks = G.kq / GramCfg<PREC>::KSTEP;
-    if constexpr (PREC == FNN_PREC_I8) {
-        switch (nks) {
-        case 2: launch_gram_k<M, PREC, 2>(fill_pass, P, G, o, s); break;
-        case 4: launch_gram_k<M, PREC, 4>(fill_pass, P, G, o, s); break;
-        case 6: launch_gram_k<M, PREC, 6>(fill_pass, P, G, o, s); break;
-        default: launch_gram_k<M, PREC, 8>(fill_pass, P, G, o, s); break;
-        }
-    } else if constexpr (is16(PREC)) {
+    if constexpr (is16(PREC)) {
         // the narrow kernel reads the per-pack copies (made when it applies)
         const bool narrow_fits = G.qp != nullptr;
         switch (nks) {
@@ -2183,7 +2331,7 @@ void gram_launch(int metric, int prec, bool fill_pass, const Pts &P,
                  const GramArgs &G, const TileOut &o, hipStream_t s)
 {
     if (metric == M_HAM) {
-        launch_gram<M_HAM, FNN_PREC_I8>(fill_pass, P, G, o, s);
+        launch_ham(G, o, s);
     } else if (metric == M_L2) {
         if (prec == FNN_PREC_BF16)
             launch_gram<M_L2, FNN_PREC_BF16>(fill_pass, P, G, o, s);
@@ -2212,22 +2360,20 @@ float gram_eps2(int metric, double eps, const Thr &E, double t2mul, double add)
     return (float)(T2 * (1.0 + 320.0 * u32) + 1e-30);
 }
 
-// Hamming codes as +-1 bytes for the integer filter; no centring or
-// scaling, the test is exact.
+// Hamming codes as +-1 for the exact filter; no centring or scaling.
 static void quantise_ham(const fnn_tree *T, int prec, Scratch &S, GramArgs &G)
 {
     hipStream_t s = S.stream();
-    const int n = (int)T->n, dp = T->dp;
-    const int kq = dp * 64;
-    if (prec != FNN_PREC_I8 || kq > 256)
+    const int n = (int)T->n, W = T->dp;
+    if (prec != FNN_PREC_I8 || W > 4)
         fail(FNN_EUNSUPPORTED, "integer MFMA filter supports codes of <= 256 bits");
     G.gscale = 1.f;
-    G.kq = kq;
-    int8_t *qb = (int8_t *)S.raw((size_t)n * kq + 64);
+    G.kq = 64 * W;
+    unsigned char *qb = (unsigned char *)S.raw((size_t)(n + GP) * 64 * ((W + 1) / 2));
     G.q = qb;
     G.hx = nullptr;  // no per-point terms
-    FNN_LAUNCH(k_quant_ham, dim3(grid_cap((int64_t)n * kq, 256, 16384)), dim3(256), 0,
-               s, T->h, n, dp, qb);
+    FNN_LAUNCH(k_quant_ham, dim3(grid_cap((int64_t)(n + GP) * W, 256, 16384)), dim3(256), 0,
+               s, T->h, n, W, qb);
 }
 
 // Leading principal coordinates of X for the filter (see k_pca): returns K
@@ -2527,6 +2673,8 @@ void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &
     G.e2add = 0.0;
     G.dense_pairs = -1;
     G.upk = 0;
+    G.uoff = 0;
+    G.nq = (int)T->n;
     if (T->metric == M_HAM) {
         quantise_ham(T, prec, S, G);
         G.t2mul = 1.0;
@@ -2555,14 +2703,10 @@ void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &
         for (int g = 0; g < ngr; ++g)
             mu += npk - GW * g;
         if (npk > 0 && (double)ninter >= 0.95 * (double)allp && mu < INT32_MAX) {
-            int32_t *big = S.get<int32_t>(1);
-            fill(big, 0, 1, s);
-            FNN_LAUNCH(k_max_pack, dim3(grid_for(npk, 256)), dim3(256), 0, s,
-                       T->q_pt_begin + nn, T->q_pt_end + nn, npk, GP, big);
-            if (read_scalar(big, s) == 0) {
-                // one cloud: full packs of consecutive tree positions in
-                // place of the tree's (indexed from 0, not past the nodes)
-                const bool one = T->ncloud <= 1 && T->cross_a < 0;
+            // one cloud: full packs of consecutive tree positions in place of
+            // the tree's (indexed from 0, not past the nodes)
+            const bool one = T->ncloud <= 1 && T->cross_a < 0;
+            if (one || gram_packs_fit(T, S)) {
                 int base = nn, np = npk;
                 if (one) {
                     np = (int)((T->n + GP - 1) / GP);

@@ -1930,14 +1930,19 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     int2 *inter = nullptr;
     long long ninter = 0;
     bool dense = false;
-    if (use_gram && ncl == 1 && !opt.trace && T->npacks >= 256 && gram_packs_fit(T, S)) {
+    if (use_gram && ncl == 1 && !opt.trace && T->npacks >= 256) {
         const int ns = 8192;
         unsigned long long *pc = S.get<unsigned long long>(1);
         fill(pc, 0ull, 1, s);
         FNN_LAUNCH((k_prune_sample<M>), dim3(ns / 256), dim3(256), 0, s, P, Q, pr,
                    (int)T->npacks, ns, pc);
         const unsigned long long pruned = read_scalar(pc, s);
-        dense = pruned * 100 <= (unsigned long long)ns;  // at most 1 % prunable
+        // vector metrics: at most 1 % prunable.  Codes: screening a pack pair
+        // costs far less than carrying it through the traversal and its
+        // sorted lists (988258 codes with 27 % of the pairs kept: 28 ms
+        // against 30 ms of traversal and 27 ms of filter), so unless seven
+        // eighths could be pruned
+        dense = M == M_HAM ? pruned * 8 <= 7ull * ns : pruned * 100 <= (unsigned long long)ns;
         st.traverse_tests = ns;
     }
     if (dense) {
@@ -1964,6 +1969,10 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
             G.validate = opt.validate;
             G.perm = T->perm;
             gram_pad_packs(M, prec, G, S);
+            G.kmax = 0;  // Hamming codes: E.lo is floor(eps)
+            if (M == M_HAM)
+                for (const CloudThr &t : ct_h)
+                    G.kmax = std::max(G.kmax, (int)std::min(t.E.lo, 1048576.f));
             G.ct = ncl > 1 ? ct_d : nullptr;
             G.pcl = ncl > 1 ? T->pcl : nullptr;
             if (ncl > 1 && (G.t2mul != 1.0 || G.e2add != 0.0)) {
@@ -1984,10 +1993,9 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     }
     tm.mark();  // 2
 
-    // [0..5] see TileOut, [6..7] the learned path's re-fill, [8] sum of the
-    // exact integer filter's position degrees (twice its edges)
-    unsigned long long *cnt = S.get<unsigned long long>(9);
-    fill(cnt, 0ull, 9, s);
+    // [0..5] see TileOut, [6..7] the learned path's re-fill
+    unsigned long long *cnt = S.get<unsigned long long>(8);
+    fill(cnt, 0ull, 8, s);
     TileOut o{};
     o.cnt = cnt;
     int *bad = S.get<int>(1);
@@ -1998,7 +2006,7 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     int64_t nnz = 0;
     int64_t novf = 0;
     unsigned long long *packed = nullptr;  // packed CSR entries (see k_place_packed)
-    unsigned long long hc0[9] = {0};
+    unsigned long long hc0[8] = {0};
 
     if (use_gram || !learned) {
         // ---- count pass (plain tiles) / filter + exact survivors (MFMA) ---
@@ -2039,10 +2047,6 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                 cap = std::max<long long>(cap, (long long)n * (n - 1) / 2 + 1);
             if (opt.list_cap > 0)
                 cap = opt.list_cap;
-            // the integer filter on Hamming codes is exact: unless validating,
-            // it writes the edges, their distances and the degrees itself
-            const bool direct = M == M_HAM && !opt.validate;
-            int32_t *degp = direct ? S.get<int32_t>(n) : nullptr;
             for (int attempt = 0;; ++attempt) {
                 // a list (and its decided edges) larger than the device
                 // cannot be allocated: say so before asking
@@ -2052,10 +2056,6 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                 G.surv = S.get<int2>(cap);
                 G.surv_cap = cap;
                 G.nsurv = ns;
-                if (direct) {
-                    G.degp = degp;
-                    fill(degp, 0, n, s);
-                }
                 fill(ns, 0ull, 2, s);
                 fill(cnt + 2, 0ull, 1, s);
                 FNN_HIP(hipEventRecord(fev[0], s));
@@ -2071,30 +2071,24 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                         FNN_HIP(hipEventElapsedTime(&fms, fev[0], fev[1]));
                         st.filter_ms = fms;
                     }
-                    if (direct) {
-                        degrees_from_positions(degp, T->perm, n, o.deg, cnt + 8, s);
-                        gedges = G.surv;
-                        ngedges = got;
-                    } else {
-                        // with no plain tiles in the query every CSR entry
-                        // comes from a survivor: keep the ranks its degree
-                        // counters return and place it without cursors
-                        // (measured at C2: 2.2 ms faster at ~53 survivors per
-                        // point, 15 ms at ~350), while the ranks take under a
-                        // quarter of the free device memory
-                        size_t free_now = 0, tot_now = 0;
-                        FNN_HIP(hipMemGetInfo(&free_now, &tot_now));
-                        const bool ranks =
-                            nplain == 0 &&
-                            (double)(got + 1) * sizeof(int2) < 0.25 * (double)free_now;
-                        gedges = S.get<int2>(got + 1);
-                        gedist = S.get<float>(got + 1);
-                        if (ranks)
-                            G.erank = S.get<int2>(got + 1);
-                        // slot per survivor: holes where it is no edge
-                        survivors_launch(M, P, G, got, gedges, gedist, o, s);
-                        ngedges = got;
-                    }
+                    // with no plain tiles in the query every CSR entry
+                    // comes from a survivor: keep the ranks its degree
+                    // counters return and place it without cursors
+                    // (measured at C2: 2.2 ms faster at ~53 survivors per
+                    // point, 15 ms at ~350), while the ranks take under a
+                    // quarter of the free device memory
+                    size_t free_now = 0, tot_now = 0;
+                    FNN_HIP(hipMemGetInfo(&free_now, &tot_now));
+                    const bool ranks =
+                        nplain == 0 &&
+                        (double)(got + 1) * sizeof(int2) < 0.25 * (double)free_now;
+                    gedges = S.get<int2>(got + 1);
+                    gedist = S.get<float>(got + 1);
+                    if (ranks)
+                        G.erank = S.get<int2>(got + 1);
+                    // slot per survivor: holes where it is no edge
+                    survivors_launch(M, P, G, got, gedges, gedist, o, s);
+                    ngedges = got;
                     break;
                 }
                 S.release(G.surv);
@@ -2168,9 +2162,7 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
             FNN_LAUNCH(k_cursor_init, dim3(grid_for(n, 256)), dim3(256), 0, s,
                        C->row_ptr, n, o.cursor);
             if (nnz > 0) {
-                if (G.degp)
-                    edges_scatter_ham(gedges, ngedges, P, T->perm, o, s);
-                else if (use_gram)
+                if (use_gram)
                     edges_scatter(gedges, gedist, ngedges, true, o, s);
                 if (listed)
                     edges_scatter(o.elist, o.edist, nlisted, false, o, s);
@@ -2335,7 +2327,6 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     st.n = n;
     st.nodes = T->nnodes;
     st.packs = T->npacks;
-    hc0[3] += hc0[8] / 2;  // exact integer filter: its edges are its survivors
     st.tile_pairs = (int64_t)(hc0[0] + hc0[3]);
     st.fp64_rechecks = (int64_t)hc0[1];
     st.filter_pairs = (int64_t)hc0[2];
