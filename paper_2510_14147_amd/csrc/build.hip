@@ -2366,6 +2366,52 @@ __global__ void k_widen_peq(const uint64_t *__restrict__ in, int n, int sig_in, 
     }
 }
 
+__global__ void k_iota_from(int32_t *__restrict__ q, int n, int v0)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += gridDim.x * blockDim.x)
+        q[i] = v0 + i;
+}
+
+fnn_tree *rows_pair(const fnn_tree *A, const Pts &B, int nB, Scratch &S)
+{
+    hipStream_t s = S.stream();
+    fnn_tree *F = new fnn_tree();
+    try {
+        const int nA = (int)A->n, n = nA + nB;
+        F->metric = A->metric;
+        F->n = n;
+        F->dim = A->dim;
+        F->dp = A->dp;
+        F->opt = A->opt;
+        F->rect = nA;
+        F->cloud_off_h = {0, n};
+        F->cloud_src = {0};
+        auto cat = [&](const void *a, const void *b, size_t row_bytes) -> void * {
+            if (!a)
+                return nullptr;
+            char *d = (char *)F->own(row_bytes * (size_t)n);
+            FNN_HIP(hipMemcpyAsync(d, a, row_bytes * nA, hipMemcpyDeviceToDevice, s));
+            FNN_HIP(hipMemcpyAsync(d + row_bytes * nA, b, row_bytes * nB,
+                                   hipMemcpyDeviceToDevice, s));
+            return d;
+        };
+        F->x = (float *)cat(A->x, B.x, sizeof(float) * A->dp);
+        F->xn = (float *)cat(A->xn, B.xn, sizeof(float) * A->dp);
+        F->h = (uint64_t *)cat(A->h, B.h, sizeof(uint64_t) * A->dp);
+        F->perm = (int32_t *)F->own(sizeof(int32_t) * n);
+        FNN_HIP(hipMemcpyAsync(F->perm, A->perm, sizeof(int32_t) * nA,
+                               hipMemcpyDeviceToDevice, s));
+        FNN_LAUNCH(k_iota_from, dim3(grid_cap(nB, 256, 4096)), dim3(256), 0, s, F->perm + nA,
+                   nB, nA);
+        return F;
+    } catch (...) {
+        (void)hipStreamSynchronize(s);
+        delete F;
+        throw;
+    }
+}
+
 fnn_tree *forest_pair(const fnn_tree *A, const fnn_tree *B, Scratch &S)
 {
     hipStream_t s = S.stream();

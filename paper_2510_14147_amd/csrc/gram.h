@@ -87,6 +87,9 @@ struct GramArgs {
     // consecutive; upk 0: packs from q_pb / q_pe and the list
     int upk, uoff;
     int nq;    // rows of q
+    // bichromatic rectangle: the result holds only the rows of the points
+    // with ids row0 and up (one of every pair); -1: both endpoints'
+    int row0;
     int kmax;  // Hamming codes: the largest floor(eps) of the query
 };
 
@@ -106,11 +109,11 @@ void survivors_launch(int metric, const Pts &P, const GramArgs &G,
 void edges_scatter(const int2 *edges, const float *edist, long long ne, bool both,
                    const TileOut &o, hipStream_t s);
 // Decided survivors into the CSR without cursors: edge i goes to slots
-// row_ptr[a] + ranks[i].x of row a and row_ptr[b] + ranks[i].y of row b, the
-// ranks its degree counters returned (each in [0, degree), so the rows
-// fill exactly); a rank past its row sets ERR_INDEX.
+// row_ptr[a] + ranks[i].x of row a and (both) row_ptr[b] + ranks[i].y of row
+// b, the ranks its degree counters returned (each in [0, degree), so the
+// rows fill exactly); a rank past its row sets ERR_INDEX.
 void edges_place(const int2 *edges, const float *edist, const int2 *erank, long long ne,
-                 const int64_t *row_ptr, const TileOut &o, hipStream_t s);
+                 bool both, const int64_t *row_ptr, const TileOut &o, hipStream_t s);
 // 2 c1 mean|x - mu|^2 / t2min for the BF16 filter (mu per cloud): how much
 // its rounding margin widens the test against the smallest squared
 // threshold; small values mean a selective filter.
@@ -126,9 +129,22 @@ struct GramPre {
 double gram_margin_ratio(const fnn_tree *T, double t2min, int prec, Scratch &S,
                          GramPre *pre = nullptr);
 
+// The same from a given mean |x - mu|^2.
+double gram_margin_of(double mean, double t2min, int prec, int dp, int d);
+
+// Milliseconds that screening one pair of a large closed-form list takes
+// (measured over 2e10 to 5e11 pairs: the narrow kernel at 16 and 32
+// coordinates, the staged one at 112; rows above 32 coordinates count as
+// staged although a projection may make them narrow; codes by whether the
+// early test on two words applies).
+double gram_pair_ms(int metric, int dp, double kmax);
+
 // True when no query pack exceeds the filter's tile height (the work list
 // of every pack pair then exists in closed form).
 bool gram_packs_fit(const fnn_tree *T, Scratch &S);
+
+// True when the rectangle of na rows against nb has a work list.
+bool gram_rect_fits(int64_t na, int64_t nb);
 
 // Squared threshold of the filter's key (eps^2, or the squared chord of
 // the angular threshold).

@@ -698,6 +698,36 @@ __global__ void k_dense_units(const int32_t *__restrict__ ubeg,
         }
 }
 
+// The closed-form list of a rectangle: every pack of the first na rows
+// (packs 0 .. npa - 1, padded with empty ones to whole groups) against every
+// pack of the nb rows after them (packs npa and up), in the same order of
+// units: by run of B packs, then by group.
+__global__ void k_rect_packs(int na, int nb, int npa, int np, int32_t *__restrict__ pb,
+                             int32_t *__restrict__ pe)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < np;
+         i += gridDim.x * blockDim.x) {
+        const int o = i < npa ? 0 : na, m = i < npa ? na : nb, k = i < npa ? i : i - npa;
+        pb[i] = o + min(k * GP, m);
+        pe[i] = o + min(k * GP + GP, m);
+    }
+}
+
+__global__ void k_rect_units(int ng, int npb, int R, int npa, int nu,
+                             int32_t *__restrict__ ubeg, int32_t *__restrict__ ug,
+                             int32_t *__restrict__ ulo)
+{
+    for (int u = blockIdx.x * blockDim.x + threadIdx.x; u < nu;
+         u += gridDim.x * blockDim.x) {
+        const int k = u / ng, g = u - k * ng;
+        ubeg[u] = k * R * ng + g * min(R, npb - k * R);
+        ug[u] = g;
+        ulo[u] = npa + k * R;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        ubeg[nu] = ng * npb;
+}
+
 // After sorting by (group, B): mark the first of each distinct pair.
 __global__ void k_uniq_flags(const uint32_t *__restrict__ g,
                              const uint32_t *__restrict__ b, long long m,
@@ -2004,7 +2034,14 @@ k_survive(Pts P, GramArgs G, long long ns, int2 *__restrict__ edges,
                 }
                 oi = G.perm[pi];
                 oj = G.perm[pj];
-                if (G.erank) {
+                if (G.row0 >= 0) {
+                    // only the query's row exists (ids row0 and up): it
+                    // comes first
+                    const int q = max(oi, oj);
+                    oj = min(oi, oj);
+                    oi = q - G.row0;
+                    rk.x = atomicAdd(&out.deg[oi], 1);
+                } else if (G.erank) {
                     rk.y = atomicAdd(&out.deg[oj], 1);
                 } else {
                     atomicAdd(&out.deg[oi], 1);
@@ -2014,7 +2051,7 @@ k_survive(Pts P, GramArgs G, long long ns, int2 *__restrict__ edges,
         }
         // the first endpoint's rank: the list holds a row's survivors of a
         // block in runs, so one returning atomic serves a run
-        if (G.erank)
+        if (G.erank && G.row0 < 0)
             rk.x = claim_run(out.deg, edge ? oi : -1);
         // the survivor's own slot: an edge, or a hole (-1, -1) that the
         // scatter skips (no shared counter to contend on)
@@ -2079,7 +2116,7 @@ __global__ void k_edges_scatter(const int2 *__restrict__ edges,
 
 __global__ void k_edges_place(const int2 *__restrict__ edges,
                               const float *__restrict__ edist,
-                              const int2 *__restrict__ erank, long long ne,
+                              const int2 *__restrict__ erank, long long ne, bool both,
                               const int64_t *__restrict__ row_ptr, TileOut out)
 {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < ne;
@@ -2090,6 +2127,16 @@ __global__ void k_edges_place(const int2 *__restrict__ edges,
         const int2 r = erank[i];
         const float d = edist[i];
         const int64_t a0 = row_ptr[e.x], a1 = row_ptr[e.x + 1];
+        if (!both) {
+            const int64_t s1 = a0 + r.x;
+            if (r.x >= 0 && s1 < a1) {
+                out.col[s1] = e.y;
+                out.dist[s1] = d;
+            } else {
+                atomicOr(out.err, ERR_INDEX);
+            }
+            continue;
+        }
         const int64_t b0 = row_ptr[e.y], b1 = row_ptr[e.y + 1];
         const int64_t s1 = a0 + r.x, s2 = b0 + r.y;
         if (r.x >= 0 && r.y >= 0 && s1 < a1 && s2 < b1) {
@@ -2104,12 +2151,12 @@ __global__ void k_edges_place(const int2 *__restrict__ edges,
 }
 
 void edges_place(const int2 *edges, const float *edist, const int2 *erank, long long ne,
-                 const int64_t *row_ptr, const TileOut &o, hipStream_t s)
+                 bool both, const int64_t *row_ptr, const TileOut &o, hipStream_t s)
 {
     if (ne <= 0)
         return;
     FNN_LAUNCH(k_edges_place, dim3(grid_cap(ne, 256, 65536)), dim3(256), 0, s, edges, edist,
-               erank, ne, row_ptr, o);
+               erank, ne, both, row_ptr, o);
 }
 
 void survivors_launch(int metric, const Pts &P, const GramArgs &G,
@@ -2510,6 +2557,11 @@ double gram_margin_ratio(const fnn_tree *T, double t2min, int prec, Scratch &S,
         pre->inv = inv;
         pre->have = true;
     }
+    return gram_margin_of(mean, t2min, prec, dp, d);
+}
+
+double gram_margin_of(double mean, double t2min, int prec, int dp, int d)
+{
     const double u32 = 1.0 / 16777216.0;
     const int kq = (int)cdiv(dp, 16) * 16;
     const double u = prec == FNN_PREC_FP16 ? 1.0 / 2048.0 : 1.0 / 256.0;
@@ -2664,6 +2716,49 @@ double gram_t2(int metric, double eps, const Thr &E)
     return metric == M_L2 ? eps * eps : 2.0 - 2.0 * E.p64;
 }
 
+double gram_pair_ms(int metric, int dp, double kmax)
+{
+    if (metric == M_HAM)
+        return dp <= 2 || kmax <= 36 ? 5.7e-11 : 1.15e-10;
+    return dp <= 16 ? 4.6e-11 : dp <= 32 ? 8.5e-11 : 2.5e-10;
+}
+
+bool gram_rect_fits(int64_t na, int64_t nb)
+{
+    return cdiv(cdiv(na, GP), GW) * cdiv(nb, GP) < INT32_MAX;
+}
+
+// Work list of a bichromatic rectangle (T->rect).
+static void rect_list(const fnn_tree *T, Scratch &S, GramArgs &G)
+{
+    hipStream_t s = S.stream();
+    const int na = (int)T->rect, nb = (int)(T->n - T->rect);
+    const int ng = (int)cdiv(cdiv(na, GP), GW), npa = ng * GW, npb = (int)cdiv(nb, GP);
+    const int np = npa + npb, R = UNIT_MAX;
+    const int nu = ng * (int)cdiv(npb, R);
+    const int64_t m = (int64_t)ng * npb;
+    int32_t *pb = S.get<int32_t>(np), *pe = S.get<int32_t>(np);
+    int32_t *lg = S.get<int32_t>(m + 1), *lb = S.get<int32_t>(m + 1);
+    int32_t *ubeg = S.get<int32_t>(nu + 1), *ug = S.get<int32_t>(nu), *ulo = S.get<int32_t>(nu);
+    FNN_LAUNCH(k_rect_packs, dim3(grid_for(np, 256)), dim3(256), 0, s, na, nb, npa, np, pb, pe);
+    FNN_LAUNCH(k_rect_units, dim3(grid_for(nu, 256)), dim3(256), 0, s, ng, npb, R, npa, nu,
+               ubeg, ug, ulo);
+    FNN_LAUNCH(k_dense_units, dim3(grid_cap(nu, 4, 16384)), dim3(256), 0, s, ubeg, ug, ulo, nu,
+               lg, lb);
+    G.q_pb = pb;
+    G.q_pe = pe;
+    G.nn = 0;
+    G.npacks = np;
+    G.upk = (int)T->n;
+    G.uoff = na - npa * GP;
+    G.lg = lg;
+    G.lb = lb;
+    G.ubeg = ubeg;
+    G.nunits = nu;
+    G.nlist = (int)m;
+    G.dense_pairs = (long long)na * nb;
+}
+
 // Quantised copy + per-point terms, and the MFMA work lists, for one query.
 void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &E,
                   double t2min, const int2 *inter, long long ninter, Scratch &S,
@@ -2687,6 +2782,12 @@ void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &
     G.E = E;
     G.q_pb = T->q_pt_begin;
     G.q_pe = T->q_pt_end;
+    if (T->rect >= 0) {
+        *rest = nullptr;
+        *nrest = 0;
+        rect_list(T, S, G);
+        return;
+    }
 
     const int nn = (int)T->nnodes;
     const int npk = (int)T->npacks;

@@ -91,6 +91,60 @@ __global__ void k_prune_sample(Pts P, QView Q, Prune pr, int npk, int ns,
         atomicAdd(pruned, c);
 }
 
+// The same sample for query rows before they have a tree: (data pack, query
+// row) pairs, the row as a ball of radius 0 (a pack of queries prunes no
+// more).  q: the caller's rows (a row that is no number counts as pruned).
+// *sum: the sampled pairs' squared distances (vector metrics).
+template <int M>
+__global__ void k_prune_rows(Pts P, QView Q, Prune pr, int npk, const void *__restrict__ q,
+                             long long nq, int ns, unsigned long long *__restrict__ pruned,
+                             float *__restrict__ sum)
+{
+    unsigned long long c = 0;
+    float m = 0.f;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ns;
+         i += gridDim.x * blockDim.x) {
+        unsigned h = (unsigned)i * 0x9E3779B1u + 0x7F4A7C15u;
+        h ^= h >> 16;
+        h *= 0x85EBCA6Bu;
+        h ^= h >> 13;
+        const unsigned h2 = h * 0xC2B2AE35u ^ (h >> 16);
+        const int a = Q.nn + (int)(h % (unsigned)npk);
+        const long long b = (long long)(h2 % (unsigned long long)nq);
+        const int cp = Q.cpos[a];
+        float d;
+        if constexpr (M == M_HAM) {
+            d = (float)ham_words(P.h + (size_t)cp * P.dp, (const uint64_t *)q + (size_t)b * P.dp,
+                                 P.dp);
+        } else {
+            const float *x = (M == M_ANG ? P.xn : P.x) + (size_t)cp * P.dp;
+            const float *y = (const float *)q + (size_t)b * P.dim;
+            float inv = 1.f;
+            if (M == M_ANG) {
+                float n2 = 0.f;
+                for (int k = 0; k < P.dim; ++k)
+                    n2 = fmaf(y[k], y[k], n2);
+                inv = rsqrtf(n2);
+            }
+            float s2 = 0.f;
+            for (int k = 0; k < P.dim; ++k) {
+                const float t = x[k] - y[k] * inv;
+                s2 = fmaf(t, t, s2);
+            }
+            d = key_to_dist<M>(s2);
+            m += s2;
+        }
+        c += d <= (Q.rad[a] + pr.eps) * (1.f + pr.rel) + pr.abs_ ? 0 : 1;
+    }
+    c = wave_sum(c);
+    m = wave_sum(m);
+    if ((threadIdx.x & (WAVE - 1)) == 0) {
+        if (c)
+            atomicAdd(pruned, c);
+        atomicAdd(sum, m);
+    }
+}
+
 // ------------------------------------------------------------ traversal --
 
 struct Emit {
@@ -882,12 +936,12 @@ k_tile(Pts P, const int2 *__restrict__ inter, long long ninter,
 
 // Decided survivors into their CSR slots as packed entries (column << 32 |
 // distance bits, the row sort's key): edge i (input ids a, b) goes to slot
-// row_ptr[a] + rank.x and row_ptr[b] + rank.y, one 8-byte store each, so the
+// row_ptr[a] + rank.x and (both) row_ptr[b] + rank.y, one 8-byte store each, so the
 // scattered stores are half as many as with separate column and distance
 // stores; the row sort writes col and dist.  A rank past its row sets
 // ERR_INDEX.
 __global__ void k_place_packed(const int2 *__restrict__ edges, const float *__restrict__ edist,
-                               const int2 *__restrict__ erank, long long ne,
+                               const int2 *__restrict__ erank, long long ne, bool both,
                                const int64_t *__restrict__ row_ptr,
                                unsigned long long *__restrict__ pk, int *__restrict__ err)
 {
@@ -899,6 +953,14 @@ __global__ void k_place_packed(const int2 *__restrict__ edges, const float *__re
         const int2 r = erank[i];
         const uint32_t d = __float_as_uint(edist[i]);
         const int64_t a0 = row_ptr[e.x], a1 = row_ptr[e.x + 1];
+        if (!both) {
+            const int64_t s1 = a0 + r.x;
+            if (r.x >= 0 && s1 < a1)
+                pk[s1] = ((unsigned long long)(uint32_t)e.y << 32) | d;
+            else
+                atomicOr(err, ERR_INDEX);
+            continue;
+        }
         const int64_t b0 = row_ptr[e.y], b1 = row_ptr[e.y + 1];
         const int64_t s1 = a0 + r.x, s2 = b0 + r.y;
         if (r.x >= 0 && r.y >= 0 && s1 < a1 && s2 < b1) {
@@ -1824,8 +1886,55 @@ struct Learned {
 
 const float *cost_model_device();
 
+// What a traversal costs beside the filter, milliseconds: launches and host
+// reads, per point (its levels' tests), and per pack pair it keeps
+// (expansion, two radix sorts, unique groups).  Measured: 20K to 60K points
+// in 20 clusters, 5 % kept, 0.4 to 0.7 ms; 200K points 1.3 to 2.1 ms; 988258
+// codes, 76.7M pairs kept, 30 ms.
+constexpr double TRAV_MS = 0.4, TRAV_POINT_MS = 4e-6, TRAV_PAIR_MS = 4.2e-7;
+// A bichromatic query's general path builds a tree over the queries and
+// joins two trees first: about 1.2 ms of launches and host reads more.
+constexpr double QUERY_TREE_MS = 1.2;
+
+// Device view of a tree's points (tree order).
+static Pts tree_points(const fnn_tree *T)
+{
+    Pts P{};
+    P.metric = T->metric;
+    P.n = (int)T->n;
+    P.dim = T->dim;
+    P.dp = T->dp;
+    P.W = T->W;
+    P.sigma = T->sigma;
+    P.x = T->x;
+    P.xn = T->xn;
+    P.h = T->h;
+    P.s = T->s;
+    P.len = T->len;
+    P.peq = T->peq;
+    return P;
+}
+
+// Slack of the pruning test for the tree's metric and row length.
+static Prune prune_slack(const fnn_tree *T)
+{
+    Prune pr{};
+    const double u = 1.0 / 16777216.0;
+    pr.rel = (float)std::max(1e-4, 8.0 * (T->dp + 4) * u);
+    pr.abs_ = T->metric == M_ANG ? 1e-5f : (T->metric == M_L2 ? 1e-30f : 0.f);
+    return pr;
+}
+
+// eps as the pruning test's distance.
+static float prune_eps(int metric, double eps, const Thr &E)
+{
+    if (metric == M_HAM || metric == M_LEV)
+        return E.lo;
+    return metric == M_ANG && eps >= M_PI ? 4.f : (float)eps;  // 4: every pair may touch
+}
+
 template <int M>
-static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
+static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                            const Options &opt, fnn_csr *C, fnn_stats &st,
                            Scratch &S, float **trace_feat, float **trace_targ)
 {
@@ -1839,19 +1948,10 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     Timer tm(s);
     tm.mark();  // 0
 
-    Pts P{};
-    P.metric = M;
-    P.n = n;
-    P.dim = T->dim;
-    P.dp = T->dp;
-    P.W = T->W;
-    P.sigma = T->sigma;
-    P.x = T->x;
-    P.xn = T->xn;
-    P.h = T->h;
-    P.s = T->s;
-    P.len = T->len;
-    P.peq = T->peq;
+    const Pts P = tree_points(T);
+    // rows of the result: every point's, or a bichromatic rectangle's queries'
+    const bool rect = T->rect >= 0;
+    const int nr = rect ? (int)(T->n - T->rect) : n;
 
     QView Q{T->q_center_pos, T->q_pt_begin, T->q_pt_end, T->q_kbeg,
             T->q_kcnt,       T->q_kids,     T->q_radius, (int)T->nnodes};
@@ -1862,9 +1962,7 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         const double e = epsv[c];
         CloudThr &t = ct_h[c];
         t.E = make_thr_eps(M, T->dp, e);
-        t.peps = (M == M_HAM || M == M_LEV) ? t.E.lo : (float)e;
-        if (M == M_ANG && e >= M_PI)
-            t.peps = 4.f;  // every pair may touch
+        t.peps = prune_eps(M, e, t.E);
         t.e2f = gram_eps2(M, e, t.E);
         t.feps = std::max(t.peps, 0.5f);
         t.pad_ = 0.f;
@@ -1874,10 +1972,8 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                            hipMemcpyHostToDevice, s));
     const Thr E = ct_h[0].E;
     const double eps = epsv[0];
-    Prune pr;
     const double u = 1.0 / 16777216.0;
-    pr.rel = (float)std::max(1e-4, 8.0 * (T->dp + 4) * u);
-    pr.abs_ = M == M_ANG ? 1e-5f : (M == M_L2 ? 1e-30f : 0.f);
+    Prune pr = prune_slack(T);
     pr.eps = ct_h[0].peps;
     pr.ct = ncl > 1 ? ct_d : nullptr;
     pr.pcl = ncl > 1 ? T->pcl : nullptr;
@@ -1922,30 +2018,38 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     const bool use_gram = ((M == M_L2 || M == M_ANG) && prec != FNN_PREC_FP32) ||
                           (M == M_HAM && prec == FNN_PREC_I8);
 
+    if (rect && !use_gram)
+        return false;  // the caller builds a query tree instead
+
     // ---- traversal ------------------------------------------------------
-    // Where the traversal's own pack-level test would keep nearly every pack
-    // pair (high-dimensional data), the MFMA filter takes every pair from a
-    // closed-form list instead; a seeded sample of pack pairs decides.  Any
-    // pair set that contains the needed ones gives the exact graph.
+    // The filter may take every pair from a closed-form list instead of the
+    // traversal's (any pair set that contains the needed ones gives the
+    // exact graph): at once while the whole list costs no more than a
+    // traversal's launches and host reads, else where a seeded sample of
+    // pack pairs under the traversal's own test says that what it could
+    // prune is worth less than itself.
     int2 *inter = nullptr;
     long long ninter = 0;
-    bool dense = false;
-    if (use_gram && ncl == 1 && !opt.trace && T->npacks >= 256) {
-        const int ns = 8192;
-        unsigned long long *pc = S.get<unsigned long long>(1);
-        fill(pc, 0ull, 1, s);
-        FNN_LAUNCH((k_prune_sample<M>), dim3(ns / 256), dim3(256), 0, s, P, Q, pr,
-                   (int)T->npacks, ns, pc);
-        const unsigned long long pruned = read_scalar(pc, s);
-        // vector metrics: at most 1 % prunable.  Codes: screening a pack pair
-        // costs far less than carrying it through the traversal and its
-        // sorted lists (988258 codes with 27 % of the pairs kept: 28 ms
-        // against 30 ms of traversal and 27 ms of filter), so unless seven
-        // eighths could be pruned
-        dense = M == M_HAM ? pruned * 8 <= 7ull * ns : pruned * 100 <= (unsigned long long)ns;
-        st.traverse_tests = ns;
+    bool dense = rect;
+    if (!rect && use_gram && ncl == 1 && !opt.trace && T->npacks > 0) {
+        const double pairs = 0.5 * n * (double)n, c = gram_pair_ms(M, T->dp, E.lo);
+        const double fixed = TRAV_MS + TRAV_POINT_MS * n;
+        dense = pairs * c <= fixed;
+        if (!dense) {
+            const int ns = 8192;
+            unsigned long long *pc = S.get<unsigned long long>(1);
+            fill(pc, 0ull, 1, s);
+            FNN_LAUNCH((k_prune_sample<M>), dim3(ns / 256), dim3(256), 0, s, P, Q, pr,
+                       (int)T->npacks, ns, pc);
+            const double gone = (double)read_scalar(pc, s) / ns;
+            const double kept = 0.5 * (1.0 - gone) * T->npacks * (double)T->npacks;
+            dense = gone * pairs * c <= fixed + TRAV_PAIR_MS * kept;
+            st.traverse_tests = ns;
+        }
     }
-    if (dense) {
+    if (rect) {
+        ninter = 0;  // the list is the rectangle (gram_prepare)
+    } else if (dense) {
         ninter = (long long)T->npacks * (T->npacks + 1) / 2;
         st.interactions = ninter;
     } else {
@@ -1959,6 +2063,7 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     // of <= 256 bits) ------------------------------------------------------
     GramArgs G{};
     G.cross = T->cross_a >= 0;
+    G.row0 = rect ? (int)T->rect : -1;
     int2 *plain = inter;
     long long nplain = ninter;
     if constexpr (M == M_L2 || M == M_ANG || M == M_HAM) {
@@ -2001,8 +2106,8 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     int *bad = S.get<int>(1);
     fill(bad, 0, 1, s);
     o.err = bad;
-    C->n = n;
-    C->row_ptr = (int64_t *)out_alloc(sizeof(int64_t) * ((size_t)n + 1));
+    C->n = nr;
+    C->row_ptr = (int64_t *)out_alloc(sizeof(int64_t) * ((size_t)nr + 1));
     int64_t nnz = 0;
     int64_t novf = 0;
     unsigned long long *packed = nullptr;  // packed CSR entries (see k_place_packed)
@@ -2010,8 +2115,8 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
 
     if (use_gram || !learned) {
         // ---- count pass (plain tiles) / filter + exact survivors (MFMA) ---
-        o.deg = S.get<int32_t>(n);
-        fill(o.deg, 0, n, s);
+        o.deg = S.get<int32_t>(nr);
+        fill(o.deg, 0, nr, s);
         int2 *gedges = nullptr;
         float *gedist = nullptr;
         long long ngedges = 0;
@@ -2025,7 +2130,7 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
             size_t freeb = 0, totb = 0;
             FNN_HIP(hipMemGetInfo(&freeb, &totb));
             const long long room = (long long)(freeb / 16 / sizeof(int2));
-            long long cap = std::max({1ll << 24, 64ll * n, std::min(room, 512ll * n)});
+            long long cap = std::max({1ll << 24, 64ll * nr, std::min(room, 512ll * nr)});
             if (learned) {
                 // predicted ordered edges / 2, times the filter's survivor
                 // factor (BF16 ~1.5, FP8 tens on high-dimensional data)
@@ -2044,7 +2149,8 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                 cap = std::max<long long>(1ll << 20, (long long)(0.5 * hacc[1] * fac));
             }
             if (opt.validate)
-                cap = std::max<long long>(cap, (long long)n * (n - 1) / 2 + 1);
+                cap = std::max<long long>(cap, rect ? T->rect * nr + 1
+                                                   : (long long)n * (n - 1) / 2 + 1);
             if (opt.list_cap > 0)
                 cap = opt.list_cap;
             for (int attempt = 0;; ++attempt) {
@@ -2126,8 +2232,8 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         }
         tm.mark();  // 3
 
-        scan_i32_to_i64(o.deg, C->row_ptr, n, S);
-        nnz = read_scalar(C->row_ptr + n, s);
+        scan_i32_to_i64(o.deg, C->row_ptr, nr, S);
+        nnz = read_scalar(C->row_ptr + nr, s);
         C->nnz = nnz;
         FNN_HIP(hipMemcpy(hc0, cnt, sizeof hc0, hipMemcpyDeviceToHost));
         C->col = (int32_t *)out_alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1));
@@ -2150,28 +2256,28 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                     packed = S.get<unsigned long long>(nnz);
                     st.fill_path = 2;
                     FNN_LAUNCH(k_place_packed, dim3(grid_cap(ngedges, 256, 65536)), dim3(256),
-                               0, s, gedges, gedist, G.erank, ngedges, C->row_ptr, packed,
+                               0, s, gedges, gedist, G.erank, ngedges, !rect, C->row_ptr, packed,
                                o.err);
                 } else {
-                    edges_place(gedges, gedist, G.erank, ngedges, C->row_ptr, o, s);
+                    edges_place(gedges, gedist, G.erank, ngedges, !rect, C->row_ptr, o, s);
                     st.fill_path = 1;
                 }
             }
         } else {
-            o.cursor = S.get<unsigned long long>(n);
-            FNN_LAUNCH(k_cursor_init, dim3(grid_for(n, 256)), dim3(256), 0, s,
-                       C->row_ptr, n, o.cursor);
+            o.cursor = S.get<unsigned long long>(nr);
+            FNN_LAUNCH(k_cursor_init, dim3(grid_for(nr, 256)), dim3(256), 0, s,
+                       C->row_ptr, nr, o.cursor);
             if (nnz > 0) {
                 if (use_gram)
-                    edges_scatter(gedges, gedist, ngedges, true, o, s);
+                    edges_scatter(gedges, gedist, ngedges, !rect, o, s);
                 if (listed)
                     edges_scatter(o.elist, o.edist, nlisted, false, o, s);
                 else
                     launch_tiles<M>(TILE_FILL, P, plain, nplain, T, E, ct_d, fp64_dist,
                                     o, s);
             }
-            FNN_LAUNCH(k_cursor_check_rows, dim3(grid_for(n, 256)), dim3(256), 0, s,
-                       C->row_ptr, n, o.cursor, (const int32_t *)nullptr, bad);
+            FNN_LAUNCH(k_cursor_check_rows, dim3(grid_for(nr, 256)), dim3(256), 0, s,
+                       C->row_ptr, nr, o.cursor, (const int32_t *)nullptr, bad);
         }
         tm.mark();  // 5
     } else {
@@ -2293,7 +2399,7 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     }
 
     // ---- per-row sort ---------------------------------------------------
-    sort_csr_rows(C->row_ptr, n, C->col, C->dist, nnz, S, packed);
+    sort_csr_rows(C->row_ptr, nr, C->col, C->dist, nnz, S, packed);
     tm.mark();  // 6
 
     // ---- trace targets, prediction error ---------------------------------
@@ -2347,25 +2453,74 @@ static void eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     st.sort_ms = tm.ms(5, 6);
     st.tile_ms = st.count_ms + st.fill_ms;
     st.total_ms = tm.ms(0, 6);
+    return true;
 }
 
-void eps_graph(const fnn_tree *T, const double *eps, const Options &opt,
+bool eps_graph(const fnn_tree *T, const double *eps, const Options &opt,
                fnn_csr *C, fnn_stats &st, Scratch &S, float **tf, float **tt)
 {
     switch (T->metric) {
     case M_L2:
-        eps_graph_impl<M_L2>(T, eps, opt, C, st, S, tf, tt);
-        break;
+        return eps_graph_impl<M_L2>(T, eps, opt, C, st, S, tf, tt);
     case M_ANG:
-        eps_graph_impl<M_ANG>(T, eps, opt, C, st, S, tf, tt);
-        break;
+        return eps_graph_impl<M_ANG>(T, eps, opt, C, st, S, tf, tt);
     case M_HAM:
-        eps_graph_impl<M_HAM>(T, eps, opt, C, st, S, tf, tt);
-        break;
+        return eps_graph_impl<M_HAM>(T, eps, opt, C, st, S, tf, tt);
     default:
-        eps_graph_impl<M_LEV>(T, eps, opt, C, st, S, tf, tt);
-        break;
+        return eps_graph_impl<M_LEV>(T, eps, opt, C, st, S, tf, tt);
     }
+}
+
+bool query_screens_all(const fnn_tree *T, const void *q, int64_t nq, double eps,
+                       const Options &opt, Scratch &S)
+{
+    const int M = T->metric;
+    const bool vec = M == M_L2 || M == M_ANG;
+    // the filters' formats (the automatic rule may still choose none)
+    const bool can = vec ? opt.precision != FNN_PREC_FP32 && opt.precision != FNN_PREC_I8 &&
+                               T->dp <= 128 &&
+                               (opt.precision != FNN_PREC_AUTO || T->dim >= 16)
+                         : M == M_HAM && T->dp <= 4 &&
+                               (opt.precision == FNN_PREC_I8 || opt.precision == FNN_PREC_AUTO);
+    if (!can || T->npacks <= 0 || !gram_rect_fits(T->n, nq))
+        return false;
+    hipStream_t s = S.stream();
+    const Thr E = make_thr_eps(M, T->dp, eps);
+    Prune pr = prune_slack(T);
+    pr.eps = prune_eps(M, eps, E);
+    pr.ct = nullptr;
+    pr.pcl = nullptr;
+    const QView Q{T->q_center_pos, T->q_pt_begin, T->q_pt_end, T->q_kbeg,
+                  T->q_kcnt,       T->q_kids,     T->q_radius, (int)T->nnodes};
+    const int ns = 8192;
+    unsigned long long *pc = S.get<unsigned long long>(2);  // pruned; sum (float)
+    fill(pc, 0ull, 2, s);
+    auto go = [&](auto m) {
+        FNN_LAUNCH((k_prune_rows<decltype(m)::value>), dim3(ns / 256), dim3(256), 0, s,
+                   tree_points(T), Q, pr, (int)T->npacks, q, (long long)nq, ns, pc,
+                   reinterpret_cast<float *>(pc + 1));
+    };
+    if (M == M_L2)
+        go(std::integral_constant<int, M_L2>{});
+    else if (M == M_ANG)
+        go(std::integral_constant<int, M_ANG>{});
+    else
+        go(std::integral_constant<int, M_HAM>{});
+    unsigned long long h[2];
+    FNN_HIP(hipMemcpyAsync(h, pc, sizeof h, hipMemcpyDeviceToHost, s));
+    FNN_HIP(hipStreamSynchronize(s));
+    float sum;
+    memcpy(&sum, &h[1], sizeof sum);
+    // the automatic precision would most likely choose the plain tiles: half
+    // the mean squared distance of random pairs is the mean |x - mu|^2
+    if (vec && opt.precision == FNN_PREC_AUTO &&
+        !(gram_margin_of(0.5 * sum / ns, gram_t2(M, eps, E), FNN_PREC_FP16, T->dp, T->dim) <=
+          0.5))
+        return false;
+    const double gone = (double)h[0] / ns, pairs = (double)T->n * (double)nq;
+    const double kept = (1.0 - gone) * T->npacks * (nq / 40.0 + 1.0);
+    return gone * pairs * gram_pair_ms(M, T->dp, E.lo) <=
+           QUERY_TREE_MS + TRAV_MS + TRAV_POINT_MS * (double)nq + TRAV_PAIR_MS * kept;
 }
 
 }  // namespace fnn

@@ -96,6 +96,10 @@ struct fnn_tree {
     // two-tree forest of a bichromatic query: the query-tree roots of the
     // two clouds, whose pair seeds the traversal (-1 otherwise)
     int32_t cross_a = -1, cross_b = -1;
+    // rows of a bichromatic query that screens every pair: the data tree's
+    // rows, then the query rows from this position on (-1 otherwise); no
+    // vertices
+    int64_t rect = -1;
 
     int depth = 0;
     fnn_stats stats{};
