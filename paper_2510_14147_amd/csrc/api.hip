@@ -93,6 +93,7 @@ Options read_options(const fnn_options *o)
         r.slack_pct = o->slack_pct < -90 ? -90 : o->slack_pct;
     if (o->graph_passes < 0)
         fail(FNN_EINVAL, "negative graph_passes");
+    r.graph_set = o->graph_passes != 0;
     if (o->graph_passes)
         r.graph_passes = o->graph_passes > 64 ? 64 : o->graph_passes;
     if (o->proj < -1 || o->proj > 128 || (o->proj > 0 && o->proj % 16))

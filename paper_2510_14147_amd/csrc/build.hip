@@ -533,7 +533,7 @@ template <int M>
 __global__ void __launch_bounds__(CH * UPD_W)
 k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
          const int32_t *__restrict__ ch_e, const int32_t *__restrict__ queue,
-         const int32_t *__restrict__ qlen, Hubs hb,
+         const int32_t *__restrict__ qlen, int32_t *__restrict__ qnext, Hubs hb,
          const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
          float *__restrict__ D, int32_t *__restrict__ L,
          const LevelTab *__restrict__ tab, float *__restrict__ cb_D,
@@ -550,6 +550,8 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
     // the queue lists the chunks of the hubs still active (device-resident
     // length, so passes need no host round trip)
     const int nq = *qlen;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *qnext = 0;  // this pass's selection appends to it
     for (int t0 = blockIdx.x * UPD_W; t0 < nq; t0 += gridDim.x * UPD_W) {
     const int t = t0 + w;
     const int c = t < nq ? queue[t] : 0;
@@ -704,7 +706,8 @@ template <int NW, int NB>
 __global__ void __launch_bounds__(CH *LEV_W)
 k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
              const int32_t *__restrict__ ch_e, const int32_t *__restrict__ queue,
-             const int32_t *__restrict__ qlen, Hubs hb, const int32_t *__restrict__ cent,
+             const int32_t *__restrict__ qlen, int32_t *__restrict__ qnext, Hubs hb,
+             const int32_t *__restrict__ cent,
              const int32_t *__restrict__ perm, float *__restrict__ D,
              int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
              float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax,
@@ -714,6 +717,8 @@ k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restric
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CH));
     const int lane = threadIdx.x % CH;
     const int nq = *qlen;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *qnext = 0;  // this pass's selection appends to it
     for (int t = blockIdx.x; t < nq; t += gridDim.x) {
         const int c = queue[t], h = ch_hub[c];
         if (!hb.act[h])
@@ -1511,7 +1516,51 @@ __global__ void k_forest_roots(int C, const int32_t *__restrict__ off,
     }
 }
 
+// Vertex 0 (level set unless it is a forest's virtual root, whose level is
+// the roots' maximum) and, with hub set, the first hub: the root itself.
+__global__ void k_root_vertex(NodeArrays nd, int set_level, int hub, int level, int cbeg,
+                              int ccnt, int n, float radius, Hubs hb, int32_t *__restrict__ cent)
+{
+    nd.center[0] = 0;
+    if (set_level)
+        nd.level[0] = level;
+    nd.cbeg[0] = cbeg;
+    nd.ccnt[0] = ccnt;
+    nd.pb[0] = 0;
+    nd.pe[0] = n;
+    nd.radius[0] = radius;
+    if (hub) {
+        hb.node[0] = 0;
+        hb.b[0] = 0;
+        hb.e[0] = n;
+        hb.lvl[0] = level;
+        hb.m[0] = hb.ma[0] = hb.act[0] = 1;
+        hb.cb[0] = hb.ce[0] = hb.kof[0] = 0;
+        cent[0] = 0;
+    }
+}
+
 // ------------------------------------------------------------ finalize ---
+
+// The vertex arrays and the permutation into the tree's own.
+__global__ void k_copy_nodes(NodeArrays a, int nn, const int32_t *__restrict__ perm, int n,
+                             NodeArrays o, int32_t *__restrict__ operm)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < max(nn, n);
+         i += gridDim.x * blockDim.x) {
+        if (i < nn) {
+            o.center[i] = a.center[i];
+            o.radius[i] = a.radius[i];
+            o.level[i] = a.level[i];
+            o.cbeg[i] = a.cbeg[i];
+            o.ccnt[i] = a.ccnt[i];
+            o.pb[i] = a.pb[i];
+            o.pe[i] = a.pe[i];
+        }
+        if (i < n)
+            operm[i] = perm[i];
+    }
+}
 
 __global__ void k_inverse(const int32_t *__restrict__ perm, int n,
                           int32_t *__restrict__ inv)
@@ -1879,11 +1928,12 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     // ---- ingest (input order) -------------------------------------------
     Pts P = ingest_impl<M>(T, points, S);
 
-    LevelTab htab;
-    make_level_table(M, T->dp, &htab);
+    // (pinned: the reads below wait for the copy before its next use)
+    static_assert(sizeof(LevelTab) <= HOST_WRITE, "level table fits the upload area");
+    LevelTab *htab = reinterpret_cast<LevelTab *>(host_stage() + HOST_READ);
+    make_level_table(M, T->dp, htab);
     LevelTab *tab = S.get<LevelTab>(1);
-    FNN_HIP(hipMemcpyAsync(tab, &htab, sizeof(LevelTab), hipMemcpyHostToDevice,
-                           st));
+    FNN_HIP(hipMemcpyAsync(tab, htab, sizeof(LevelTab), hipMemcpyHostToDevice, st));
 
     // ---- node arrays (at most 2n - 1 vertices) ------------------------------
     const size_t cap = 2 * (size_t)n + 2 + (size_t)T->ncloud;
@@ -1941,14 +1991,8 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
 
     int H = 0;
     int64_t node_count = 1;
-    // host staging values stay alive until the synchronisation below
-    int32_t zero = 0;
     const int NCL = T->ncloud;
-    std::vector<int32_t> offh;
-    int32_t v0[5] = {0, 1, NCL, 0, n};
-    const float inf = INFINITY;
-    int32_t h0[7] = {0, 0, 0, 0, 0, n, 0};
-    int32_t one[10] = {0, 0, n, 0, 1, 1, 1, 0, 0, 0};
+    std::vector<int32_t> offh;  // uploaded; alive until the reads below
     float r0 = 0.f;
     if (NCL > 1) {
         // ---- forest: one root per cloud, all clouds share every launch ---
@@ -1970,12 +2014,8 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
         FNN_LAUNCH(k_forest_roots, dim3(grid_for(NCL, 256)), dim3(256), 0, st,
                    NCL, off, ck, M, T->dp, T->opt.zeta, nd, cflag);
         // vertex 0: the virtual root (never part of a query pair)
-        FNN_HIP(hipMemcpyAsync(nd.center, &v0[0], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.cbeg, &v0[1], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.ccnt, &v0[2], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.pb, &v0[3], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.pe, &v0[4], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.radius, &inf, 4, hipMemcpyHostToDevice, st));
+        FNN_LAUNCH(k_root_vertex, dim3(1), dim3(1), 0, st, nd, 0, 0, 0, 1, NCL, n, INFINITY,
+                   hubs, cent);
         scan_i32(cflag, cscan, NCL, S);
         H = read_scalar(cscan + NCL, st);
         if (H > hub_cap)
@@ -1994,26 +2034,11 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
         memcpy(&r0key, &r0bits, sizeof r0key);
         r0 = radius_from_key(M, T->dp, r0key);
         const int l0 = r0 > 0.f ? level_of(r0) : 0;
-        h0[1] = l0;
-        one[3] = l0;
+        H = n > T->opt.zeta && r0key > 0.f ? 1 : 0;
         // root vertex: centre 0, all points
-        FNN_HIP(hipMemcpyAsync(nd.center, &h0[0], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.level, &h0[1], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.cbeg, &h0[2], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.ccnt, &h0[3], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.pb, &h0[4], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.pe, &h0[5], 4, hipMemcpyHostToDevice, st));
-        FNN_HIP(hipMemcpyAsync(nd.radius, &r0, 4, hipMemcpyHostToDevice, st));
-        if (n > T->opt.zeta && r0key > 0.f) {
-            int32_t *dst[10] = {hubs.node, hubs.b, hubs.e, hubs.lvl, hubs.m,
-                                hubs.ma, hubs.act, hubs.cb, hubs.ce, hubs.kof};
-            for (int i = 0; i < 10; ++i)
-                FNN_HIP(hipMemcpyAsync(dst[i], &one[i], 4, hipMemcpyHostToDevice, st));
-            FNN_HIP(hipMemcpyAsync(cent, &zero, 4, hipMemcpyHostToDevice, st));
-            H = 1;
-        }
+        FNN_LAUNCH(k_root_vertex, dim3(1), dim3(1), 0, st, nd, 1, H, l0, 0, 0, n, r0, hubs,
+                   cent);
     }
-    FNN_HIP(hipStreamSynchronize(st));
 
     int rounds = 0, passes = 0;
     while (H > 0) {
@@ -2023,10 +2048,9 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                            hubs.b, hubs.e, H, nch, hsz);
         scan_i32(nch, choff, H, S);
         scan_i32(hsz, itemoff, H, S);
-        int32_t tot[2];
-        FNN_HIP(hipMemcpyAsync(&tot[0], choff + H, 4, hipMemcpyDeviceToHost, st));
-        FNN_HIP(hipMemcpyAsync(&tot[1], itemoff + H, 4, hipMemcpyDeviceToHost, st));
-        FNN_HIP(hipStreamSynchronize(st));
+        int32_t tot[2] = {(int32_t)cdiv(n, CH), n};  // the root alone
+        if (rounds > 1 || NCL > 1)
+            Readback(st).add(&tot[0], choff + H).add(&tot[1], itemoff + H).wait();
         const int NC = tot[0], NH = tot[1];
         if (NC > maxch || NH > n)
             fail(FNN_EINTERNAL, "chunk table overflow (%d > %d)", NC, maxch);
@@ -2053,17 +2077,18 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
             sp = S.get<SelPart>(H);
         auto pass = [&](hipStream_t s, int k) {
             int32_t *qc = k ? qb : qa, *qx = k ? qa : qb;
-            fill(qlen + (1 - k), 0, 1, s);
             if constexpr (M == M_LEV)
                 launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, ch_s, ch_e, qc,
-                                  qlen + k, hubs, cent, perm, D, L, tab, cb_D, cb_id,
+                                  qlen + k, qlen + (1 - k), hubs, cent, perm, D, L, tab, cb_D, cb_id,
                                   T->opt.kmax, cnt);
             else
                 FNN_LAUNCH((k_update<M>), dim3(gu), dim3(CH * UPD_W), upd_lds, s, P, ch_hub,
-                           ch_s, ch_e, qc, qlen + k, hubs, cent, perm, D, L, tab, cb_D,
+                           ch_s, ch_e, qc, qlen + k, qlen + (1 - k), hubs, cent, perm, D, L, tab, cb_D,
                            cb_id, T->opt.kmax, cnt);
-            FNN_LAUNCH(k_select_pre, dim3(grid_cap((int64_t)H * SEL_SL, 1, 8192)),
-                       dim3(SEL_T), 0, s, hubs, H, cb_D, cb_id, T->opt.kmax);
+            // (no hub of this level can have more than NC + 2 kmax candidates)
+            if (NC + 2ll * T->opt.kmax > SEL_PRE)
+                FNN_LAUNCH(k_select_pre, dim3(grid_cap((int64_t)H * SEL_SL, 1, 8192)),
+                           dim3(SEL_T), 0, s, hubs, H, cb_D, cb_id, T->opt.kmax);
             const dim3 gs(grid_cap(H, 1, 4096));
             if constexpr (M == M_LEV) {
                 if (sp) {
@@ -2082,30 +2107,42 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
             FNN_LAUNCH((k_select<M, SEL_ALL>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent, cb_D,
                        cb_id, tab, T->opt.kmax, qx, qlen + (1 - k), cnt, nullptr);
         };
-        if (GP <= 1) {
-            for (int k = 0;; k ^= 1) {
-                pass(st, k);
-                ++passes;
-                if (read_scalar(qlen + (1 - k), st) == 0)
-                    break;
+        // The first passes of a level run eagerly with one read after them (a
+        // graph of four passes costs 140 us to record, instantiate and drop,
+        // their launches 22 to 45 us, and most levels of small inputs end
+        // here); the children's count is read along.
+        int C = -1, live = 0;
+        for (int k = 0; k < GP; ++k)
+            pass(st, k & 1);
+        passes += GP;
+        scan_i32(hubs.m, child_base, H, S);
+        Readback(st).add(&live, qlen + (GP & 1)).add(&C, child_base + H).wait();
+        if (live) {
+            if (GP <= 1) {
+                for (int k = 1;; k ^= 1) {
+                    pass(st, k);
+                    ++passes;
+                    if (read_scalar(qlen + (1 - k), st) == 0)
+                        break;
+                }
+            } else {
+                GraphRun gr;
+                gr.begin();
+                for (int k = 0; k < GP; ++k)
+                    pass(gr.cs, k & 1);
+                gr.end();
+                for (;;) {
+                    gr.launch(st);
+                    passes += GP;
+                    if (read_scalar(qlen, st) == 0)
+                        break;
+                }
             }
-        } else {
-            GraphRun gr;
-            gr.begin();
-            for (int k = 0; k < GP; ++k)
-                pass(gr.cs, k & 1);
-            gr.end();
-            for (;;) {
-                gr.launch(st);
-                passes += GP;
-                if (read_scalar(qlen, st) == 0)
-                    break;
-            }
+            scan_i32(hubs.m, child_base, H, S);
+            C = read_scalar(child_base + H, st);
         }
 
         // ---- partition into children ---------------------------------------
-        scan_i32(hubs.m, child_base, H, S);
-        const int C = read_scalar(child_base + H, st);
         if (node_count + C > (int64_t)cap)
             fail(FNN_EINTERNAL, "vertex capacity exceeded");
         FNN_LAUNCH(k_part_keys, dim3(grid_cap(NC, 1, 16384)), dim3(CH), 0, st, ch_hub,
@@ -2135,8 +2172,6 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     const int nn = (int)node_count;
     T->nnodes = nn;
     T->perm = (int32_t *)T->own(sizeof(int32_t) * n);
-    FNN_HIP(hipMemcpyAsync(T->perm, perm, sizeof(int32_t) * n,
-                           hipMemcpyDeviceToDevice, st));
     int32_t *inv = S.get<int32_t>(n);
     FNN_LAUNCH(k_inverse, dim3(cdiv(n, 256)), dim3(256), 0, st, perm, n,
                        inv);
@@ -2154,16 +2189,10 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
         T->pt_begin = (int32_t *)v[6];
         T->pt_end = (int32_t *)v[7];
     }
-    auto cp = [&](void *dst, const void *src, size_t b) {
-        FNN_HIP(hipMemcpyAsync(dst, src, b, hipMemcpyDeviceToDevice, st));
-    };
-    cp(T->center, nd.center, 4 * (size_t)nn);
-    cp(T->radius, nd.radius, 4 * (size_t)nn);
-    cp(T->level, nd.level, 4 * (size_t)nn);
-    cp(T->child_begin, nd.cbeg, 4 * (size_t)nn);
-    cp(T->child_count, nd.ccnt, 4 * (size_t)nn);
-    cp(T->pt_begin, nd.pb, 4 * (size_t)nn);
-    cp(T->pt_end, nd.pe, 4 * (size_t)nn);
+    const NodeArrays own{T->center,      T->level,    T->child_begin, T->child_count,
+                         T->pt_begin,    T->pt_end,   T->radius};
+    FNN_LAUNCH(k_copy_nodes, dim3(grid_cap(std::max(nn, n), 256, 4096)), dim3(256), 0, st, nd,
+               nn, perm, n, own, T->perm);
     FNN_LAUNCH(k_center_pos, dim3(cdiv(nn, 256)), dim3(256), 0, st,
                        nd.center, inv, nn, T->center_pos);
 
@@ -2211,9 +2240,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     scan_i32(npk, pkoff, nn, S);
     scan_i32(nqk, kidoff, nn, S);
     int32_t tots[2];
-    FNN_HIP(hipMemcpyAsync(&tots[0], pkoff + nn, 4, hipMemcpyDeviceToHost, st));
-    FNN_HIP(hipMemcpyAsync(&tots[1], kidoff + nn, 4, hipMemcpyDeviceToHost, st));
-    FNN_HIP(hipStreamSynchronize(st));
+    Readback(st).add(&tots[0], pkoff + nn).add(&tots[1], kidoff + nn).wait();
     int npacks = tots[0], nkids = tots[1];
     const bool root_leaf = (nn == 1);
     if (root_leaf)
@@ -2262,17 +2289,14 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
 
     FNN_HIP(hipEventRecord(ev1, st));
     unsigned long long hc[4];
-    FNN_HIP(hipMemcpyAsync(hc, cnt, sizeof hc, hipMemcpyDeviceToHost, st));
-    FNN_HIP(hipStreamSynchronize(st));
+    int herr = 0;
+    Readback(st).add(hc, cnt, 4).add(&herr, err).wait();
     float ms = 0.f;
     FNN_HIP(hipEventElapsedTime(&ms, ev0, ev1));
     (void)hipEventDestroy(ev0);
     (void)hipEventDestroy(ev1);
-    {
-        int e = read_scalar(err, st);
-        if (e & ERR_INDEX)
-            fail(FNN_EINTERNAL, "build index check failed");
-    }
+    if (herr & ERR_INDEX)
+        fail(FNN_EINTERNAL, "build index check failed");
 
     fnn_stats &s = T->stats;
     s.n = n;

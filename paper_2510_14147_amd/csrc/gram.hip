@@ -649,6 +649,48 @@ __global__ void k_uniform_packs(int n, int np, int32_t *__restrict__ pb,
     }
 }
 
+// Units c and entries l of run k of the closed-form list over np packs.
+__host__ __device__ inline void dense_run(long long k, int R, int np, long long &c, long long &l)
+{
+    const long long kR = k * R, h = kR + R < np ? kR + R : np;
+    const long long ngp = (np + GW - 1) / GW;
+    c = ngp < (h + GW - 1) / GW ? ngp : (h + GW - 1) / GW;
+    const long long a = c < kR / GW + 1 ? c : kR / GW + 1;
+    l = a * (h - kR) + (c - a) * h - (long long)GW * ((a + c - 1) * (c - a) / 2);
+}
+
+// Running sums U of the runs' units and E of their entries (one wave).
+__global__ void __launch_bounds__(WAVE)
+k_dense_runs(int nrun, int R, int np, long long *__restrict__ U, long long *__restrict__ E)
+{
+    const int lane = threadIdx.x;
+    long long u0 = 0, e0 = 0;
+    for (int k0 = 0; k0 < nrun; k0 += WAVE) {
+        long long c = 0, l = 0;
+        if (k0 + lane < nrun)
+            dense_run(k0 + lane, R, np, c, l);
+        long long ci = c, li = l;  // inclusive over the wave
+#pragma unroll
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const long long x = __shfl_up(ci, o, WAVE), y = __shfl_up(li, o, WAVE);
+            if (lane >= o) {
+                ci += x;
+                li += y;
+            }
+        }
+        if (k0 + lane < nrun) {
+            U[k0 + lane] = u0 + ci - c;
+            E[k0 + lane] = e0 + li - l;
+        }
+        u0 += __shfl(ci, WAVE - 1, WAVE);
+        e0 += __shfl(li, WAVE - 1, WAVE);
+    }
+    if (lane == 0) {
+        U[nrun] = u0;
+        E[nrun] = e0;
+    }
+}
+
 // Unit table of the closed-form work list from per-run tables.  Run k
 // covers B packs [k R, h_k), h_k = min((k + 1) R, npk); its units are
 // U[k] .. U[k+1] - 1, unit U[k] + g pairing group g with packs
@@ -2461,10 +2503,9 @@ static int project_pca(const float *X, int n, int dp, int kq_full, int proj,
     FNN_LAUNCH(k_pca_power, gp, dim3(256), 0, s, Cv, dp, kmax, trd, (const double *)Z, Y);
     FNN_LAUNCH(k_pca, dim3(1), dim3(256), 0, s, Cv, dp, kmax, proj, t2min, 0.5, trd, Y, Qd,
                kout, info);
-    const int K = read_scalar(kout, s);
+    int K = 0;
     double hinfo[2];
-    FNN_HIP(hipMemcpyAsync(hinfo, info, sizeof hinfo, hipMemcpyDeviceToHost, s));
-    FNN_HIP(hipStreamSynchronize(s));
+    Readback(s).add(&K, kout).add(hinfo, info, 2).wait();
     if (K <= 0)
         return 0;
     // FP64 rounding of the projection: |z~_k - z_k| <= gamma sum_c |Q_ck| |v_c|
@@ -2546,8 +2587,7 @@ double gram_margin_ratio(const fnn_tree *T, double t2min, int prec, Scratch &S,
                dp, CX, acc,
                reinterpret_cast<unsigned *>(acc + 1));
     double h[2];
-    FNN_HIP(hipMemcpyAsync(h, acc, sizeof h, hipMemcpyDeviceToHost, s));
-    FNN_HIP(hipStreamSynchronize(s));
+    Readback(s).add(h, acc, 2).wait();
     const double mean = h[0] / std::max(n, 1);
     if (pre) {
         unsigned mb;
@@ -2823,37 +2863,29 @@ void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &
                     for (int g = 0; g < ng1; ++g)
                         mu += np - GW * g;
                 }
-                const int ngp = (np + GW - 1) / GW;
                 // units ordered by B run (runs aligned to RUN packs), then by
                 // group: the units of one run read the same B tiles.  The
-                // host sums the per-run counts; the unit table itself is
-                // filled on the device (k_dense_plan).
+                // host only sums the per-run counts; the run and unit tables
+                // are filled on the device (k_dense_runs, k_dense_plan).
                 const int nrun = (np + RUN - 1) / RUN;
-                std::vector<long long> U(nrun + 1, 0), E(nrun + 1, 0);
+                long long nu_ = 0, e = 0;
                 for (int k = 0; k < nrun; ++k) {
-                    const long long kR = (long long)k * RUN;
-                    const long long h = std::min<long long>(kR + RUN, np);
-                    const long long c = std::min<long long>(ngp, (h + GW - 1) / GW);
-                    const long long a = std::min<long long>(c, kR / GW + 1);
-                    U[k + 1] = U[k] + c;
-                    E[k + 1] = E[k] + a * (h - kR) + (c - a) * h -
-                               (long long)GW * ((a + c - 1) * (c - a) / 2);
+                    long long c, l;
+                    dense_run(k, RUN, np, c, l);
+                    nu_ += c;
+                    e += l;
                 }
-                const int nu = (int)U[nrun];
-                const int64_t e = E[nrun];
+                const int nu = (int)nu_;
                 int32_t *lg = S.get<int32_t>(mu + 1), *lb = S.get<int32_t>(mu + 1);
                 int32_t *ubeg = S.get<int32_t>(nu + 1);
                 int32_t *ug_d = S.get<int32_t>(nu), *ulo_d = S.get<int32_t>(nu);
                 long long *UE = S.get<long long>(2 * (size_t)(nrun + 1));
-                FNN_HIP(hipMemcpyAsync(UE, U.data(), sizeof(long long) * (nrun + 1),
-                                       hipMemcpyHostToDevice, s));
-                FNN_HIP(hipMemcpyAsync(UE + nrun + 1, E.data(), sizeof(long long) * (nrun + 1),
-                                       hipMemcpyHostToDevice, s));
+                FNN_LAUNCH(k_dense_runs, dim3(1), dim3(WAVE), 0, s, nrun, RUN, np, UE,
+                           UE + nrun + 1);
                 FNN_LAUNCH(k_dense_plan, dim3(grid_for(nu, 256)), dim3(256), 0, s, UE,
                            UE + nrun + 1, nrun, RUN, np, nu, ubeg, ug_d, ulo_d);
                 FNN_LAUNCH(k_dense_units, dim3(grid_cap(nu, 4, 16384)), dim3(256), 0, s,
                            ubeg, ug_d, ulo_d, nu, lg, lb);
-                FNN_HIP(hipStreamSynchronize(s));  // host vectors go out of scope
                 *rest = nullptr;
                 *nrest = 0;
                 G.nn = base;

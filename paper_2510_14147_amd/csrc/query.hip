@@ -1565,6 +1565,19 @@ __global__ void k_forest_frontier(QView Q, int2 *__restrict__ cur, int cap)
     }
 }
 
+// The traversal's counters, and its start from one pair (a forest's frontier
+// is k_forest_frontier's).
+__global__ void k_traverse_init(int2 *__restrict__ cur, int2 root, int one,
+                                unsigned long long ncur, unsigned long long *__restrict__ cnt,
+                                int *__restrict__ ovf)
+{
+    if (one)
+        cur[0] = root;
+    cnt[0] = ncur;
+    cnt[1] = cnt[2] = cnt[3] = cnt[4] = 0ull;
+    ovf[0] = ovf[1] = 0;
+}
+
 constexpr unsigned EXPAND_GRID = 4096;  // work-groups of the expansion
 
 // Launch of one level of the expansion (eager: ncur from the host; device:
@@ -1606,13 +1619,15 @@ static void launch_expand(const Pts &P, const QView &Q, const Prune &pr, const i
 
 // The level-synchronous expansion.  With gp > 1, levels first run as
 // device-queue passes: gp levels (even) recorded once into a graph and
-// replayed until the frontier is empty, one host read per replay; a level
+// replayed until the frontier is empty, one host read per replay (with
+// eager_first the first gp levels are launched as they are: a shallow tree
+// ends there, and a graph costs 110 us before its first replay); a level
 // whose output may not fit the fixed buffers stops the replays with its
 // frontier intact, and the eager loop below (one bound and one count read
 // per level, buffers grown to fit) finishes from there.
 template <int M>
 static void traverse(const fnn_tree *T, const Pts &P, const QView &Q,
-                     const Prune &pr, Scratch &S, int gp, long long list_cap,
+                     const Prune &pr, Scratch &S, int gp, bool eager_first, long long list_cap,
                      int2 **inter_out, long long *ninter_out, fnn_stats &st)
 {
     hipStream_t s = S.stream();
@@ -1643,31 +1658,37 @@ static void traverse(const fnn_tree *T, const Pts &P, const QView &Q,
     }
     int2 *cur = S.get<int2>(cap_cur), *next = S.get<int2>(cap_next);
     int2 *inter = S.get<int2>(cap_int);
-    int2 root = cross ? make_int2(T->cross_a, T->cross_b) : make_int2(T->qroot, T->qroot);
-    if (T->ncloud > 1 && !cross)
+    const int2 root = cross ? make_int2(T->cross_a, T->cross_b) : make_int2(T->qroot, T->qroot);
+    const bool forest = T->ncloud > 1 && !cross;
+    if (forest)
         FNN_LAUNCH(k_forest_frontier, dim3(grid_for(nroot, 256)), dim3(256), 0, s,
                    Q, cur, (int)nroot);
-    else
-        FNN_HIP(hipMemcpyAsync(cur, &root, sizeof(int2), hipMemcpyHostToDevice, s));
     long long ncur = nroot, ninter = 0, tests = 0;
-    fill(ovf, 0, 2, s);
+    FNN_LAUNCH(k_traverse_init, dim3(1), dim3(1), 0, s, cur, root, forest ? 0 : 1,
+               (unsigned long long)ncur, cnt, ovf);
 
     if (gp > 1 && ncur > 0) {
-        const unsigned long long init[5] = {(unsigned long long)ncur, 0ull, 0ull, 0ull, 0ull};
-        FNN_HIP(hipMemcpyAsync(cnt, init, sizeof init, hipMemcpyHostToDevice, s));
         int2 *buf[2] = {cur, next};
+        auto levels = [&](hipStream_t q) {
+            for (int k = 0; k < gp; ++k) {
+                const int a = k & 1;  // this level's frontier: buf[a], length cnt[a]
+                FNN_LAUNCH(k_expand_bound_d, dim3(256), dim3(256), 0, q, Q, buf[a], cnt + a,
+                           cap_cur, ovf + 1, cnt + 4);
+                FNN_LAUNCH(k_level_guard, dim3(1), dim3(1), 0, q, cnt + a, cnt + 4, cnt + 2,
+                           cap_cur, cap_int, a, ovf + 1, cnt + (1 - a));
+                Emit E{buf[1 - a], inter, cnt + (1 - a), cnt + 2, cnt + 3, cap_cur, cap_int,
+                       ovf};
+                launch_expand<M>(P, Q, pr, buf[a], 0, cnt + a, ovf + 1, E, q);
+            }
+        };
         GraphRun gr;
-        gr.begin();
-        for (int k = 0; k < gp; ++k) {
-            const int a = k & 1;  // this level's frontier: buf[a], length cnt[a]
-            FNN_LAUNCH(k_expand_bound_d, dim3(256), dim3(256), 0, gr.cs, Q, buf[a], cnt + a,
-                       cap_cur, ovf + 1, cnt + 4);
-            FNN_LAUNCH(k_level_guard, dim3(1), dim3(1), 0, gr.cs, cnt + a, cnt + 4, cnt + 2,
-                       cap_cur, cap_int, a, ovf + 1, cnt + (1 - a));
-            Emit E{buf[1 - a], inter, cnt + (1 - a), cnt + 2, cnt + 3, cap_cur, cap_int, ovf};
-            launch_expand<M>(P, Q, pr, buf[a], 0, cnt + a, ovf + 1, E, gr.cs);
-        }
-        gr.end();
+        auto record = [&]() {
+            gr.begin();
+            levels(gr.cs);
+            gr.end();
+        };
+        if (!eager_first)
+            record();
         // a tree of depth D takes about 2 D levels; past a generous multiple
         // the eager loop takes over from the frontier in buf[0]
         const int max_replays = (int)(4 * (T->depth + 8) / gp + 4);
@@ -1677,12 +1698,16 @@ static void traverse(const fnn_tree *T, const Pts &P, const QView &Q,
                 next = buf[1];
                 break;
             }
-            gr.launch(s);
+            if (r == 0 && eager_first) {
+                levels(s);
+            } else {
+                if (!gr.exec)
+                    record();
+                gr.launch(s);
+            }
             unsigned long long hc[5];
             int hf[2];
-            FNN_HIP(hipMemcpyAsync(hc, cnt, sizeof hc, hipMemcpyDeviceToHost, s));
-            FNN_HIP(hipMemcpyAsync(hf, ovf, sizeof hf, hipMemcpyDeviceToHost, s));
-            FNN_HIP(hipStreamSynchronize(s));
+            Readback(s).add(hc, cnt, 5).add(hf, ovf, 2).wait();
             if (hf[0])
                 fail(FNN_EINTERNAL, "traversal emitted more pairs than its bound");
             ninter = (long long)hc[2];
@@ -1727,9 +1752,7 @@ static void traverse(const fnn_tree *T, const Pts &P, const QView &Q,
         launch_expand<M>(P, Q, pr, cur, ncur, nullptr, nullptr, E, s);
         unsigned long long hc[3];
         int hov = 0;
-        FNN_HIP(hipMemcpyAsync(hc, cnt + 1, sizeof hc, hipMemcpyDeviceToHost, s));
-        FNN_HIP(hipMemcpyAsync(&hov, ovf, sizeof(int), hipMemcpyDeviceToHost, s));
-        FNN_HIP(hipStreamSynchronize(s));
+        Readback(s).add(hc, cnt + 1, 3).add(&hov, ovf).wait();
         if (hov)
             fail(FNN_EINTERNAL, "traversal emitted more pairs than its bound");
         ncur = (long long)hc[0];
@@ -1791,19 +1814,29 @@ __global__ void k_pair_bound(const int2 *__restrict__ inter, long long ni,
 // entries packed as (column << 32 | distance bits) in their slots, when the
 // fill wrote them so (col and dist are then written here); null: they are
 // in col and dist.
+// cc: two zeroed counts (null: taken here); err: a device flag to read along
+// with them into *herr (optional).
 void sort_csr_rows(const int64_t *row_ptr, int n, int32_t *col, float *dist,
-                   int64_t nnz, Scratch &S, const unsigned long long *pk)
+                   int64_t nnz, Scratch &S, const unsigned long long *pk, int32_t *cc,
+                   const int *err, int *herr)
 {
     hipStream_t s = S.stream();
     int32_t *mid = S.get<int32_t>(n), *lng = S.get<int32_t>(n);
-    int32_t *cc = S.get<int32_t>(2);
-    fill(cc, 0, 2, s);
+    if (!cc) {
+        cc = S.get<int32_t>(2);
+        fill(cc, 0, 2, s);
+    }
+    if (nnz <= 0 && err)
+        *herr = read_scalar(err, s);
     if (nnz > 0) {
         FNN_LAUNCH(k_sort_small, dim3(grid_cap(n, 4, 16384)), dim3(256), 0, s,
                    row_ptr, n, col, dist, mid, lng, cc, pk);
         int32_t hcc[2];
-        FNN_HIP(hipMemcpyAsync(hcc, cc, sizeof hcc, hipMemcpyDeviceToHost, s));
-        FNN_HIP(hipStreamSynchronize(s));
+        Readback rb(s);
+        rb.add(hcc, (const int32_t *)cc, 2);
+        if (err)
+            rb.add(herr, err);
+        rb.wait();
         if (hcc[0] > 0) {
             FNN_LAUNCH(k_sort_wave, dim3(grid_cap(hcc[0], 4, 4096)), dim3(256), 0, s,
                        row_ptr, mid, hcc[0], col, dist);
@@ -2055,7 +2088,7 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     } else {
         traverse<M>(T, P, Q, pr, S,
                     opt.graph_passes <= 1 ? 1 : (opt.graph_passes + 1) / 2 * 2,
-                    opt.list_cap, &inter, &ninter, st);
+                    !opt.graph_set, opt.list_cap, &inter, &ninter, st);
     }
     tm.mark();  // 1
 
@@ -2099,12 +2132,14 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     tm.mark();  // 2
 
     // [0..5] see TileOut, [6..7] the learned path's re-fill
-    unsigned long long *cnt = S.get<unsigned long long>(8);
-    fill(cnt, 0ull, 8, s);
+    // [8] error flag, [9] pair bound, [10] listed edges, [11] rows for the
+    // longer sorts (two counts)
+    unsigned long long *cnt = S.get<unsigned long long>(12);
+    fill(cnt, 0ull, 12, s);
     TileOut o{};
     o.cnt = cnt;
-    int *bad = S.get<int>(1);
-    fill(bad, 0, 1, s);
+    int *bad = reinterpret_cast<int *>(cnt + 8);
+    int32_t *nlong = reinterpret_cast<int32_t *>(cnt + 11);
     o.err = bad;
     C->n = nr;
     C->row_ptr = (int64_t *)out_alloc(sizeof(int64_t) * ((size_t)nr + 1));
@@ -2210,8 +2245,7 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         bool listed = false;
         long long nlisted = 0;
         if (nplain > 0) {
-            unsigned long long *pb_ = S.get<unsigned long long>(1);
-            fill(pb_, 0ull, 1, s);
+            unsigned long long *pb_ = cnt + 9;
             FNN_LAUNCH(k_pair_bound, dim3(grid_for(nplain, 256)), dim3(256), 0, s,
                        plain, nplain, T->q_pt_begin, T->q_pt_end, pb_);
             const unsigned long long bound = read_scalar(pb_, s);
@@ -2224,8 +2258,7 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                 o.ecap = (unsigned long long)opt.list_cap;
             o.elist = S.get<int2>(o.ecap);
             o.edist = S.get<float>(o.ecap);
-            o.ecnt = S.get<unsigned long long>(1);
-            fill(o.ecnt, 0ull, 1, s);
+            o.ecnt = cnt + 10;
             launch_tiles<M>(TILE_LIST, P, plain, nplain, T, E, ct_d, fp64_dist, o, s);
             nlisted = (long long)read_scalar(o.ecnt, s);
             listed = (unsigned long long)nlisted <= o.ecap;
@@ -2233,9 +2266,8 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         tm.mark();  // 3
 
         scan_i32_to_i64(o.deg, C->row_ptr, nr, S);
-        nnz = read_scalar(C->row_ptr + nr, s);
+        Readback(s).add(&nnz, C->row_ptr + nr).add(hc0, cnt, 8).wait();
         C->nnz = nnz;
-        FNN_HIP(hipMemcpy(hc0, cnt, sizeof hc0, hipMemcpyDeviceToHost));
         C->col = (int32_t *)out_alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1));
         C->dist = (float *)out_alloc(sizeof(float) * (size_t)std::max<int64_t>(nnz, 1));
         tm.mark();  // 4
@@ -2337,9 +2369,8 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         FNN_LAUNCH(k_deg_from_cursor, dim3(grid_for(n, 256)), dim3(256), 0, s,
                    o.cursor, sb, n, o.deg);
         scan_i32_to_i64(o.deg, C->row_ptr, n, S);
-        nnz = read_scalar(C->row_ptr + n, s);
+        Readback(s).add(&nnz, C->row_ptr + n).add(hc0, cnt, 8).wait();
         C->nnz = nnz;
-        FNN_HIP(hipMemcpy(hc0, cnt, sizeof hc0, hipMemcpyDeviceToHost));
         C->col = (int32_t *)out_alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1));
         C->dist = (float *)out_alloc(sizeof(float) * (size_t)std::max<int64_t>(nnz, 1));
         tm.mark();  // 4
@@ -2399,7 +2430,9 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     }
 
     // ---- per-row sort ---------------------------------------------------
-    sort_csr_rows(C->row_ptr, nr, C->col, C->dist, nnz, S, packed);
+    // (the fill's error flag is read with the sort's counts)
+    int hbad = 0;
+    sort_csr_rows(C->row_ptr, nr, C->col, C->dist, nnz, S, packed, nlong, bad, &hbad);
     tm.mark();  // 6
 
     // ---- trace targets, prediction error ---------------------------------
@@ -2424,8 +2457,6 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         st.pred_mae = hacc[0] / std::max(n, 1);
         st.pred_sum_ratio = hacc[2] > 0 ? hacc[1] / hacc[2] : 0.0;
     }
-    int hbad = 0;
-    FNN_HIP(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s));
     FNN_HIP(hipStreamSynchronize(s));
     if (hbad)
         fail(FNN_EINTERNAL, "count and fill passes disagree");

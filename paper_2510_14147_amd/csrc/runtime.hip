@@ -65,6 +65,29 @@ int num_cus()
     return c;
 }
 
+namespace {
+struct HostStage {
+    char *p = nullptr;
+    ~HostStage()
+    {
+        if (p)
+            (void)hipHostFree(p);
+    }
+};
+}  // namespace
+
+char *host_stage()
+{
+    static thread_local HostStage h;
+    if (!h.p) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, HOST_READ + HOST_WRITE, hipHostMallocPortable) != hipSuccess || !p)
+            fail(-2, "pinned host allocation of %zu bytes failed", HOST_READ + HOST_WRITE);
+        h.p = static_cast<char *>(p);
+    }
+    return h.p;
+}
+
 LaunchCount &launch_count()
 {
     static thread_local LaunchCount c;
@@ -379,9 +402,10 @@ k_scan_tiles(const TI *__restrict__ in, TO *__restrict__ out,
         tile_sums[blockIdx.x] = tot;
 }
 
+// Adds each tile's offset; out[n] = the total (tile_off[ntiles]).
 template <class TO>
 __global__ void __launch_bounds__(SCAN_T)
-k_scan_add(TO *__restrict__ out, const TO *__restrict__ tile_off, int64_t n)
+k_scan_add(TO *__restrict__ out, const TO *__restrict__ tile_off, int64_t ntiles, int64_t n)
 {
     const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
     const TO o = tile_off[blockIdx.x];
@@ -390,20 +414,40 @@ k_scan_add(TO *__restrict__ out, const TO *__restrict__ tile_off, int64_t n)
         if (g < n)
             out[g] += o;
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        out[n] = tile_off[ntiles];
 }
 
-template <class TO>
-__global__ void k_scan_total(TO *__restrict__ out, const TO *__restrict__ tile_off,
-                             int64_t ntiles, int64_t n)
+// The whole scan of n <= SCAN_ONE values by one work-group, total included:
+// a launch is 2.7 us on the host and as much on the device, a step of this
+// loop under 1 us, so up to here one launch beats three.
+constexpr int64_t SCAN_ONE = 8 * SCAN_TILE;
+template <class TI, class TO>
+__global__ void __launch_bounds__(SCAN_T)
+k_scan_one(const TI *__restrict__ in, TO *__restrict__ out, int64_t n)
 {
-    out[n] = tile_off[ntiles];
-}
-
-template <class TO>
-__global__ void k_scan_single(TO *__restrict__ offs, const TO *__restrict__ sums)
-{
-    offs[0] = 0;
-    offs[1] = sums[0];
+    TO carry = 0;
+    for (int64_t t = 0; t < n; t += SCAN_TILE) {
+        const int64_t base = t + (int64_t)threadIdx.x * SCAN_ITEMS;
+        TO v[SCAN_ITEMS];
+        TO s = 0;
+#pragma unroll
+        for (int i = 0; i < SCAN_ITEMS; ++i) {
+            v[i] = base + i < n ? (TO)in[base + i] : (TO)0;
+            s += v[i];
+        }
+        TO tot;
+        TO off = carry + block_excl_scan<TO>(s, &tot);
+#pragma unroll
+        for (int i = 0; i < SCAN_ITEMS; ++i) {
+            if (base + i < n)
+                out[base + i] = off;
+            off += v[i];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0)
+        out[n] = carry;
 }
 
 template <class TI, class TO>
@@ -414,21 +458,18 @@ static void scan_impl(const TI *in, TO *out, int64_t n, Scratch &S)
         fill(out, (TO)0, 1, s);
         return;
     }
+    if (n <= SCAN_ONE) {
+        FNN_LAUNCH((k_scan_one<TI, TO>), dim3(1), dim3(SCAN_T), 0, s, in, out, n);
+        return;
+    }
     int64_t ntiles = cdiv(n, SCAN_TILE);
     TO *sums = S.get<TO>(ntiles + 1);
     TO *offs = S.get<TO>(ntiles + 1);
     FNN_LAUNCH((k_scan_tiles<TI, TO>), dim3((unsigned)ntiles),
                        dim3(SCAN_T), 0, s, in, out, sums, n);
-    if (ntiles == 1) {
-        FNN_LAUNCH((k_scan_single<TO>), dim3(1), dim3(1), 0, s, offs,
-                           sums);
-    } else {
-        scan_impl<TO, TO>(sums, offs, ntiles, S);
-    }
+    scan_impl<TO, TO>(sums, offs, ntiles, S);
     FNN_LAUNCH((k_scan_add<TO>), dim3((unsigned)ntiles), dim3(SCAN_T),
-                       0, s, out, offs, n);
-    FNN_LAUNCH((k_scan_total<TO>), dim3(1), dim3(1), 0, s, out, offs,
-                       ntiles, n);
+                       0, s, out, offs, ntiles, n);
 }
 
 void scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, Scratch &S)

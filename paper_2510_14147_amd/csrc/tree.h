@@ -26,6 +26,7 @@ struct Options {
     int trace = 0;
     int slack_pct = 30;
     int graph_passes = 4;
+    bool graph_set = false;  // graph_passes is the caller's
     int proj = 0;
     long long list_cap = 0;  // initial survivor / edge list entries (0: automatic)
     int lpt = 0;             // learned schedule: LPT order of the tile pass
