@@ -340,12 +340,16 @@ struct Hubs {
 
 __global__ void k_hub_sizes(const int32_t *__restrict__ b,
                             const int32_t *__restrict__ e, int H,
-                            int32_t *__restrict__ nch, int32_t *__restrict__ sz)
+                            int32_t *__restrict__ nch, int32_t *__restrict__ sz,
+                            int32_t *__restrict__ most)
 {
     const int h = blockIdx.x * blockDim.x + threadIdx.x;
+    const int s = h < H ? e[h] - b[h] : 0;
+    const int m = wave_max(s);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && m)
+        atomicMax(most, m);  // the level's largest hub
     if (h >= H)
         return;
-    int s = e[h] - b[h];
     nch[h] = (s + CH - 1) / CH;
     sz[h] = s;
 }
@@ -691,6 +695,300 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
         if (lane == 0 && j1 > j0)
             atomicAdd(cnt, (unsigned long long)(j1 - j0) * (unsigned)(e - s));
     }
+    }
+}
+
+// ---- update screened on the matrix cores --------------------------------
+//
+// Of the (point, new centre) pairs of a pass only those that bring a point
+// nearer matter, a few in a hundred.  Rows of 16..128 floats therefore go
+// through FP16 products first: per level every hub's rows are copied as
+// (x - c) 2^e, c the hub's centre and 2^e so that its radius lands below
+// 2^14 (the margin then follows the hub's own size), with their squared
+// norms; a pass multiplies a chunk's 64 points by 32 new centres at a time
+// and keeps, for every point, the centres that may be its nearest in the
+// batch and nearer than its D.  Those keys are then computed as in the scan
+// (one FMA chain in index order), so D, L and the tree are the same bit for
+// bit.
+//
+// With |q(a).q(b) - a.b| below c1 (|a|^2 + |b|^2) / 2 + add / 2 in scaled
+// units (the filter's bound, see gram.hip), d^2 lies within
+// c1 (|a|^2 + |b|^2) + add of |a|^2 + |b|^2 - 2 g.  A centre is dropped when
+// its smallest possible d^2 exceeds D^2, or the largest possible d^2 of the
+// batch's best one, both widened by the FP32 key's own rounding (keyrel).
+//
+// What bounds it: the chain of loads of a chunk (queue, hub, rows, centres)
+// over few passes in flight, and the keys left over.  A wave owns a chunk and
+// waits for no other: the new centres are points of the hub, so their FP16
+// rows are read from the level's copy, found by position, straight into
+// MFMA operands.  All updates of a build, plus the copies: 1M points x 128
+// 11.3 -> 6.7 + 0.5 ms, 581K x 55 (528 passes) 41.3 -> 16.6 + 0.1 ms, 50K x
+// 128 build 2.5 -> 1.7 ms (centres staged through LDS for eight waves with
+// two barriers a batch: 7.2 and 17.8 ms).  Three waves per SIMD for rows above
+// 32 floats: four spill the point operands and take 8.0 and 20.2 ms.
+typedef __attribute__((ext_vector_type(8))) _Float16 mx_f16x8;
+typedef __attribute__((ext_vector_type(4))) _Float16 mx_f16x4;
+typedef __attribute__((ext_vector_type(16))) float mx_f32x16;
+
+struct MxArgs {
+    const _Float16 *q;       // [n][16 NKS], by position
+    const float *nrm;        // [n] |.|^2, scaled
+    const int32_t *pos;      // [n] position of every hub point's input id
+    const int32_t *center;   // of every vertex (input ids)
+    const float *radius;
+    float c1, add, keyrel;
+};
+
+// 2^e with r 2^e in [2^13, 2^14) (e at most 60: squares stay finite).
+__device__ __forceinline__ float mx_scale(float r)
+{
+    int e = 0;
+    (void)frexpf(r, &e);  // r < 2^e
+    return ldexpf(1.f, min(14 - e, 60));
+}
+
+// Scaled FP16 rows and norms of every chunk (one wave each; eight lanes to a
+// row).
+template <int M, int NKS>
+__global__ void __launch_bounds__(256)
+k_mx_rows(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
+          const int32_t *__restrict__ ch_e, int NC, Hubs hb, const int32_t *__restrict__ perm,
+          const int32_t *__restrict__ center, const float *__restrict__ radius,
+          _Float16 *__restrict__ q, float *__restrict__ nrm, int32_t *__restrict__ pos)
+{
+    constexpr int KQ = 16 * NKS;
+    const float *X = M == M_ANG ? P.xn : P.x;
+    const int lane = threadIdx.x % CH, part = lane & 7, dp = P.dp;
+    for (int c = blockIdx.x * 4 + threadIdx.x / CH; c < NC; c += gridDim.x * 4) {
+        const int v = hb.node[ch_hub[c]];
+        const float sc = mx_scale(radius[v]);
+        const float *cr = X + (size_t)center[v] * dp;
+        const int s = ch_s[c], m = ch_e[c] - s;
+        for (int r0 = 0; r0 < m; r0 += 8) {
+            const int r = r0 + lane / 8;
+            const bool in = r < m;
+            const int id = perm[s + min(r, m - 1)];
+            const float *x = X + (size_t)id * dp;
+            float ss = 0.f;
+#pragma unroll
+            for (int k = 4 * part; k < KQ; k += 32) {
+                float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+                if (k < dp) {
+                    a = *reinterpret_cast<const float4 *>(x + k);
+                    b = *reinterpret_cast<const float4 *>(cr + k);
+                }
+                const float v0 = (a.x - b.x) * sc, v1 = (a.y - b.y) * sc,
+                            v2 = (a.z - b.z) * sc, v3 = (a.w - b.w) * sc;
+                ss = fmaf(v0, v0, fmaf(v1, v1, fmaf(v2, v2, fmaf(v3, v3, ss))));
+                if (in)
+                    *reinterpret_cast<mx_f16x4 *>(q + (size_t)(s + r) * KQ + k) =
+                        (mx_f16x4){(_Float16)v0, (_Float16)v1, (_Float16)v2, (_Float16)v3};
+            }
+            ss += __shfl_xor(ss, 1, WAVE);
+            ss += __shfl_xor(ss, 2, WAVE);
+            ss += __shfl_xor(ss, 4, WAVE);
+            if (in && part == 0) {
+                nrm[s + r] = ss;
+                pos[id] = s + r;
+            }
+        }
+    }
+}
+
+// The scan's FP32 key (upd_lane, sqdiff_seq), four float4 of both rows in
+// flight.
+__device__ __forceinline__ float mx_key(const float *__restrict__ a,
+                                        const float *__restrict__ b, int dp)
+{
+    float s = 0.f;
+#pragma unroll 1
+    for (int k0 = 0; k0 < dp; k0 += 16) {
+        float4 u[4], v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (k0 + 4 * i < dp) {
+                u[i] = *reinterpret_cast<const float4 *>(a + k0 + 4 * i);
+                v[i] = *reinterpret_cast<const float4 *>(b + k0 + 4 * i);
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (k0 + 4 * i < dp) {
+                const float d0 = u[i].x - v[i].x, d1 = u[i].y - v[i].y, d2 = u[i].z - v[i].z,
+                            d3 = u[i].w - v[i].w;
+                s = fmaf(d0, d0, s);
+                s = fmaf(d1, d1, s);
+                s = fmaf(d2, d2, s);
+                s = fmaf(d3, d3, s);
+            }
+    }
+    return s;
+}
+
+template <int M, int NKS>
+__global__ void __launch_bounds__(CH *UPD_W, NKS >= 4 ? 3 : 4)  // unspilled
+k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
+            const int32_t *__restrict__ ch_e, const int32_t *__restrict__ queue,
+            const int32_t *__restrict__ qlen, int32_t *__restrict__ qnext, Hubs hb,
+            const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
+            float *__restrict__ D, int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
+            float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax,
+            unsigned long long *__restrict__ cnt, MxArgs A)
+{
+    constexpr int KQ = 16 * NKS;
+    __shared__ __align__(16) float cterm_s[UPD_W][CH];  // -(1 - c1) |b|^2 / 2; -FLT_MAX: none
+    const float *X = M == M_ANG ? P.xn : P.x;
+    const int dp = P.dp;
+    const int w = threadIdx.x / CH, lane = threadIdx.x % CH;
+    const int l32 = lane & 31, hi = lane >> 5;
+    float *cterm = cterm_s[w];
+    const int nq = *qlen;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *qnext = 0;  // this pass's selection appends to it
+    const float omc1 = 1.f - A.c1;
+    // no wave waits for another: a new centre is a point of the hub, so its
+    // FP16 row is read from the level's copy like the points' own
+    for (int t = blockIdx.x * UPD_W + w; t < nq; t += gridDim.x * UPD_W) {
+        const int c = queue[t], h = ch_hub[c];
+        if (!hb.act[h])
+            continue;
+        const int s = ch_s[c], e = ch_e[c], p = s + lane;
+        const bool valid = p < e;
+        const int b = hb.b[h], j0 = hb.ma[h], j1 = hb.m[h];
+        const int o = valid ? perm[p] : 0;
+        float dcur = valid ? D[p] : 0.f;
+        int lcur = valid ? L[p] : 0;
+        if (j1 > j0) {
+            const float sc = mx_scale(A.radius[hb.node[h]]);
+            // this chunk's points: columns 32 cb + l32, k 16 ks + 8 hi ..
+            mx_f16x8 B[2][NKS];
+            float a2[2];
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                const int pp = min(s + cb * 32 + l32, e - 1);
+                a2[cb] = A.nrm[pp];
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+                    B[cb][ks] = *reinterpret_cast<const mx_f16x8 *>(A.q + (size_t)pp * KQ +
+                                                                    16 * ks + 8 * hi);
+            }
+            int cid = -1, cp = 0;  // lane's of 64 centres: input id, position
+            float b2 = 0.f;        // the 64's largest |b|^2
+            for (int jb = j0; jb < j1; jb += 32) {
+                const int u = (jb - j0) & 32;
+                if (u == 0) {
+                    cid = jb + lane < j1 ? cent[b + jb + lane] : -1;
+                    cp = cid >= 0 ? A.pos[cid] : s;
+                    const float n2 = cid >= 0 ? A.nrm[cp] : 0.f;
+                    b2 = wave_max(n2);
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    cterm[lane] = cid >= 0 ? -0.5f * omc1 * n2 : -FLT_MAX;
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                }
+                const _Float16 *cr = A.q + (size_t)__shfl(cp, u + l32, WAVE) * KQ + 8 * hi;
+                mx_f32x16 acc[2];
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const float4 v =
+                        *reinterpret_cast<const float4 *>(cterm + u + 8 * q4 + 4 * hi);
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        acc[cb][4 * q4] = v.x;
+                        acc[cb][4 * q4 + 1] = v.y;
+                        acc[cb][4 * q4 + 2] = v.z;
+                        acc[cb][4 * q4 + 3] = v.w;
+                    }
+                }
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) {
+                    const mx_f16x8 a = *reinterpret_cast<const mx_f16x8 *>(cr + 16 * ks);
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb)
+                        acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, B[cb][ks], acc[cb],
+                                                                        0, 0, 0);
+                }
+                // candidates: bit 16 cb + q, centre 8 (q / 4) + 4 hi + q % 4
+                unsigned mask = 0;
+                const float s2 = sc * sc;
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    const int pi = cb * 32 + l32;
+                    const float D2 = __shfl(dcur, pi, WAVE) * s2;
+                    const float mag = a2[cb] + b2;
+                    float mx = acc[cb][0];
+#pragma unroll
+                    for (int q = 1; q < 16; ++q)
+                        mx = fmaxf(mx, acc[cb][q]);
+                    mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+                    const float lo = 0.5f * (omc1 * a2[cb] - D2 - A.add) -
+                                     A.keyrel * (mag + D2);
+                    if (__ballot(s + pi < e && mx >= lo) == 0ull)
+                        continue;  // no point of this block can come nearer
+                    const float thr =
+                        fmaxf(lo, mx - (A.c1 + A.keyrel) * mag - A.add);
+                    unsigned k = 0;
+#pragma unroll
+                    for (int q = 0; q < 16; ++q)
+                        k |= acc[cb][q] >= thr ? 1u << q : 0u;
+                    mask |= (s + pi < e ? k : 0u) << (16 * cb);
+                }
+                float bk[2] = {FLT_MAX, FLT_MAX};
+                int bj[2] = {INT_MAX, INT_MAX};
+                while (__ballot(mask != 0u)) {
+                    const bool on = mask != 0u;
+                    const int bit = on ? __ffs(mask) - 1 : 0;
+                    mask &= mask - 1u;
+                    const int cb = bit >> 4, q = bit & 15;
+                    const int j = 8 * (q >> 2) + 4 * hi + (q & 3);
+                    const int op = __shfl(o, cb * 32 + l32, WAVE);
+                    const int oc = __shfl(cid, u + j, WAVE);
+                    if (on) {
+                        const float k = mx_key(X + (size_t)op * dp, X + (size_t)oc * dp, dp);
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            if (cb == i && (k < bk[i] || (k == bk[i] && j < bj[i]))) {
+                                bk[i] = k;
+                                bj[i] = j;
+                            }
+                    }
+                }
+                // the two halves of a column, then column i to lane i
+                float mk = FLT_MAX;
+                int mj = INT_MAX;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const float k2 = __shfl_xor(bk[i], 32, WAVE);
+                    const int j2 = __shfl_xor(bj[i], 32, WAVE);
+                    if (k2 < bk[i] || (k2 == bk[i] && j2 < bj[i])) {
+                        bk[i] = k2;
+                        bj[i] = j2;
+                    }
+                    if (hi == i) {
+                        mk = bk[i];
+                        mj = bj[i];
+                    }
+                }
+                if (valid && mk < dcur) {
+                    dcur = mk;
+                    lcur = jb + mj;
+                }
+            }
+        }
+        float dv = -1.f;
+        int id = INT_MAX;
+        if (valid) {
+            if (j1 > j0) {
+                D[p] = dcur;
+                L[p] = lcur;
+            }
+            const Thr T = tab->t[hb.lvl[h] - 1 + LOFF];
+            if (!within<M>(P, o, cent[b + lcur], dcur, T, cnt + 1)) {
+                dv = dcur;
+                id = o;
+            }
+        }
+        report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
+        if (lane == 0 && j1 > j0)
+            atomicAdd(cnt, (unsigned long long)(j1 - j0) * (unsigned)(e - s));
     }
 }
 
@@ -1876,6 +2174,58 @@ Pts ingest_input(fnn_tree *T, const void *points, Scratch &S)
     }
 }
 
+// The screened update's copies and launches for rows of 16..128 floats.
+struct MxLevel {
+    bool on = false;
+    _Float16 *q = nullptr;
+    float *nrm = nullptr;
+    int32_t *pos = nullptr;
+    MxArgs a{};
+
+    template <int M, class F>
+    static void widths(int dp, F f)
+    {
+        if (dp <= 16)
+            f(std::integral_constant<int, 1>{});
+        else if (dp <= 32)
+            f(std::integral_constant<int, 2>{});
+        else if (dp <= 64)
+            f(std::integral_constant<int, 4>{});
+        else
+            f(std::integral_constant<int, 8>{});
+    }
+    // Rows below 16 floats keep the scan (a product would be mostly padding),
+    // as do sets whose copy does not fit easily.
+    void init(const Pts &P, const NodeArrays &nd, Scratch &S)
+    {
+        if ((P.metric != M_L2 && P.metric != M_ANG) || P.dp < 16 || P.dp > UPD_D)
+            return;
+        int kq = 128;
+        widths<M_L2>(P.dp, [&](auto k) { kq = 16 * decltype(k)::value; });
+        const size_t bytes = (size_t)P.n * (2 * kq + 8);
+        if (bytes > ((size_t)256 << 20)) {
+            size_t freeb = 0, totb = 0;
+            FNN_HIP(hipMemGetInfo(&freeb, &totb));
+            if (bytes > freeb / 8)
+                return;
+        }
+        q = S.get<_Float16>((size_t)P.n * kq);
+        nrm = S.get<float>(P.n);
+        pos = S.get<int32_t>(P.n);
+        const double u32 = 1.0 / 16777216.0, u = 1.0 / 2048.0, eta = ldexp(1.0, -25);
+        a.q = q;
+        a.nrm = nrm;
+        a.pos = pos;
+        a.center = nd.center;
+        a.radius = nd.radius;
+        a.c1 = (float)(2.25 * u + (4.0 * kq + 2.0 * P.dim + 72.0) * u32 +
+                       2.01 * eta * sqrt((double)kq));
+        a.add = (float)(4.02 * eta * sqrt((double)kq) + 2.0 * kq * eta * eta);
+        a.keyrel = (float)((8.0 * (P.dp + 8) + 64.0) * u32);
+        on = true;
+    }
+};
+
 // k_update_lev for the words and planes of the set's strings.
 template <class... A>
 static void launch_update_lev(dim3 g, hipStream_t s, const Pts &P, A... a)
@@ -2040,17 +2390,27 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                    cent);
     }
 
+    MxLevel mx;
+    if constexpr (M == M_L2 || M == M_ANG)
+        if (H > 0)
+            mx.init(P, nd, S);
+    int32_t *most = S.get<int32_t>(NLEV + 1);  // largest hub of every round
+    fill(most, 0, NLEV + 1, st);
     int rounds = 0, passes = 0;
     while (H > 0) {
         ++rounds;
         // chunk table of this level's hubs
         FNN_LAUNCH(k_hub_sizes, dim3(cdiv(H, 256)), dim3(256), 0, st,
-                           hubs.b, hubs.e, H, nch, hsz);
+                           hubs.b, hubs.e, H, nch, hsz, most + std::min(rounds, NLEV));
         scan_i32(nch, choff, H, S);
         scan_i32(hsz, itemoff, H, S);
-        int32_t tot[2] = {(int32_t)cdiv(n, CH), n};  // the root alone
+        int32_t tot[2] = {(int32_t)cdiv(n, CH), n}, big = n;  // the root alone
         if (rounds > 1 || NCL > 1)
-            Readback(st).add(&tot[0], choff + H).add(&tot[1], itemoff + H).wait();
+            Readback(st)
+                .add(&tot[0], choff + H)
+                .add(&tot[1], itemoff + H)
+                .add(&big, most + std::min(rounds, NLEV))
+                .wait();
         const int NC = tot[0], NH = tot[1];
         if (NC > maxch || NH > n)
             fail(FNN_EINTERNAL, "chunk table overflow (%d > %d)", NC, maxch);
@@ -2070,6 +2430,13 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
         const size_t upd_lds =
             (M == M_L2 || M == M_ANG) && T->dp <= UPD_D ? sizeof(float) * UPD_K * (T->dp + 4)
                                                         : 16;
+        if constexpr (M == M_L2 || M == M_ANG)
+            if (mx.on)
+                MxLevel::widths<M>(T->dp, [&](auto k) {
+                    FNN_LAUNCH((k_mx_rows<M, decltype(k)::value>), dim3(grid_cap(NC, 4, 8192)),
+                               dim3(256), 0, st, P, ch_hub, ch_s, ch_e, NC, hubs, perm,
+                               nd.center, nd.radius, mx.q, mx.nrm, mx.pos);
+                });
         // strings: a level of fewer hubs than CUs spreads its conflict tests;
         // from there on the hubs' own work-groups fill the chip
         SelPart *sp = nullptr;
@@ -2081,12 +2448,23 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                 launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, ch_s, ch_e, qc,
                                   qlen + k, qlen + (1 - k), hubs, cent, perm, D, L, tab, cb_D, cb_id,
                                   T->opt.kmax, cnt);
-            else
-                FNN_LAUNCH((k_update<M>), dim3(gu), dim3(CH * UPD_W), upd_lds, s, P, ch_hub,
-                           ch_s, ch_e, qc, qlen + k, qlen + (1 - k), hubs, cent, perm, D, L, tab, cb_D,
-                           cb_id, T->opt.kmax, cnt);
-            // (no hub of this level can have more than NC + 2 kmax candidates)
-            if (NC + 2ll * T->opt.kmax > SEL_PRE)
+            else {
+                if (mx.on) {
+                    if constexpr (M == M_L2 || M == M_ANG)
+                        MxLevel::widths<M>(T->dp, [&](auto kw) {
+                            FNN_LAUNCH((k_update_mx<M, decltype(kw)::value>), dim3(gu),
+                                       dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, qc,
+                                       qlen + k, qlen + (1 - k), hubs, cent, perm, D, L, tab,
+                                       cb_D, cb_id, T->opt.kmax, cnt, mx.a);
+                        });
+                } else {
+                    FNN_LAUNCH((k_update<M>), dim3(gu), dim3(CH * UPD_W), upd_lds, s, P,
+                               ch_hub, ch_s, ch_e, qc, qlen + k, qlen + (1 - k), hubs, cent,
+                               perm, D, L, tab, cb_D, cb_id, T->opt.kmax, cnt);
+                }
+            }
+            // (a hub of m chunks has at most m + 2 kmax candidates)
+            if (cdiv(big, CH) + 2ll * T->opt.kmax > SEL_PRE)
                 FNN_LAUNCH(k_select_pre, dim3(grid_cap((int64_t)H * SEL_SL, 1, 8192)),
                            dim3(SEL_T), 0, s, hubs, H, cb_D, cb_id, T->opt.kmax);
             const dim3 gs(grid_cap(H, 1, 4096));
