@@ -250,6 +250,18 @@ def roofline(dim, precision, tq, workload=""):
                 "traffic": measured_traffic(kname, workload),
                 "kernel": kname, "kernel_ms": round(kms, 3), "k": kq,
                 "flops_per_launch": flops}
+    if tq["filter_pairs"]:
+        # plain precision, screened: one FP16 product per pair of the tiles,
+        # the survivors' FP32 keys beside it
+        kq = next(w for w in (16, 32, 64, 128) if w >= dim)
+        flops = 2.0 * kq * tq["filter_pairs"]
+        ach = flops / (tq["count_ms"] / 1e3) / 1e12
+        kname = f"k_tile_screen<L2,k{kq}>"
+        return {"bound": "mfma", "achieved": round(ach, 3), "peak": PEAK_BF16_TFLOPS,
+                "unit": "TFLOP/s", "frac": round(ach / PEAK_BF16_TFLOPS, 4),
+                "traffic": measured_traffic(kname, workload),
+                "kernel": kname, "kernel_ms": round(tq["count_ms"], 3), "k": kq,
+                "flops_per_launch": flops}
     flops = 3.0 * dim * tq["tile_pairs"]
     ach = flops / (tq["count_ms"] / 1e3) / 1e12
     return {"bound": "alu", "achieved": round(ach, 3),

@@ -61,7 +61,8 @@ enum {
 
 /* Leaf-tile arithmetic of the query. */
 typedef enum {
-    FNN_PREC_FP32 = 0,   /* direct-difference FP32 tiles (the plain path)      */
+    FNN_PREC_FP32 = 0,   /* direct-difference FP32 tiles (the plain path);    */
+                         /* long lists are screened first: same results        */
     FNN_PREC_BF16 = 1,   /* MFMA BF16 Gram filter, FP32 recompute of survivors */
     FNN_PREC_FP8 = 2,    /* MFMA FP8 (E4M3) Gram filter, FP32 recompute        */
     FNN_PREC_I8 = 3,     /* Hamming codes of <= 256 bits: exact MFMA Gram of   */

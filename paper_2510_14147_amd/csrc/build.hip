@@ -28,7 +28,7 @@
 
 #include <algorithm>
 
-#include "tree.h"
+#include "gram.h"
 
 namespace fnn {
 
@@ -711,9 +711,8 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
 // (one FMA chain in index order), so D, L and the tree are the same bit for
 // bit.
 //
-// With |q(a).q(b) - a.b| below c1 (|a|^2 + |b|^2) / 2 + add / 2 in scaled
-// units (the filter's bound, see gram.hip), d^2 lies within
-// c1 (|a|^2 + |b|^2) + add of |a|^2 + |b|^2 - 2 g.  A centre is dropped when
+// With the margins of fp16_margin, d^2 lies within c1 (|a|^2 + |b|^2) + add
+// of |a|^2 + |b|^2 - 2 g (g the product).  A centre is dropped when
 // its smallest possible d^2 exceeds D^2, or the largest possible d^2 of the
 // batch's best one, both widened by the FP32 key's own rounding (keyrel).
 //
@@ -736,16 +735,8 @@ struct MxArgs {
     const int32_t *pos;      // [n] position of every hub point's input id
     const int32_t *center;   // of every vertex (input ids)
     const float *radius;
-    float c1, add, keyrel;
+    Fp16Margin m;
 };
-
-// 2^e with r 2^e in [2^13, 2^14) (e at most 60: squares stay finite).
-__device__ __forceinline__ float mx_scale(float r)
-{
-    int e = 0;
-    (void)frexpf(r, &e);  // r < 2^e
-    return ldexpf(1.f, min(14 - e, 60));
-}
 
 // Scaled FP16 rows and norms of every chunk (one wave each; eight lanes to a
 // row).
@@ -761,7 +752,7 @@ k_mx_rows(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__
     const int lane = threadIdx.x % CH, part = lane & 7, dp = P.dp;
     for (int c = blockIdx.x * 4 + threadIdx.x / CH; c < NC; c += gridDim.x * 4) {
         const int v = hb.node[ch_hub[c]];
-        const float sc = mx_scale(radius[v]);
+        const float sc = fp16_scale(radius[v]);
         const float *cr = X + (size_t)center[v] * dp;
         const int s = ch_s[c], m = ch_e[c] - s;
         for (int r0 = 0; r0 < m; r0 += 8) {
@@ -844,7 +835,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
     const int nq = *qlen;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         *qnext = 0;  // this pass's selection appends to it
-    const float omc1 = 1.f - A.c1;
+    const float omc1 = 1.f - A.m.c1;
     // no wave waits for another: a new centre is a point of the hub, so its
     // FP16 row is read from the level's copy like the points' own
     for (int t = blockIdx.x * UPD_W + w; t < nq; t += gridDim.x * UPD_W) {
@@ -858,7 +849,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
         float dcur = valid ? D[p] : 0.f;
         int lcur = valid ? L[p] : 0;
         if (j1 > j0) {
-            const float sc = mx_scale(A.radius[hb.node[h]]);
+            const float sc = fp16_scale(A.radius[hb.node[h]]);
             // this chunk's points: columns 32 cb + l32, k 16 ks + 8 hi ..
             mx_f16x8 B[2][NKS];
             float a2[2];
@@ -919,12 +910,12 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                     for (int q = 1; q < 16; ++q)
                         mx = fmaxf(mx, acc[cb][q]);
                     mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-                    const float lo = 0.5f * (omc1 * a2[cb] - D2 - A.add) -
-                                     A.keyrel * (mag + D2);
+                    const float lo = 0.5f * (omc1 * a2[cb] - D2 - A.m.add) -
+                                     A.m.keyrel * (mag + D2);
                     if (__ballot(s + pi < e && mx >= lo) == 0ull)
                         continue;  // no point of this block can come nearer
                     const float thr =
-                        fmaxf(lo, mx - (A.c1 + A.keyrel) * mag - A.add);
+                        fmaxf(lo, mx - (A.m.c1 + A.m.keyrel) * mag - A.m.add);
                     unsigned k = 0;
 #pragma unroll
                     for (int q = 0; q < 16; ++q)
@@ -2182,18 +2173,6 @@ struct MxLevel {
     int32_t *pos = nullptr;
     MxArgs a{};
 
-    template <int M, class F>
-    static void widths(int dp, F f)
-    {
-        if (dp <= 16)
-            f(std::integral_constant<int, 1>{});
-        else if (dp <= 32)
-            f(std::integral_constant<int, 2>{});
-        else if (dp <= 64)
-            f(std::integral_constant<int, 4>{});
-        else
-            f(std::integral_constant<int, 8>{});
-    }
     // Rows below 16 floats keep the scan (a product would be mostly padding),
     // as do sets whose copy does not fit easily.
     void init(const Pts &P, const NodeArrays &nd, Scratch &S)
@@ -2201,7 +2180,7 @@ struct MxLevel {
         if ((P.metric != M_L2 && P.metric != M_ANG) || P.dp < 16 || P.dp > UPD_D)
             return;
         int kq = 128;
-        widths<M_L2>(P.dp, [&](auto k) { kq = 16 * decltype(k)::value; });
+        fp16_width(P.dp, [&](auto k) { kq = 16 * decltype(k)::value; });
         const size_t bytes = (size_t)P.n * (2 * kq + 8);
         if (bytes > ((size_t)256 << 20)) {
             size_t freeb = 0, totb = 0;
@@ -2212,16 +2191,12 @@ struct MxLevel {
         q = S.get<_Float16>((size_t)P.n * kq);
         nrm = S.get<float>(P.n);
         pos = S.get<int32_t>(P.n);
-        const double u32 = 1.0 / 16777216.0, u = 1.0 / 2048.0, eta = ldexp(1.0, -25);
         a.q = q;
         a.nrm = nrm;
         a.pos = pos;
         a.center = nd.center;
         a.radius = nd.radius;
-        a.c1 = (float)(2.25 * u + (4.0 * kq + 2.0 * P.dim + 72.0) * u32 +
-                       2.01 * eta * sqrt((double)kq));
-        a.add = (float)(4.02 * eta * sqrt((double)kq) + 2.0 * kq * eta * eta);
-        a.keyrel = (float)((8.0 * (P.dp + 8) + 64.0) * u32);
+        a.m = fp16_margin(kq, P.dp, P.dim);
         on = true;
     }
 };
@@ -2432,7 +2407,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                                                         : 16;
         if constexpr (M == M_L2 || M == M_ANG)
             if (mx.on)
-                MxLevel::widths<M>(T->dp, [&](auto k) {
+                fp16_width(T->dp, [&](auto k) {
                     FNN_LAUNCH((k_mx_rows<M, decltype(k)::value>), dim3(grid_cap(NC, 4, 8192)),
                                dim3(256), 0, st, P, ch_hub, ch_s, ch_e, NC, hubs, perm,
                                nd.center, nd.radius, mx.q, mx.nrm, mx.pos);
@@ -2451,7 +2426,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
             else {
                 if (mx.on) {
                     if constexpr (M == M_L2 || M == M_ANG)
-                        MxLevel::widths<M>(T->dp, [&](auto kw) {
+                        fp16_width(T->dp, [&](auto kw) {
                             FNN_LAUNCH((k_update_mx<M, decltype(kw)::value>), dim3(gu),
                                        dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, qc,
                                        qlen + k, qlen + (1 - k), hubs, cent, perm, D, L, tab,

@@ -162,4 +162,55 @@ void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &
 void gram_launch(int metric, int prec, bool fill_pass, const Pts &P,
                  const GramArgs &G, const TileOut &o, hipStream_t s);
 
+// ---- pairs screened by FP16 products in a local frame --------------------
+//
+// Rows are taken as (x - c) 2^e, c a nearby point and 2^e such that r 2^e
+// lies in [2^13, 2^14) for a radius r that covers them (e at most 60: the
+// squares stay finite).
+__device__ __forceinline__ float fp16_scale(float r)
+{
+    int e = 0;
+    (void)frexpf(r, &e);  // r < 2^e
+    return ldexpf(1.f, min(14 - e, 60));
+}
+
+// With q() the rounding to FP16 and kq coordinates, |q(a).q(b) - a.b| is at
+// most c1 (|a|^2 + |b|^2) / 2 + add / 2 in scaled units (derived with the
+// filter's bound, see quantise_real), and the FP32 key of a pair differs
+// from |a - b|^2 by at most keyrel (|a|^2 + |b|^2 + |a - b|^2).
+struct Fp16Margin {
+    float c1, add, keyrel;
+};
+inline Fp16Margin fp16_margin(int kq, int dp, int dim)
+{
+    const double u32 = 1.0 / 16777216.0, u = 1.0 / 2048.0, eta = ldexp(1.0, -25);
+    Fp16Margin m;
+    m.c1 = (float)(2.25 * u + (4.0 * kq + 2.0 * dim + 72.0) * u32 +
+                   2.01 * eta * sqrt((double)kq));
+    m.add = (float)(4.02 * eta * sqrt((double)kq) + 2.0 * kq * eta * eta);
+    m.keyrel = (float)((8.0 * (dp + 8) + 64.0) * u32);
+    return m;
+}
+
+// f(NKS) for the narrowest product width 16 NKS that holds dp <= 128
+// coordinates
+template <class F>
+inline void fp16_width(int dp, F &&f)
+{
+    if (dp <= 16)
+        f(std::integral_constant<int, 1>{});
+    else if (dp <= 32)
+        f(std::integral_constant<int, 2>{});
+    else if (dp <= 64)
+        f(std::integral_constant<int, 4>{});
+    else
+        f(std::integral_constant<int, 8>{});
+}
+
+// Screens the point pairs of a list of pack pairs; those that may be edges
+// go to the survivor list (G.surv, G.nsurv).  Needs rows of at most 128
+// coordinates.
+void screen_tiles(const fnn_tree *T, const Pts &P, const GramArgs &G, const int2 *inter,
+                  long long ninter, const TileOut &o, hipStream_t s);
+
 }  // namespace fnn

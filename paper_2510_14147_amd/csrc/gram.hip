@@ -1660,6 +1660,225 @@ k_gram_direct(Pts P, GramArgs G, TileOut out)
     surv_flush(G, survS[w], (unsigned)__builtin_amdgcn_readfirstlane((int)fillS[w]));
 }
 
+// Plain-precision tiles of long lists, screened: the pairs of a pack pair
+// that may be edges by an FP16 product, at a margin that follows the packs'
+// own size, go to the survivor list and are decided there exactly as a tile
+// decides them (same FP32 key, same FP64 band), so the graph is the same bit
+// for bit.
+//
+// A wave takes a pack pair and waits for no other: the larger pack's 64
+// points, as (x - c) 2^e with c its centre and e from its radius (which
+// bounds where the other pack can lie), become one MFMA operand in registers,
+// the other pack's rows 32 at a time the second one, converted as they are
+// loaded.  No copy of the rows is made: a pack meets packs of all sizes, and
+// one scale for all would widen the margin past eps on clustered data (where
+// one works, the filter above is faster).
+//
+// What bounds it: the chain of loads of a pack pair (list, packs, rows) and
+// their latency; its products take a tenth of the time.  581K x 55, 7.0e9
+// pairs: 30.3 ms of tiles -> 6.1 here + 2.5 deciding 0.5 % of them; 64 clouds
+// x 16, 7.3e9 pairs: 20.9 -> 4.2 + 4.4 (1.0 %).
+template <int M, int NKS>
+__global__ void __launch_bounds__(256, NKS >= 8 ? 2 : NKS >= 4 ? 3 : 4)  // unspilled
+k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
+              long long ninter, const int32_t *__restrict__ q_cpos,
+              const float *__restrict__ q_rad, TileOut out)
+{
+    constexpr int KQ = 16 * NKS;
+    __shared__ __align__(16) float cen_s[4][KQ];    // the frame's origin
+    __shared__ __align__(16) float cterm_s[4][32];  // -(1 - c1) |b|^2 / 2
+    __shared__ int2 surv_s[4][SURV_BUF];
+    const float *X = M == M_ANG ? P.xn : P.x;
+    const int dp = P.dp;
+    const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
+    const int l32 = lane & 31, hi = lane >> 5;
+    const uint64_t ltmask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    float *cen = cen_s[w], *cterm = cterm_s[w];
+    int2 *sb = surv_s[w];
+    unsigned fill = 0;
+    unsigned long long npairs = 0;
+    const float omc1 = 1.f - mg.c1;
+    for (long long it = (long long)blockIdx.x * 4 + w; it < ninter; it += (long long)gridDim.x * 4) {
+        int A = __builtin_amdgcn_readfirstlane(inter[it].x);
+        int B = __builtin_amdgcn_readfirstlane(inter[it].y);
+        const bool diag = A == B;
+        if (q_rad[A] < q_rad[B]) {
+            const int t = A;
+            A = B;
+            B = t;
+        }
+        const int a0 = G.q_pb[A], na = G.q_pe[A] - a0;
+        const int b0 = G.q_pb[B], nb = G.q_pe[B] - b0;
+        const float e2 = G.pcl ? G.ct[G.pcl[a0]].e2f : G.e2f;
+        const float sc = fp16_scale(3.f * q_rad[A] + sqrtf(e2));
+        const float D2 = e2 * (sc * sc);
+        npairs += diag ? (unsigned long long)na * (na - 1) / 2 : (unsigned long long)na * nb;
+        const float *C = X + (size_t)q_cpos[A] * dp;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        for (int k = lane; k < KQ; k += WAVE)
+            cen[k] = k < dp ? C[k] : 0.f;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        // a lane's half (k 16 ks + 8 hi ..) of a row, scaled; its |.|^2
+        auto frag = [&](int p, f16x8 (&f)[NKS]) {
+            const float *x = X + (size_t)p * dp;
+            float4 u[2 * NKS];
+#pragma unroll
+            for (int i = 0; i < 2 * NKS; ++i) {
+                const int k = 16 * (i >> 1) + 8 * hi + 4 * (i & 1);
+                u[i] = k < dp ? *reinterpret_cast<const float4 *>(x + k)
+                              : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+            float ss = 0.f;
+#pragma unroll
+            for (int i = 0; i < 2 * NKS; ++i) {
+                const int k = 16 * (i >> 1) + 8 * hi + 4 * (i & 1);
+                const float4 c = *reinterpret_cast<const float4 *>(cen + k);
+                const float v0 = (u[i].x - c.x) * sc, v1 = (u[i].y - c.y) * sc,
+                            v2 = (u[i].z - c.z) * sc, v3 = (u[i].w - c.w) * sc;
+                ss = fmaf(v0, v0, fmaf(v1, v1, fmaf(v2, v2, fmaf(v3, v3, ss))));
+                f[i >> 1][4 * (i & 1)] = (_Float16)v0;
+                f[i >> 1][4 * (i & 1) + 1] = (_Float16)v1;
+                f[i >> 1][4 * (i & 1) + 2] = (_Float16)v2;
+                f[i >> 1][4 * (i & 1) + 3] = (_Float16)v3;
+            }
+            return ss + __shfl_xor(ss, 32, WAVE);
+        };
+        for (int ia = 0; ia < na; ia += 64) {
+            f16x8 Bf[2][NKS];
+            float a2[2];
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+                a2[cb] = frag(a0 + min(ia + cb * 32 + l32, na - 1), Bf[cb]);
+            for (int jb = diag ? ia : 0; jb < nb; jb += 32) {
+                f16x8 Af[NKS];
+                const float n2 = frag(b0 + min(jb + l32, nb - 1), Af);
+                const float b2 = wave_max(n2);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                if (hi == 0)
+                    cterm[l32] = jb + l32 < nb ? -0.5f * omc1 * n2 : -FLT_MAX;
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                f32x16 acc[2];
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const float4 v = *reinterpret_cast<const float4 *>(cterm + 8 * q4 + 4 * hi);
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        acc[cb][4 * q4] = v.x;
+                        acc[cb][4 * q4 + 1] = v.y;
+                        acc[cb][4 * q4 + 2] = v.z;
+                        acc[cb][4 * q4 + 3] = v.w;
+                    }
+                }
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb)
+                        acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[ks], Bf[cb][ks],
+                                                                        acc[cb], 0, 0, 0);
+                // a coordinate beyond FP16 (no pack pair of the traversal has
+                // one): every pair of the block survives
+                const bool wild = __any(!(a2[0] < 4e9f) || !(a2[1] < 4e9f) || !(n2 < 4e9f));
+                // rows past nb, and on a self pair rows up to the column's
+                const bool part = jb + 32 > nb || (diag && jb < ia + 64) || wild;
+                unsigned mask[2] = {0u, 0u};
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    const int ca = ia + cb * 32 + l32;
+                    const float mag = a2[cb] + b2;
+                    const float lo = 0.5f * (omc1 * a2[cb] - D2 - mg.add) -
+                                     mg.keyrel * (mag + D2);
+                    float mx = acc[cb][0];
+#pragma unroll
+                    for (int q = 1; q < 16; ++q)
+                        mx = fmaxf(mx, acc[cb][q]);
+                    if (!__any(ca < na && mx >= lo) && !wild)
+                        continue;
+                    unsigned k = 0;
+#pragma unroll
+                    for (int q = 0; q < 16; ++q)
+                        k |= acc[cb][q] >= lo ? 1u << q : 0u;
+                    if (part) {
+                        const int top = diag ? ca : -1;  // rows above it
+                        unsigned ok = 0;
+#pragma unroll
+                        for (int q = 0; q < 16; ++q) {
+                            const int r = jb + 8 * (q >> 2) + 4 * hi + (q & 3);
+                            ok |= r < nb && r > top ? 1u << q : 0u;
+                        }
+                        k = wild ? ok : k & ok;
+                    }
+                    mask[cb] = ca < na ? k : 0u;
+                }
+                unsigned todo = mask[0] | mask[1] << 16;
+                if (!__any(todo != 0u))
+                    continue;
+                // the lane's count (at most 32: six bits), its exclusive
+                // prefix over the wave and the wave's total
+                const unsigned c = __popc(todo);
+                unsigned pre = 0, tot = 0;
+#pragma unroll
+                for (int b = 0; b < 6; ++b) {
+                    const uint64_t m = __ballot((c >> b) & 1u);
+                    pre += (unsigned)__popcll(m & ltmask) << b;
+                    tot += (unsigned)__popcll(m) << b;
+                }
+                if (fill + tot > (unsigned)SURV_BUF) {
+                    surv_flush(G, sb, fill);
+                    fill = 0;
+                }
+                unsigned long long o = 0;  // slots in the list, if not in sb
+                const bool direct = tot > (unsigned)SURV_BUF;
+                if (direct) {
+                    if (lane == 0)
+                        o = atomicAdd(G.nsurv, (unsigned long long)tot);
+                    o = uniform_u64(o) + pre;
+                }
+                unsigned f = fill + pre;
+                while (todo) {
+                    const int bit = __ffs(todo) - 1;
+                    todo &= todo - 1;
+                    const int q = bit & 15;
+                    const int2 e = make_int2(
+                        a0 + ia + (bit >> 4) * 32 + l32,
+                        (b0 + jb + 8 * (q >> 2) + 4 * hi + (q & 3)) | (int)0x80000000u);
+                    if (!direct) {
+                        sb[f++] = e;
+                    } else {
+                        if ((long long)o < G.surv_cap)
+                            G.surv[o] = e;
+                        ++o;
+                    }
+                }
+                if (!direct)
+                    fill += tot;
+            }
+        }
+    }
+    surv_flush(G, sb, fill);
+    if (lane == 0 && npairs)
+        atomicAdd(&out.cnt[2], npairs);
+}
+
+void screen_tiles(const fnn_tree *T, const Pts &P, const GramArgs &G, const int2 *inter,
+                  long long ninter, const TileOut &o, hipStream_t s)
+{
+    if (ninter <= 0)
+        return;
+    int kq = 0;
+    fp16_width(P.dp, [&](auto w) { kq = 16 * decltype(w)::value; });
+    const Fp16Margin mg = fp16_margin(kq, P.dp, P.dim);
+    // resident work-groups, a few rounds of each
+    const dim3 g(grid_cap(ninter, 4, 16 * num_cus()));
+    fp16_width(P.dp, [&](auto w) {
+        if (P.metric == M_ANG)
+            FNN_LAUNCH((k_tile_screen<M_ANG, decltype(w)::value>), g, dim3(256), 0, s, P, G, mg,
+                       inter, ninter, T->q_center_pos, T->q_radius, o);
+        else
+            FNN_LAUNCH((k_tile_screen<M_L2, decltype(w)::value>), g, dim3(256), 0, s, P, G, mg,
+                       inter, ninter, T->q_center_pos, T->q_radius, o);
+    });
+}
+
 // The exact filter for Hamming codes of W = S1 + S2 words, the narrow
 // kernel's scheme on 32 x 32 x 64 products of 4-bit floats (one word of both
 // codes per instruction).  With S2 > 0 a block first takes only its first S1

@@ -1929,6 +1929,13 @@ constexpr double TRAV_MS = 0.4, TRAV_POINT_MS = 4e-6, TRAV_PAIR_MS = 4.2e-7;
 // joins two trees first: about 1.2 ms of launches and host reads more.
 constexpr double QUERY_TREE_MS = 1.2;
 
+// Plain-precision tiles of 16..128 coordinates are screened from SCREEN_MIN
+// pairs on (the tiles of fewer take under 0.15 ms) while at most one pair in
+// SCREEN_RATIO survives: a survivor costs 80 ps (decision and placement), a
+// screened pair saves 2.2 (16 coordinates) to 3.4 ps (55).
+constexpr unsigned long long SCREEN_MIN = 30000000ull;
+constexpr unsigned long long SCREEN_RATIO = 32;
+
 // Device view of a tree's points (tree order).
 static Pts tree_points(const fnn_tree *T)
 {
@@ -2155,6 +2162,28 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         int2 *gedges = nullptr;
         float *gedist = nullptr;
         long long ngedges = 0;
+        // survivors decided exactly; slot per survivor: holes where it is no
+        // edge
+        auto decide = [&](long long got) {
+            // with no plain tiles in the query every CSR entry
+            // comes from a survivor: keep the ranks its degree
+            // counters return and place it without cursors
+            // (measured at C2: 2.2 ms faster at ~53 survivors per
+            // point, 15 ms at ~350), while the ranks take under a
+            // quarter of the free device memory
+            size_t free_now = 0, tot_now = 0;
+            FNN_HIP(hipMemGetInfo(&free_now, &tot_now));
+            const bool ranks =
+                nplain == 0 &&
+                (double)(got + 1) * sizeof(int2) < 0.25 * (double)free_now;
+            gedges = S.get<int2>(got + 1);
+            gedist = S.get<float>(got + 1);
+            if (ranks)
+                G.erank = S.get<int2>(got + 1);
+            // slot per survivor: holes where it is no edge
+            survivors_launch(M, P, G, got, gedges, gedist, o, s);
+            ngedges = got;
+        };
         if (use_gram) {
             unsigned long long *ns = S.get<unsigned long long>(2);
             Events fev(s);
@@ -2212,29 +2241,54 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                         FNN_HIP(hipEventElapsedTime(&fms, fev[0], fev[1]));
                         st.filter_ms = fms;
                     }
-                    // with no plain tiles in the query every CSR entry
-                    // comes from a survivor: keep the ranks its degree
-                    // counters return and place it without cursors
-                    // (measured at C2: 2.2 ms faster at ~53 survivors per
-                    // point, 15 ms at ~350), while the ranks take under a
-                    // quarter of the free device memory
-                    size_t free_now = 0, tot_now = 0;
-                    FNN_HIP(hipMemGetInfo(&free_now, &tot_now));
-                    const bool ranks =
-                        nplain == 0 &&
-                        (double)(got + 1) * sizeof(int2) < 0.25 * (double)free_now;
-                    gedges = S.get<int2>(got + 1);
-                    gedist = S.get<float>(got + 1);
-                    if (ranks)
-                        G.erank = S.get<int2>(got + 1);
-                    // slot per survivor: holes where it is no edge
-                    survivors_launch(M, P, G, got, gedges, gedist, o, s);
-                    ngedges = got;
+                    decide(got);
                     break;
                 }
                 S.release(G.surv);
                 cap = got + got / 8 + 1024;
                 ++novf;  // a second filter pass was needed
+            }
+        }
+        unsigned long long bound = 0;  // pairs the plain tiles hold
+        if (nplain > 0) {
+            unsigned long long *pb_ = cnt + 9;
+            FNN_LAUNCH(k_pair_bound, dim3(grid_for(nplain, 256)), dim3(256), 0, s,
+                       plain, nplain, T->q_pt_begin, T->q_pt_end, pb_);
+            bound = read_scalar(pb_, s);
+        }
+        // Plain precision, long lists of vector rows: screened first, and
+        // only the pairs that may be edges computed.  More of them than the
+        // list takes: the tiles run instead.
+        if constexpr (M == M_L2 || M == M_ANG) {
+            if (!use_gram && T->dp >= 16 && T->dp <= 128 && bound >= SCREEN_MIN) {
+                size_t freeb = 0, totb = 0;
+                FNN_HIP(hipMemGetInfo(&freeb, &totb));
+                long long cap = (long long)std::min<unsigned long long>(
+                    bound / SCREEN_RATIO, freeb / 16 / sizeof(int2));
+                if (opt.list_cap > 0)
+                    cap = opt.list_cap;
+                unsigned long long *ns = S.get<unsigned long long>(1);
+                fill(ns, 0ull, 1, s);
+                G.surv = S.get<int2>(cap);
+                G.surv_cap = cap;
+                G.nsurv = ns;
+                G.e2f = ct_h[0].e2f;
+                G.E = E;
+                G.ct = ncl > 1 ? ct_d : nullptr;
+                G.pcl = ncl > 1 ? T->pcl : nullptr;
+                G.q_pb = T->q_pt_begin;
+                G.q_pe = T->q_pt_end;
+                G.perm = T->perm;
+                G.fp64_dist = fp64_dist;
+                screen_tiles(T, P, G, plain, nplain, o, s);
+                const long long got = (long long)read_scalar(ns, s);
+                if (got <= cap) {
+                    nplain = 0;
+                    decide(got);
+                } else {
+                    S.release(G.surv);
+                    fill(cnt + 2, 0ull, 1, s);
+                }
             }
         }
         // Plain tiles: count degrees and append each edge, in both
@@ -2245,10 +2299,6 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         bool listed = false;
         long long nlisted = 0;
         if (nplain > 0) {
-            unsigned long long *pb_ = cnt + 9;
-            FNN_LAUNCH(k_pair_bound, dim3(grid_for(nplain, 256)), dim3(256), 0, s,
-                       plain, nplain, T->q_pt_begin, T->q_pt_end, pb_);
-            const unsigned long long bound = read_scalar(pb_, s);
             size_t freeb = 0, totb = 0;
             FNN_HIP(hipMemGetInfo(&freeb, &totb));
             const unsigned long long room = (unsigned long long)(freeb / 8 / 12);
@@ -2300,7 +2350,7 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
             FNN_LAUNCH(k_cursor_init, dim3(grid_for(nr, 256)), dim3(256), 0, s,
                        C->row_ptr, nr, o.cursor);
             if (nnz > 0) {
-                if (use_gram)
+                if (gedges)
                     edges_scatter(gedges, gedist, ngedges, !rect, o, s);
                 if (listed)
                     edges_scatter(o.elist, o.edist, nlisted, false, o, s);
