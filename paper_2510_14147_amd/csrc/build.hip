@@ -411,7 +411,7 @@ __device__ __forceinline__ int cand_per_chunk(int nch, int kmax)
 }
 constexpr int UPD_D = 128;  // largest row stride staged in LDS
 
-constexpr int UPD_W = 4;  // queue entries (one wave each) per work-group
+constexpr int UPD_W = 4;  // chunks (one wave each) per work-group
 static_assert(CH == 64 && UPD_K % 8 == 0, "lane layout of the distance loop");
 
 // One point per lane against a staged batch of nj (<= UPD_K) centres
@@ -505,6 +505,27 @@ __device__ __forceinline__ void upd_lane(const float *__restrict__ X, int o, flo
 
 // The chunk's R farthest uncovered points (dv, id of each lane; dv < 0:
 // covered), farthest first.  Called by a whole wave.
+// Evaluations and FP64 rechecks are counted in CNT_SLOTS pairs of counters a
+// line apart, summed at the end: adds to one address take 12 ns each, one
+// after another (a count per chunk was 190 of the 205 us of an update of 988K
+// codes, 360 of 410 us of one of 2.1M points x 16).
+constexpr int CNT_SLOTS = 256, CNT_LINE = 16;
+__device__ __forceinline__ unsigned long long *count_slot(unsigned long long *cnt, int i)
+{
+    return cnt + (size_t)(i % CNT_SLOTS) * CNT_LINE;
+}
+__global__ void __launch_bounds__(CNT_SLOTS)
+k_count_sum(const unsigned long long *__restrict__ cnt, unsigned long long *__restrict__ out)
+{
+    unsigned long long a = cnt[threadIdx.x * CNT_LINE], b = cnt[threadIdx.x * CNT_LINE + 1];
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if ((threadIdx.x & (WAVE - 1)) == 0) {
+        atomicAdd(&out[0], a);
+        atomicAdd(&out[1], b);
+    }
+}
+
 __device__ __forceinline__ void report_chunk(int c, int R, float dv, int id,
                                              float *__restrict__ cb_D,
                                              int32_t *__restrict__ cb_id)
@@ -536,8 +557,8 @@ __device__ __forceinline__ void report_chunk(int c, int R, float dv, int id,
 template <int M>
 __global__ void __launch_bounds__(CH * UPD_W)
 k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
-         const int32_t *__restrict__ ch_e, const int32_t *__restrict__ queue,
-         const int32_t *__restrict__ qlen, int32_t *__restrict__ qnext, Hubs hb,
+         const int32_t *__restrict__ ch_e, int NC, const int32_t *__restrict__ live,
+         int32_t *__restrict__ live_next, Hubs hb,
          const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
          float *__restrict__ D, int32_t *__restrict__ L,
          const LevelTab *__restrict__ tab, float *__restrict__ cb_D,
@@ -546,19 +567,19 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
     // staged centres: UPD_K rows of the point stride (sized at launch, so
     // low-dimensional inputs keep many work-groups resident), shared by the
     // work-group's waves whose chunks belong to the same hub (a hub's chunks
-    // are consecutive in the queue)
+    // are consecutive)
     extern __shared__ __align__(16) float cen[];
     __shared__ __align__(16) float ustg[UPD_W][CH * US_LDR];  // each wave's staged rows
     __shared__ int hub_s[UPD_W];
     const int w = threadIdx.x / CH, lane = threadIdx.x % CH;
-    // the queue lists the chunks of the hubs still active (device-resident
-    // length, so passes need no host round trip)
-    const int nq = *qlen;
+    // every chunk of the level while a hub is still active (a flag on the
+    // device, so passes need no host round trip); those of the others skip
+    const int nq = *live ? NC : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
-        *qnext = 0;  // this pass's selection appends to it
+        *live_next = 0;  // set by this pass's selection
     for (int t0 = blockIdx.x * UPD_W; t0 < nq; t0 += gridDim.x * UPD_W) {
     const int t = t0 + w;
-    const int c = t < nq ? queue[t] : 0;
+    const int c = t < nq ? t : 0;
     const int h = t < nq ? ch_hub[c] : 0;
     const bool act = t < nq && hb.act[h];
     const int s = act ? ch_s[c] : 0, e = act ? ch_e[c] : 0;
@@ -633,46 +654,7 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
         }
     }
     if (valid) {
-        bool scanned = staged;  // the new centres already compared
-        if constexpr (M == M_HAM) {
-            if (!scanned && P.dp <= 4) {
-                // codes of up to 256 bits: the point's words stay in
-                // registers and eight centres' indices and words are
-                // fetched at once (the scan order is unchanged)
-                uint64_t mine[4];
-#pragma unroll
-                for (int w = 0; w < 4; ++w)
-                    mine[w] = w < P.dp ? P.h[(size_t)o * P.dp + w] : 0ull;
-                for (int j = j0; j < j1; j += 8) {
-                    int cj[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        cj[u] = j + u < j1 ? cent[b + j + u] : -1;
-                    uint64_t cw[8][4];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-#pragma unroll
-                        for (int w = 0; w < 4; ++w)
-                            cw[u][w] = cj[u] >= 0 && w < P.dp ? P.h[(size_t)cj[u] * P.dp + w]
-                                                              : 0ull;
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (cj[u] >= 0) {
-                            int dh = 0;
-#pragma unroll
-                            for (int w = 0; w < 4; ++w)
-                                dh += __popcll(mine[w] ^ cw[u][w]);
-                            const float k = (float)dh;
-                            if (k < dcur) {
-                                dcur = k;
-                                lcur = j + u;
-                            }
-                        }
-                }
-                scanned = true;
-            }
-        }
-        if (!scanned)
+        if (!staged)
             for (int j = j0; j < j1; ++j) {
                 float k = key32<M>(P, o, cent[b + j]);
                 if (k < dcur) {
@@ -692,8 +674,6 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
     }
     if (act) {
         report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
-        if (lane == 0 && j1 > j0)
-            atomicAdd(cnt, (unsigned long long)(j1 - j0) * (unsigned)(e - s));
     }
     }
 }
@@ -716,15 +696,16 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
 // its smallest possible d^2 exceeds D^2, or the largest possible d^2 of the
 // batch's best one, both widened by the FP32 key's own rounding (keyrel).
 //
-// What bounds it: the chain of loads of a chunk (queue, hub, rows, centres)
+// What bounds it: the chain of loads of a chunk (hub, rows, centres)
 // over few passes in flight, and the keys left over.  A wave owns a chunk and
 // waits for no other: the new centres are points of the hub, so their FP16
 // rows are read from the level's copy, found by position, straight into
 // MFMA operands.  All updates of a build, plus the copies: 1M points x 128
-// 11.3 -> 6.7 + 0.5 ms, 581K x 55 (528 passes) 41.3 -> 16.6 + 0.1 ms, 50K x
-// 128 build 2.5 -> 1.7 ms (centres staged through LDS for eight waves with
-// two barriers a batch: 7.2 and 17.8 ms).  Three waves per SIMD for rows above
-// 32 floats: four spill the point operands and take 8.0 and 20.2 ms.
+// 11.3 -> 5.2 + 0.5 ms, 581K x 55 (528 passes) 41.3 -> 9.2 + 0.1 ms (with the
+// counters of count_slot; before those 6.7 and 16.6, and with centres staged
+// through LDS for eight waves, two barriers a batch, 7.2 and 17.8 ms).  Three
+// waves per SIMD for rows above 32 floats: four spill the point operands and
+// took 8.0 and 20.2 ms.
 typedef __attribute__((ext_vector_type(8))) _Float16 mx_f16x8;
 typedef __attribute__((ext_vector_type(4))) _Float16 mx_f16x4;
 typedef __attribute__((ext_vector_type(16))) float mx_f32x16;
@@ -818,8 +799,8 @@ __device__ __forceinline__ float mx_key(const float *__restrict__ a,
 template <int M, int NKS>
 __global__ void __launch_bounds__(CH *UPD_W, NKS >= 4 ? 3 : 4)  // unspilled
 k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
-            const int32_t *__restrict__ ch_e, const int32_t *__restrict__ queue,
-            const int32_t *__restrict__ qlen, int32_t *__restrict__ qnext, Hubs hb,
+            const int32_t *__restrict__ ch_e, int NC, const int32_t *__restrict__ live,
+            int32_t *__restrict__ live_next, Hubs hb,
             const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
             float *__restrict__ D, int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
             float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax,
@@ -832,14 +813,14 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
     const int w = threadIdx.x / CH, lane = threadIdx.x % CH;
     const int l32 = lane & 31, hi = lane >> 5;
     float *cterm = cterm_s[w];
-    const int nq = *qlen;
+    const int nq = *live ? NC : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
-        *qnext = 0;  // this pass's selection appends to it
+        *live_next = 0;  // set by this pass's selection
     const float omc1 = 1.f - A.m.c1;
     // no wave waits for another: a new centre is a point of the hub, so its
     // FP16 row is read from the level's copy like the points' own
     for (int t = blockIdx.x * UPD_W + w; t < nq; t += gridDim.x * UPD_W) {
-        const int c = queue[t], h = ch_hub[c];
+        const int c = t, h = ch_hub[c];
         if (!hb.act[h])
             continue;
         const int s = ch_s[c], e = ch_e[c], p = s + lane;
@@ -978,8 +959,87 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
             }
         }
         report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
-        if (lane == 0 && j1 > j0)
-            atomicAdd(cnt, (unsigned long long)(j1 - j0) * (unsigned)(e - s));
+    }
+}
+
+// k_update for codes of up to 64 NW bits.  A wave owns a chunk: every lane
+// keeps its point's code in registers and fetches one of 64 new centres'
+// codes, and each centre is then broadcast from its lane's registers (one
+// scalar read per word), so a batch costs two dependent loads where a lane
+// that reads every centre itself costs two for eight centres.
+//
+// What bounds it: the points' scattered codes and the exclusive-or, count and
+// broadcast of every word (three instructions).  988258 codes of 256 bits,
+// 2.0e9 evaluations in 76 passes: 10.4 -> 3.2 ms, the counters' share
+// included (see count_slot).
+template <int NW>
+__global__ void __launch_bounds__(CH *UPD_W)
+k_update_ham(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
+             const int32_t *__restrict__ ch_e, int NC, const int32_t *__restrict__ live,
+             int32_t *__restrict__ live_next, Hubs hb,
+             const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
+             float *__restrict__ D, int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
+             float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax,
+             unsigned long long *__restrict__ cnt)
+{
+    const int w = threadIdx.x / CH, lane = threadIdx.x % CH, W = P.dp;
+    const int nq = *live ? NC : 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *live_next = 0;  // set by this pass's selection
+    auto code = [&](int id, uint32_t (&v)[2 * NW]) {
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const uint64_t x = i < W ? P.h[(size_t)id * W + i] : 0ull;
+            v[2 * i] = (uint32_t)x;
+            v[2 * i + 1] = (uint32_t)(x >> 32);
+        }
+    };
+    for (int t = blockIdx.x * UPD_W + w; t < nq; t += gridDim.x * UPD_W) {
+        const int c = t, h = ch_hub[c];
+        if (!hb.act[h])
+            continue;
+        const int s = ch_s[c], e = ch_e[c], p = s + lane;
+        const bool valid = p < e;
+        const int b = hb.b[h], j0 = hb.ma[h], j1 = hb.m[h];
+        const int o = perm[valid ? p : s];
+        float dcur = valid ? D[p] : 0.f;
+        int lcur = valid ? L[p] : 0;
+        if (j1 > j0) {
+            uint32_t mine[2 * NW];
+            code(o, mine);
+            for (int jb = j0; jb < j1; jb += CH) {
+                const int m = min(CH, j1 - jb);
+                uint32_t cw[2 * NW];
+                code(cent[b + jb + min(lane, m - 1)], cw);
+#pragma unroll 2
+                for (int j = 0; j < m; ++j) {
+                    int d = 0;
+#pragma unroll
+                    for (int i = 0; i < 2 * NW; ++i)
+                        d += __popc(mine[i] ^
+                                    (uint32_t)__builtin_amdgcn_readlane((int)cw[i], j));
+                    const float k = (float)d;
+                    if (k < dcur) {
+                        dcur = k;
+                        lcur = jb + j;
+                    }
+                }
+            }
+        }
+        float dv = -1.f;
+        int id = INT_MAX;
+        if (valid) {
+            if (j1 > j0) {
+                D[p] = dcur;
+                L[p] = lcur;
+            }
+            const Thr T = tab->t[hb.lvl[h] - 1 + LOFF];
+            if (!within<M_HAM>(P, o, cent[b + lcur], dcur, T, cnt + 1)) {
+                dv = dcur;
+                id = o;
+            }
+        }
+        report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
     }
 }
 
@@ -994,8 +1054,8 @@ constexpr int LEV_W = 8;
 template <int NW, int NB>
 __global__ void __launch_bounds__(CH *LEV_W)
 k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
-             const int32_t *__restrict__ ch_e, const int32_t *__restrict__ queue,
-             const int32_t *__restrict__ qlen, int32_t *__restrict__ qnext, Hubs hb,
+             const int32_t *__restrict__ ch_e, int NC, const int32_t *__restrict__ live,
+             int32_t *__restrict__ live_next, Hubs hb,
              const int32_t *__restrict__ cent,
              const int32_t *__restrict__ perm, float *__restrict__ D,
              int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
@@ -1005,11 +1065,11 @@ k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restric
     __shared__ int sd[LEV_W][CH], sj[LEV_W][CH];
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CH));
     const int lane = threadIdx.x % CH;
-    const int nq = *qlen;
+    const int nq = *live ? NC : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
-        *qnext = 0;  // this pass's selection appends to it
+        *live_next = 0;  // set by this pass's selection
     for (int t = blockIdx.x; t < nq; t += gridDim.x) {
-        const int c = queue[t], h = ch_hub[c];
+        const int c = t, h = ch_hub[c];
         if (!hb.act[h])
             continue;  // the same for the whole work-group
         const int s = ch_s[c], e = ch_e[c], p = s + lane;
@@ -1067,8 +1127,6 @@ k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restric
             }
         }
         report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
-        if (lane == 0 && j1 > j0)
-            atomicAdd(cnt, (unsigned long long)(j1 - j0) * (unsigned)(e - s));
     }
 }
 
@@ -1394,22 +1452,22 @@ k_conflicts(Pts P, Hubs hb, int nt, SelPart *__restrict__ sp,
     }
     const int tests = __popcll(__ballot(in));
     if (threadIdx.x == 0 && tests)
-        atomicAdd(cnt, (unsigned long long)tests);
+        atomicAdd(count_slot(cnt, blockIdx.x), (unsigned long long)tests);
 }
 
 template <int M, int PH>
 __global__ void __launch_bounds__(SEL_T)
 k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
          const float *__restrict__ cb_D, const int32_t *__restrict__ cb_id,
-         const LevelTab *__restrict__ tab, int kmax, int32_t *__restrict__ qnext,
-         int32_t *__restrict__ qnext_len, unsigned long long *__restrict__ cnt,
+         const LevelTab *__restrict__ tab, int kmax, int32_t *__restrict__ live_next,
+         unsigned long long *__restrict__ cnt,
          SelPart *__restrict__ sp)
 {
     __shared__ unsigned long long buf[SEL_BUF], out[MAX_K];
     __shared__ unsigned long long conf[MAX_K][SEL_W];
     __shared__ __align__(16) float crow[SEL_CR * (UPD_D + 4)];  // staged candidate rows
     __shared__ int acc[MAX_K];
-    __shared__ int nacc_s, nk_s, qb_s, fill_s;
+    __shared__ int nacc_s, nk_s, fill_s;
     const int K = min(kmax, MAX_K);
     for (int h = blockIdx.x; h < H; h += gridDim.x) {
     if (!hb.act[h])
@@ -1605,28 +1663,21 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
         cent[b + m0 + a] = acc[a];
     tests = wave_sum(tests);
     if ((threadIdx.x & (WAVE - 1)) == 0 && tests)
-        atomicAdd(cnt, tests);
+        atomicAdd(count_slot(cnt, h * (SEL_T / WAVE) + threadIdx.x / WAVE), tests);
     if (threadIdx.x == 0) {
         hb.ma[h] = m0;
         hb.m[h] = m0 + nacc;
-        if (nacc == 0)
+        if (nacc == 0) {
             hb.act[h] = 0;
-        else  // the hub's chunks go to the next pass's queue
-            qb_s = atomicAdd(qnext_len, hb.ce[h] - hb.cb[h]);
+        } else {
+            *live_next = 1;  // every hub that goes on stores the same
+            // the next update compares every point with the new centres
+            atomicAdd(count_slot(cnt, h),
+                      (unsigned long long)nacc * (unsigned)(hb.e[h] - hb.b[h]));
+        }
     }
     __syncthreads();
-    if (nacc > 0)
-        for (int i = threadIdx.x; i < hb.ce[h] - hb.cb[h]; i += SEL_T)
-            qnext[qb_s + i] = hb.cb[h] + i;
-    __syncthreads();
     }
-}
-
-__global__ void k_iota(int32_t *__restrict__ q, int n)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += gridDim.x * blockDim.x)
-        q[i] = i;
 }
 
 // ----------------------------------------------------------- partition ---
@@ -2242,8 +2293,8 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     const int n = (int)T->n;
     int *err = S.get<int>(1);
     fill(err, 0, 1, st);
-    unsigned long long *cnt = S.get<unsigned long long>(4);
-    fill(cnt, 0ull, 4, st);
+    unsigned long long *cnt = S.get<unsigned long long>(CNT_SLOTS * CNT_LINE + 2);
+    fill(cnt, 0ull, CNT_SLOTS * CNT_LINE + 2, st);
 
     hipEvent_t ev0, ev1;
     FNN_HIP(hipEventCreate(&ev0));
@@ -2288,10 +2339,9 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
             *ch_e = S.get<int32_t>(maxch), *ch_k = S.get<int32_t>(maxch);
     float *cb_D = S.get<float>((size_t)maxch * CAND_R);
     int32_t *cb_id = S.get<int32_t>((size_t)maxch * CAND_R);
-    int32_t *qa = S.get<int32_t>(maxch), *qb = S.get<int32_t>(maxch);
-    int32_t *qlen = S.get<int32_t>(2);
-    // net-selection passes per graph replay (even: the live queue returns
-    // to qa); 1 = one eager pass per host check
+    int32_t *live_d = S.get<int32_t>(2);
+    // net-selection passes per graph replay (even: the flag read is live_d[0]
+    // again); 1 = one eager pass per host check
     const int GP = T->opt.graph_passes <= 1 ? 1 : (T->opt.graph_passes + 1) / 2 * 2;
 
     auto alloc_hubs = [&](int cnt_) {
@@ -2395,12 +2445,11 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                    ch_e, ch_k, NC, L, hpos);
 
         // ---- net selection passes ----------------------------------------
-        // Pass p: k_update over the queue of active chunks, k_select writes
-        // the next queue.  Once every hub is done both kernels do nothing,
+        // Pass p: k_update over the active hubs' chunks, k_select says
+        // whether a hub goes on.  Once every hub is done both do nothing,
         // so passes can run ahead of the host: G passes are recorded into a
-        // graph once per level and replayed until the queue is empty.
-        FNN_LAUNCH(k_iota, dim3(grid_for(NC, 256)), dim3(256), 0, st, qa, NC);
-        fill(qlen, NC, 1, st);
+        // graph once per level and replayed until no hub does.
+        fill(live_d, 1, 1, st);
         const unsigned gu = grid_cap(NC, UPD_W, 4096);
         const size_t upd_lds =
             (M == M_L2 || M == M_ANG) && T->dp <= UPD_D ? sizeof(float) * UPD_K * (T->dp + 4)
@@ -2418,23 +2467,33 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
         if (M == M_LEV && H < num_cus())
             sp = S.get<SelPart>(H);
         auto pass = [&](hipStream_t s, int k) {
-            int32_t *qc = k ? qb : qa, *qx = k ? qa : qb;
+            int32_t *lc = live_d + k, *lx = live_d + (1 - k);
             if constexpr (M == M_LEV)
-                launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, ch_s, ch_e, qc,
-                                  qlen + k, qlen + (1 - k), hubs, cent, perm, D, L, tab, cb_D, cb_id,
+                launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent, perm, D, L, tab, cb_D, cb_id,
                                   T->opt.kmax, cnt);
-            else {
+            else if (M == M_HAM && T->dp <= 8) {
+                auto go = [&](auto nw) {
+                    FNN_LAUNCH((k_update_ham<decltype(nw)::value>), dim3(gu), dim3(CH * UPD_W),
+                               0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs,
+                               cent, perm, D, L, tab, cb_D, cb_id, T->opt.kmax, cnt);
+                };
+                if (T->dp <= 2)
+                    go(std::integral_constant<int, 2>{});
+                else if (T->dp <= 4)
+                    go(std::integral_constant<int, 4>{});
+                else
+                    go(std::integral_constant<int, 8>{});
+            } else {
                 if (mx.on) {
                     if constexpr (M == M_L2 || M == M_ANG)
                         fp16_width(T->dp, [&](auto kw) {
                             FNN_LAUNCH((k_update_mx<M, decltype(kw)::value>), dim3(gu),
-                                       dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, qc,
-                                       qlen + k, qlen + (1 - k), hubs, cent, perm, D, L, tab,
+                                       dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent, perm, D, L, tab,
                                        cb_D, cb_id, T->opt.kmax, cnt, mx.a);
                         });
                 } else {
                     FNN_LAUNCH((k_update<M>), dim3(gu), dim3(CH * UPD_W), upd_lds, s, P,
-                               ch_hub, ch_s, ch_e, qc, qlen + k, qlen + (1 - k), hubs, cent,
+                               ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent,
                                perm, D, L, tab, cb_D, cb_id, T->opt.kmax, cnt);
                 }
             }
@@ -2448,17 +2507,17 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                     const int K = std::min(T->opt.kmax, MAX_K);
                     const int nt = (int)cdiv(std::max(1, K * (K - 1) / 2), WAVE);
                     FNN_LAUNCH((k_select<M, SEL_TOP>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent,
-                               cb_D, cb_id, tab, T->opt.kmax, qx, qlen + (1 - k), cnt, sp);
+                               cb_D, cb_id, tab, T->opt.kmax, lx, cnt, sp);
                     FNN_LAUNCH(k_conflicts, dim3((unsigned)(H * nt)), dim3(WAVE), 0, s, P,
                                hubs, nt, sp, tab, cnt);
                     FNN_LAUNCH((k_select<M, SEL_TAKE>), gs, dim3(SEL_T), 0, s, P, hubs, H,
-                               cent, cb_D, cb_id, tab, T->opt.kmax, qx, qlen + (1 - k), cnt,
+                               cent, cb_D, cb_id, tab, T->opt.kmax, lx, cnt,
                                sp);
                     return;
                 }
             }
             FNN_LAUNCH((k_select<M, SEL_ALL>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent, cb_D,
-                       cb_id, tab, T->opt.kmax, qx, qlen + (1 - k), cnt, nullptr);
+                       cb_id, tab, T->opt.kmax, lx, cnt, nullptr);
         };
         // The first passes of a level run eagerly with one read after them (a
         // graph of four passes costs 140 us to record, instantiate and drop,
@@ -2469,13 +2528,13 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
             pass(st, k & 1);
         passes += GP;
         scan_i32(hubs.m, child_base, H, S);
-        Readback(st).add(&live, qlen + (GP & 1)).add(&C, child_base + H).wait();
+        Readback(st).add(&live, live_d + (GP & 1)).add(&C, child_base + H).wait();
         if (live) {
             if (GP <= 1) {
                 for (int k = 1;; k ^= 1) {
                     pass(st, k);
                     ++passes;
-                    if (read_scalar(qlen + (1 - k), st) == 0)
+                    if (read_scalar(live_d + (1 - k), st) == 0)
                         break;
                 }
             } else {
@@ -2487,7 +2546,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                 for (;;) {
                     gr.launch(st);
                     passes += GP;
-                    if (read_scalar(qlen, st) == 0)
+                    if (read_scalar(live_d, st) == 0)
                         break;
                 }
             }
@@ -2641,9 +2700,10 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                            T->q_pt_end, T->dp, T->q_radius);
 
     FNN_HIP(hipEventRecord(ev1, st));
-    unsigned long long hc[4];
+    unsigned long long hc[2];
     int herr = 0;
-    Readback(st).add(hc, cnt, 4).add(&herr, err).wait();
+    FNN_LAUNCH(k_count_sum, dim3(1), dim3(CNT_SLOTS), 0, st, cnt, cnt + CNT_SLOTS * CNT_LINE);
+    Readback(st).add(hc, cnt + CNT_SLOTS * CNT_LINE, 2).add(&herr, err).wait();
     float ms = 0.f;
     FNN_HIP(hipEventElapsedTime(&ms, ev0, ev1));
     (void)hipEventDestroy(ev0);
