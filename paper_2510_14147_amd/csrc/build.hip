@@ -505,6 +505,16 @@ __device__ __forceinline__ void upd_lane(const float *__restrict__ X, int o, flo
 
 // The chunk's R farthest uncovered points (dv, id of each lane; dv < 0:
 // covered), farthest first.  Called by a whole wave.
+// Sort key of a chunk candidate: farther first, then the smaller input id
+// (0 = no candidate).
+__device__ __forceinline__ unsigned long long cand_key(float d, int id)
+{
+    if (!(d >= 0.f))
+        return 0ull;
+    return ((unsigned long long)__float_as_uint(d) << 32) |
+           (unsigned long long)(uint32_t)(0x7FFFFFFF - id);
+}
+
 // Evaluations and FP64 rechecks are counted in CNT_SLOTS pairs of counters a
 // line apart, summed at the end: adds to one address take 12 ns each, one
 // after another (a count per chunk was 190 of the 205 us of an update of 988K
@@ -526,9 +536,8 @@ k_count_sum(const unsigned long long *__restrict__ cnt, unsigned long long *__re
     }
 }
 
-__device__ __forceinline__ void report_chunk(int c, int R, float dv, int id,
-                                             float *__restrict__ cb_D,
-                                             int32_t *__restrict__ cb_id)
+__device__ __forceinline__ void report_chunk(int c, int NC, int R, float dv, int id,
+                                             unsigned long long *__restrict__ cand)
 {
     const int lane = threadIdx.x % CH;
     for (int r = 0; r < R; ++r) {
@@ -544,8 +553,7 @@ __device__ __forceinline__ void report_chunk(int c, int R, float dv, int id,
             }
         }
         if (lane == 0) {
-            cb_D[(size_t)c * CAND_R + r] = bd;
-            cb_id[(size_t)c * CAND_R + r] = bi;
+            cand[(size_t)r * NC + c] = cand_key(bd, bi);
         }
         if (id == bi && bd >= 0.f) {  // the winner leaves the race
             dv = -1.f;
@@ -561,8 +569,7 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
          int32_t *__restrict__ live_next, Hubs hb,
          const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
          float *__restrict__ D, int32_t *__restrict__ L,
-         const LevelTab *__restrict__ tab, float *__restrict__ cb_D,
-         int32_t *__restrict__ cb_id, int kmax, unsigned long long *__restrict__ cnt)
+         const LevelTab *__restrict__ tab, unsigned long long *__restrict__ cand, int kmax, unsigned long long *__restrict__ cnt)
 {
     // staged centres: UPD_K rows of the point stride (sized at launch, so
     // low-dimensional inputs keep many work-groups resident), shared by the
@@ -673,7 +680,7 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
         }
     }
     if (act) {
-        report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
+        report_chunk(c, NC, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cand);
     }
     }
 }
@@ -803,7 +810,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
             int32_t *__restrict__ live_next, Hubs hb,
             const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
             float *__restrict__ D, int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
-            float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax,
+            unsigned long long *__restrict__ cand, int kmax,
             unsigned long long *__restrict__ cnt, MxArgs A)
 {
     constexpr int KQ = 16 * NKS;
@@ -958,7 +965,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                 id = o;
             }
         }
-        report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
+        report_chunk(c, NC, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cand);
     }
 }
 
@@ -979,7 +986,7 @@ k_update_ham(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restric
              int32_t *__restrict__ live_next, Hubs hb,
              const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
              float *__restrict__ D, int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
-             float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax,
+             unsigned long long *__restrict__ cand, int kmax,
              unsigned long long *__restrict__ cnt)
 {
     const int w = threadIdx.x / CH, lane = threadIdx.x % CH, W = P.dp;
@@ -1039,7 +1046,7 @@ k_update_ham(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restric
                 id = o;
             }
         }
-        report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
+        report_chunk(c, NC, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cand);
     }
 }
 
@@ -1059,7 +1066,7 @@ k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restric
              const int32_t *__restrict__ cent,
              const int32_t *__restrict__ perm, float *__restrict__ D,
              int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
-             float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax,
+             unsigned long long *__restrict__ cand, int kmax,
              unsigned long long *__restrict__ cnt)
 {
     __shared__ int sd[LEV_W][CH], sj[LEV_W][CH];
@@ -1126,7 +1133,7 @@ k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restric
                 id = o;
             }
         }
-        report_chunk(c, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cb_D, cb_id);
+        report_chunk(c, NC, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cand);
     }
 }
 
@@ -1139,16 +1146,6 @@ constexpr int SEL_CR = 64;     // candidates whose rows are staged in LDS
 // a round always fits after a sort has cut buf to K keys
 constexpr int SEL_STEP = 4 * SEL_T;
 static_assert(SEL_STEP <= SEL_BUF - MAX_K, "top-K stream round too large");
-
-// Sort key of a chunk candidate: farther first, then the smaller input id
-// (0 = no candidate).
-__device__ __forceinline__ unsigned long long cand_key(float d, int id)
-{
-    if (!(d >= 0.f))
-        return 0ull;
-    return ((unsigned long long)__float_as_uint(d) << 32) |
-           (unsigned long long)(uint32_t)(0x7FFFFFFF - id);
-}
 
 __device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v, int m)
 {
@@ -1314,53 +1311,122 @@ __device__ int topk_stream(long long nv, int K, KeyF key, unsigned long long *bu
     return nk;
 }
 
-// The K largest of nv <= SEL_RANK keys (0: no candidate; the others are
-// distinct), in descending order in buf[0 .. nk), by rank: every key counts
-// the keys above it (a broadcast read per key of the buffer).  Returns nk.
-constexpr int SEL_RANK = 512;
-template <class KeyF>
-__device__ int topk_rank(int nv, int K, KeyF key, unsigned long long *buf,
-                         unsigned long long *out, int *cnt_s)
+// The K largest of the work-group's SEL_T keys v, one per thread (0: none;
+// the others are distinct), in descending order in out[0 .. nk); returns nk.
+// A wave ranks its 64 keys by broadcasts from its registers, and a key's rank
+// in the union adds its place in the other waves' sorted keys (srt).
+__device__ int rank_keys(unsigned long long v, int K, unsigned long long *srt,
+                         unsigned long long *out)
 {
-    if (threadIdx.x == 0)
-        *cnt_s = 0;
-    for (int v = threadIdx.x; v < nv; v += SEL_T)
-        buf[v] = key(v);
-    __syncthreads();
-    for (int v = threadIdx.x; v < nv; v += SEL_T) {
-        const unsigned long long k = buf[v];
-        if (!k)
-            continue;
-        atomicAdd(cnt_s, 1);
-        int r = 0;
-        // eight reads in flight (the buffer's tail past nv is never read)
-        int u = 0;
-        for (; u + 8 <= nv; u += 8) {
-#pragma unroll
-            for (int o = 0; o < 8; ++o)
-                r += buf[u + o] > k;
+    static_assert(SEL_T == 4 * WAVE, "four waves of 64 keys");
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    const unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
+    const int n = __popcll(__ballot(v != 0ull));  // this wave's keys
+    int r = 0;
+    if (n > 0) {
+#pragma unroll 16
+        for (int j = 0; j < WAVE; ++j) {
+            const unsigned long long o =
+                ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)hi, j) << 32) |
+                (unsigned)__builtin_amdgcn_readlane((int)lo, j);
+            r += o > v;
         }
-        for (; u < nv; ++u)
-            r += buf[u] > k;
-        if (r < K)
-            out[r] = k;
     }
+    // zeros share the rank n: the last places stay unwritten but for one
+    srt[w * WAVE + lane] = 0ull;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if (v)
+        srt[w * WAVE + r] = v;
     __syncthreads();
-    const int nk = min(K, *cnt_s);
+    // keys of the other waves above v: [0, p) of their 64, by bisection
+    int p[3] = {0, 0, 0};
+#pragma unroll
+    for (int step = WAVE / 2; step > 0; step >>= 1)
+#pragma unroll
+        for (int o = 0; o < 3; ++o) {
+            const int b = ((w + 1 + o) & 3) * WAVE;
+            if (srt[b + p[o] + step - 1] > v)
+                p[o] += step;
+        }
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+        if (srt[((w + 1 + o) & 3) * WAVE + p[o]] > v)
+            ++p[o];
+    r += p[0] + p[1] + p[2];
+    if (v && r < K)
+        out[r] = v;
+    const int tot = __syncthreads_count(v != 0ull);
+    return min(K, tot);
+}
+
+// The K <= MAX_K largest of nv distinct keys (0: no candidate), in descending
+// order in buf[0 .. nk); returns nk.  Up to SEL_T keys are ranked at once.
+// More are first cut to those at or above the K-th largest of the threads'
+// own maxima, a bound that K keys reach and few beyond them do; only where
+// more than SEL_T do are the keys streamed through the sort buffer.
+template <class KeyF>
+__device__ int topk(int nv, int K, KeyF key, unsigned long long *buf, int *fill_s,
+                    unsigned long long *out)
+{
+    unsigned long long v = 0ull;
+    if (nv <= SEL_T) {
+        if ((int)threadIdx.x < nv)
+            v = key(threadIdx.x);
+    } else {
+        if (threadIdx.x == 0)
+            *fill_s = 0;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < nv; i += SEL_T) {
+            const unsigned long long k = key(i);
+            v = k > v ? k : v;
+        }
+        const int nk = rank_keys(v, K, buf, out);
+        const unsigned long long thr = nk == K ? out[K - 1] : 1ull;
+        __syncthreads();  // buf is reused
+#pragma unroll 4
+        for (int i = threadIdx.x; i < nv; i += SEL_T) {
+            const unsigned long long k = key(i);
+            if (k >= thr) {
+                const int q = atomicAdd(fill_s, 1);
+                if (q < SEL_T)
+                    buf[q] = k;
+            }
+        }
+        __syncthreads();
+        const int m = *fill_s;
+        __syncthreads();
+        if (m > SEL_T)
+            return topk_stream(nv, K, key, buf, fill_s, out);
+        v = (int)threadIdx.x < m ? buf[threadIdx.x] : 0ull;
+        __syncthreads();  // buf holds the sorted keys next
+    }
+    const int nk = rank_keys(v, K, buf, out);
     for (int r = threadIdx.x; r < nk; r += SEL_T)
         buf[r] = out[r];
     __syncthreads();
     return nk;
 }
 
+// Where candidate q of a hub of nch chunks lies, from its first chunk's: the
+// chunks' r-th candidates (r < CAND_R) stand side by side, NC to a row.
+__device__ __forceinline__ size_t cand_at(int q, int nch, int NC)
+{
+    int r = 0;
+    for (; q >= nch; q -= nch)
+        ++r;
+    return (size_t)r * NC + q;
+}
+
 // Candidate slices of a hub with many candidates (more than SEL_PRE): nsl
 // slices of len candidates each (the last may be shorter); 0 when the hub
 // streams its candidates whole.
 constexpr int SEL_SL = 8;                // slices per hub at most
-constexpr long long SEL_PRE = 2 * SEL_STEP;
-__device__ __forceinline__ void sel_slices(long long ncand, int &nsl, long long &len)
+// (one work-group takes 15.6K candidates in 55 us; slices of 2K and up took
+// 30 us and their own launch before a selection of 45 us)
+constexpr int SEL_PRE = 16384;
+__device__ __forceinline__ void sel_slices(int ncand, int &nsl, int &len)
 {
-    nsl = ncand > SEL_PRE ? (int)min<long long>(SEL_SL, (ncand + SEL_STEP - 1) / SEL_STEP) : 0;
+    nsl = ncand > SEL_PRE ? SEL_SL : 0;
     len = nsl ? (ncand + nsl - 1) / nsl : 0;
 }
 
@@ -1369,7 +1435,7 @@ __device__ __forceinline__ void sel_slices(long long ncand, int &nsl, long long 
 // those slots become "no candidate"), so k_select streams nsl x K keys
 // instead of all.  The K best of the hub are among them (keys are distinct).
 __global__ void __launch_bounds__(SEL_T)
-k_select_pre(Hubs hb, int H, float *__restrict__ cb_D, int32_t *__restrict__ cb_id, int kmax)
+k_select_pre(Hubs hb, int H, unsigned long long *__restrict__ cand, int NC, int kmax)
 {
     __shared__ unsigned long long buf[SEL_BUF], out[MAX_K];
     __shared__ int fill_s;
@@ -1378,30 +1444,19 @@ k_select_pre(Hubs hb, int H, float *__restrict__ cb_D, int32_t *__restrict__ cb_
         const int h = (int)(w / SEL_SL), sl = (int)(w % SEL_SL);
         if (!hb.act[h])
             continue;
-        const int R = cand_per_chunk(hb.ce[h] - hb.cb[h], kmax);
-        const long long c0 = (long long)hb.cb[h] * R, c1 = (long long)hb.ce[h] * R;
-        int nsl;
-        long long len;
-        sel_slices(c1 - c0, nsl, len);
+        const int nch = hb.ce[h] - hb.cb[h], nc = nch * cand_per_chunk(nch, kmax);
+        int nsl, len;
+        sel_slices(nc, nsl, len);
         if (sl >= nsl)
             continue;
-        const long long qs = c0 + sl * len, qe = min(c1, qs + len);
-        auto at = [&](long long q) { return (size_t)(q / R) * CAND_R + (size_t)(q % R); };
-        const int nk = topk_stream(
-            qe - qs, K,
-            [&](long long v) { const size_t a = at(qs + v); return cand_key(cb_D[a], cb_id[a]); },
-            buf, &fill_s, out);
+        const int qs = sl * len, qe = min(nc, qs + len);
+        unsigned long long *ck = cand + hb.cb[h];
+        auto at = [&](int q) { return cand_at(q, nch, NC); };
+        const int nk = topk(
+            qe - qs, K, [&](int v) { return ck[at(qs + v)]; }, buf, &fill_s, out);
         for (int j = threadIdx.x; j < K; j += SEL_T)
-            if (qs + j < qe) {
-                const size_t a = at(qs + j);
-                if (j < nk) {
-                    cb_D[a] = __uint_as_float((uint32_t)(buf[j] >> 32));
-                    cb_id[a] = 0x7FFFFFFF - (int)(uint32_t)buf[j];
-                } else {
-                    cb_D[a] = -1.f;
-                    cb_id[a] = INT_MAX;
-                }
-            }
+            if (qs + j < qe)
+                ck[at(qs + j)] = j < nk ? buf[j] : 0ull;
         __syncthreads();  // buf is reused by the next slice
     }
 }
@@ -1455,25 +1510,35 @@ k_conflicts(Pts P, Hubs hb, int nt, SelPart *__restrict__ sp,
         atomicAdd(count_slot(cnt, blockIdx.x), (unsigned long long)tests);
 }
 
-template <int M, int PH>
+// What bounds it: one work-group's chain of dependent steps per hub while few
+// hubs are active (581K x 55: 28 -> 15 us a pass, 1M x 128 45 + 30 -> 55 us
+// with 15.6K chunks): candidates read side by side and cut by a threshold
+// (9 -> 5 us), conflict tests on FP16 products (9 -> 3 us).
+//
+// NKS > 0: the level has FP16 rows of 16 NKS coordinates (MxArgs), and the
+// conflict tests go through their products: a pair is taken or left where
+// d^2 lies outside the threshold by the margin, about one in a hundred is
+// computed.  NKS = 0 computes them all.
+template <int M, int PH, int NKS>
 __global__ void __launch_bounds__(SEL_T)
 k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
-         const float *__restrict__ cb_D, const int32_t *__restrict__ cb_id,
+         const unsigned long long *__restrict__ cand, int NC,
          const LevelTab *__restrict__ tab, int kmax, int32_t *__restrict__ live_next,
          unsigned long long *__restrict__ cnt,
-         SelPart *__restrict__ sp)
+         SelPart *__restrict__ sp, MxArgs A)
 {
     __shared__ unsigned long long buf[SEL_BUF], out[MAX_K];
     __shared__ unsigned long long conf[MAX_K][SEL_W];
-    __shared__ __align__(16) float crow[SEL_CR * (UPD_D + 4)];  // staged candidate rows
+    __shared__ __align__(16) float crow[NKS ? 4 : SEL_CR * (UPD_D + 4)];  // staged rows
+    __shared__ __align__(16) float cnrm[NKS ? MAX_K : 4];    // candidates' norms
+    __shared__ int cpos[NKS ? MAX_K : 1], cid[NKS ? MAX_K : 1];  // positions, input ids
     __shared__ int acc[MAX_K];
     __shared__ int nacc_s, nk_s, fill_s;
     const int K = min(kmax, MAX_K);
     for (int h = blockIdx.x; h < H; h += gridDim.x) {
     if (!hb.act[h])
         continue;
-    const int R = cand_per_chunk(hb.ce[h] - hb.cb[h], kmax);
-    const long long c0 = (long long)hb.cb[h] * R, c1 = (long long)hb.ce[h] * R;
+    const int cb = hb.cb[h], nch = hb.ce[h] - cb;
     const int b = hb.b[h], m0 = hb.m[h];
     const Thr T = tab->t[hb.lvl[h] - 1 + LOFF];
 
@@ -1488,19 +1553,16 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
     } else {
     // ---- top-K candidates ------------------------------------------------
     // (a hub with many candidates streams its slices' pre-selected K each)
-    int nsl;
-    long long len;
-    sel_slices(c1 - c0, nsl, len);
-    const long long nv = nsl ? (long long)nsl * K : c1 - c0;
-    auto ckey = [&](long long v) -> unsigned long long {
-        const long long q = nsl ? c0 + (v / K) * len + (v % K) : c0 + v;
-        if (q >= c1 || (nsl && (v % K) >= len))
+    const int nc = nch * cand_per_chunk(nch, kmax);
+    int nsl, len;
+    sel_slices(nc, nsl, len);
+    auto ckey = [&](int v) -> unsigned long long {
+        const int q = nsl ? (v / K) * len + v % K : v;
+        if (q >= nc || (nsl && v % K >= len))
             return 0ull;
-        const size_t a = (size_t)(q / R) * CAND_R + (size_t)(q % R);
-        return cand_key(cb_D[a], cb_id[a]);
+        return cand[cb + cand_at(q, nch, NC)];
     };
-    nk = nv <= SEL_RANK ? topk_rank((int)nv, K, ckey, buf, out, &fill_s)
-                            : topk_stream(nv, K, ckey, buf, &fill_s, out);
+    nk = topk(nsl ? nsl * K : nc, K, ckey, buf, &fill_s, out);
     if (threadIdx.x == 0)
         nk_s = nk;
     for (int i = threadIdx.x; i < MAX_K * SEL_W; i += SEL_T)
@@ -1519,6 +1581,56 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
     }
 
     // ---- pairwise conflicts (j < i): within 2^{l-1} ----------------------
+    if constexpr (NKS > 0) {
+        constexpr int KQ = 16 * NKS;
+        const float sc = fp16_scale(A.radius[hb.node[h]]), s2 = sc * sc;
+        for (int i = threadIdx.x; i < MAX_K; i += SEL_T) {
+            const int id = i < nk ? 0x7FFFFFFF - (int)(uint32_t)buf[i] : -1;
+            const int p = id >= 0 ? A.pos[id] : hb.b[h];
+            cid[i] = id;
+            cpos[i] = p;
+            cnrm[i] = id >= 0 ? A.nrm[p] : 0.f;
+        }
+        __syncthreads();
+        // 32 x 32 blocks of the triangle, one wave each: rows 32 bi ..
+        // against columns 32 bj .. (bj <= bi)
+        const int lane = threadIdx.x & (WAVE - 1), l32 = lane & 31, hi = lane >> 5;
+        const int nb = (nk + 31) / 32;
+        for (int q0 = threadIdx.x / WAVE; q0 < nb * (nb + 1) / 2; q0 += SEL_T / WAVE) {
+            int bi = 0, bj = q0;
+            while (bj > bi)
+                bj -= ++bi;
+            const _Float16 *ra = A.q + (size_t)cpos[32 * bi + l32] * KQ + 8 * hi;
+            const _Float16 *rb = A.q + (size_t)cpos[32 * bj + l32] * KQ + 8 * hi;
+            mx_f32x16 acc = {};
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                    *reinterpret_cast<const mx_f16x8 *>(ra + 16 * ks),
+                    *reinterpret_cast<const mx_f16x8 *>(rb + 16 * ks), acc, 0, 0, 0);
+            const int j = 32 * bj + l32;
+            const float nj = cnrm[j];
+            const float tl = T.lo * s2, th = T.hi * s2;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int i = 32 * bi + 8 * (q >> 2) + 4 * hi + (q & 3);
+                const float mag = cnrm[i] + nj, d2 = mag - 2.f * acc[q];
+                const float e = (A.m.c1 + 2.f * A.m.keyrel) * mag + A.m.add;
+                bool y = d2 + e < tl * (1.f - 1e-6f);
+                const bool in = j < i && i < nk;
+                if (in && !y && !(d2 - e > th * (1.f + 1e-6f))) {
+                    const int a = cid[i], c = cid[j];
+                    y = within<M>(P, a, c, key32<M>(P, a, c), T, cnt + 1);
+                }
+                const unsigned long long m = __ballot(in && y);
+                if (l32 == 0)  // this block's own half word of the row
+                    reinterpret_cast<uint32_t *>(conf[i])[bj] =
+                        (uint32_t)(m >> (32 * hi));
+            }
+        }
+        if (threadIdx.x == 0)
+            tests = (unsigned long long)nk * (nk - 1) / 2;
+    } else {
     // Vector rows of up to SEL_CR candidates are staged in LDS first (rows
     // padded by 4 floats: neighbouring rows start in different banks) and
     // tested in 2 x 2 blocks; the FP32 key is that of sqdiff_key either way.
@@ -1611,6 +1723,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
             if (within<M>(P, a, c, key32<M>(P, a, c), T, cnt + 1))
                 atomicOr(&conf[i][j >> 6], 1ull << (j & 63));
         }
+    }
     }
     }
     __syncthreads();
@@ -2337,8 +2450,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     const int maxch = (int)cdiv(n, CH) + n / 2 + 2;  // chunks over all hubs
     int32_t *ch_hub = S.get<int32_t>(maxch), *ch_s = S.get<int32_t>(maxch),
             *ch_e = S.get<int32_t>(maxch), *ch_k = S.get<int32_t>(maxch);
-    float *cb_D = S.get<float>((size_t)maxch * CAND_R);
-    int32_t *cb_id = S.get<int32_t>((size_t)maxch * CAND_R);
+    unsigned long long *cand = S.get<unsigned long long>((size_t)maxch * CAND_R);
     int32_t *live_d = S.get<int32_t>(2);
     // net-selection passes per graph replay (even: the flag read is live_d[0]
     // again); 1 = one eager pass per host check
@@ -2469,13 +2581,13 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
         auto pass = [&](hipStream_t s, int k) {
             int32_t *lc = live_d + k, *lx = live_d + (1 - k);
             if constexpr (M == M_LEV)
-                launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent, perm, D, L, tab, cb_D, cb_id,
+                launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent, perm, D, L, tab, cand,
                                   T->opt.kmax, cnt);
             else if (M == M_HAM && T->dp <= 8) {
                 auto go = [&](auto nw) {
                     FNN_LAUNCH((k_update_ham<decltype(nw)::value>), dim3(gu), dim3(CH * UPD_W),
                                0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs,
-                               cent, perm, D, L, tab, cb_D, cb_id, T->opt.kmax, cnt);
+                               cent, perm, D, L, tab, cand, T->opt.kmax, cnt);
                 };
                 if (T->dp <= 2)
                     go(std::integral_constant<int, 2>{});
@@ -2488,36 +2600,42 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                     if constexpr (M == M_L2 || M == M_ANG)
                         fp16_width(T->dp, [&](auto kw) {
                             FNN_LAUNCH((k_update_mx<M, decltype(kw)::value>), dim3(gu),
-                                       dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent, perm, D, L, tab,
-                                       cb_D, cb_id, T->opt.kmax, cnt, mx.a);
+                                       dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent, perm, D, L, tab, cand, T->opt.kmax, cnt, mx.a);
                         });
                 } else {
                     FNN_LAUNCH((k_update<M>), dim3(gu), dim3(CH * UPD_W), upd_lds, s, P,
                                ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent,
-                               perm, D, L, tab, cb_D, cb_id, T->opt.kmax, cnt);
+                               perm, D, L, tab, cand, T->opt.kmax, cnt);
                 }
             }
             // (a hub of m chunks has at most m + 2 kmax candidates)
             if (cdiv(big, CH) + 2ll * T->opt.kmax > SEL_PRE)
                 FNN_LAUNCH(k_select_pre, dim3(grid_cap((int64_t)H * SEL_SL, 1, 8192)),
-                           dim3(SEL_T), 0, s, hubs, H, cb_D, cb_id, T->opt.kmax);
+                           dim3(SEL_T), 0, s, hubs, H, cand, NC, T->opt.kmax);
             const dim3 gs(grid_cap(H, 1, 4096));
             if constexpr (M == M_LEV) {
                 if (sp) {
                     const int K = std::min(T->opt.kmax, MAX_K);
                     const int nt = (int)cdiv(std::max(1, K * (K - 1) / 2), WAVE);
-                    FNN_LAUNCH((k_select<M, SEL_TOP>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent,
-                               cb_D, cb_id, tab, T->opt.kmax, lx, cnt, sp);
+                    FNN_LAUNCH((k_select<M, SEL_TOP, 0>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent, cand, NC, tab, T->opt.kmax, lx, cnt, sp, mx.a);
                     FNN_LAUNCH(k_conflicts, dim3((unsigned)(H * nt)), dim3(WAVE), 0, s, P,
                                hubs, nt, sp, tab, cnt);
-                    FNN_LAUNCH((k_select<M, SEL_TAKE>), gs, dim3(SEL_T), 0, s, P, hubs, H,
-                               cent, cb_D, cb_id, tab, T->opt.kmax, lx, cnt,
-                               sp);
+                    FNN_LAUNCH((k_select<M, SEL_TAKE, 0>), gs, dim3(SEL_T), 0, s, P, hubs, H,
+                               cent, cand, NC, tab, T->opt.kmax, lx, cnt, sp, mx.a);
                     return;
                 }
             }
-            FNN_LAUNCH((k_select<M, SEL_ALL>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent, cb_D,
-                       cb_id, tab, T->opt.kmax, lx, cnt, nullptr);
+            auto all = [&](auto kw) {
+                FNN_LAUNCH((k_select<M, SEL_ALL, decltype(kw)::value>), gs, dim3(SEL_T), 0, s, P,
+                           hubs, H, cent, cand, NC, tab, T->opt.kmax, lx, cnt, nullptr, mx.a);
+            };
+            if constexpr (M == M_L2 || M == M_ANG) {
+                if (mx.on) {
+                    fp16_width(T->dp, all);
+                    return;
+                }
+            }
+            all(std::integral_constant<int, 0>{});
         };
         // The first passes of a level run eagerly with one read after them (a
         // graph of four passes costs 140 us to record, instantiate and drop,
@@ -2543,9 +2661,14 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                 for (int k = 0; k < GP; ++k)
                     pass(gr.cs, k & 1);
                 gr.end();
-                for (;;) {
-                    gr.launch(st);
-                    passes += GP;
+                // one read per replay at first, then per quarter of the
+                // replays so far: a read and the launch after it leave the
+                // device idle for 28 us, a replay past the end takes 15 us
+                for (int done = 0, burst = 1;; burst = std::clamp(done / 4, 1, 8)) {
+                    for (int r = 0; r < burst; ++r)
+                        gr.launch(st);
+                    done += burst;
+                    passes += GP * burst;
                     if (read_scalar(live_d, st) == 0)
                         break;
                 }

@@ -45,8 +45,8 @@ def _nearest(x, t):
     return bad
 
 
-def _check(fnn, O, x, metric, mid, eps, zeta, nearest):
-    tree = fnn.fnn_tree_build(x, metric, zeta=zeta)
+def _check(fnn, O, x, metric, mid, eps, zeta, nearest, **kw):
+    tree = fnn.fnn_tree_build(x, metric, zeta=zeta, **kw)
     rp, col, dist = fnn.fnn_eps_graph(tree, eps).to_numpy()
     t = fnn.fnn_tree_export(tree)
     if nearest:
@@ -66,6 +66,21 @@ def test_l2(d, n, zeta):
     print(f"[case] d={d} n={n}", flush=True)
     x = _points(n, d, 31 * d + n)
     _check(fnn, O, x, "l2", O.L2, 0.3 * d ** 0.5, zeta, True)
+
+
+@pytest.mark.parametrize("kmax", [1, 31, 33, 64, 65, 200, 256])
+@pytest.mark.parametrize("n,d,metric", [(6000, 20, "l2"), (6000, 64, "angular"), (40000, 16, "l2")])
+def test_candidates_per_pass(n, d, metric, kmax):
+    """Conflict blocks of 32 candidates, their keys cut by a threshold first
+    (more than 256 chunks) or not."""
+    import paper_2510_14147_amd as fnn
+    from oracle import oracle as O
+    print(f"[case] n={n} d={d} {metric} kmax={kmax}", flush=True)
+    x = _points(n, d, d + kmax)
+    t = fnn.fnn_tree_export(fnn.fnn_tree_build(x, metric, kmax=kmax))
+    t["radius"] = t["radius"].astype(np.float64)
+    v = O.check_tree(x, O.L2 if metric == "l2" else O.ANGULAR, t)
+    assert all(c == 0 for c in v.values()), v
 
 
 @pytest.mark.parametrize("scale,offset", [(1e-7, 0.0), (1e5, 0.0), (1.0, 1000.0)])
