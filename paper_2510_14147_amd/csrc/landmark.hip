@@ -37,7 +37,7 @@
 namespace fnn {
 
 Pts ingest_input(fnn_tree *T, const void *points, Scratch &S);
-void sort_csr_rows(const int64_t *row_ptr, int n, int32_t *col, float *dist,
+void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, float *dist,
                    int64_t nnz, Scratch &S, const unsigned long long *pk, int32_t *cc,
                    const int *err, int *herr);
 
@@ -521,7 +521,7 @@ void landmark_graph(fnn_tree *hdr, const void *points, double eps, int m,
     int *bad = a.err;
     FNN_LAUNCH(k_rows_check, dim3(grid_for(n, 256)), dim3(256), 0, s, C->row_ptr, (int)n,
                cur, bad);
-    sort_csr_rows(C->row_ptr, (int)n, C->col, C->dist, nnz, S, nullptr, nullptr, nullptr,
+    sort_csr_rows(C->row_ptr, (int)n, n, C->col, C->dist, nnz, S, nullptr, nullptr, nullptr,
                   nullptr);
     FNN_HIP(hipEventRecord(ev[3], s));
     if (read_scalar(bad, s))

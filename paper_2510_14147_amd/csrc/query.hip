@@ -1075,11 +1075,13 @@ __device__ __forceinline__ void wave_sort_row(int32_t *__restrict__ col,
     }
 }
 
+constexpr int SORT_WAVE_MAX = 32 * WAVE;  // longest row of k_sort_wave
+
 // Rows of at most 512 entries: one wave per row (register bitonic sort);
-// longer rows are listed for the work-group and global sorts.  With pk
-// non-null the entries are read packed from pk (same slots) and every row
-// is written to col and dist: sorted here, or unpacked in place for the
-// listed sorts.
+// longer rows are listed for the sorts below, a wave's up to 64 at a time (an
+// add to the list's counter per row took 12 ns each, one after another: 1 ms
+// of 1.1 at 2.1M rows, 4 % of them long).  With pk non-null the entries are
+// read packed from pk (same slots).
 __global__ void __launch_bounds__(256)
 k_sort_small(const int64_t *__restrict__ row_ptr, int n, int32_t *__restrict__ col,
              float *__restrict__ dist, int32_t *__restrict__ mid_list,
@@ -1090,25 +1092,36 @@ k_sort_small(const int64_t *__restrict__ row_ptr, int n, int32_t *__restrict__ c
     const int lane = threadIdx.x & (WAVE - 1);
     const int wpb = blockDim.x / WAVE;
     unsigned long long *tr = tr_s[threadIdx.x / WAVE];
+    int held[2] = {0, 0}, nh[2] = {0, 0};  // listed rows, one per lane
+    auto flush = [&](int k) {
+        int at = 0;
+        if (lane == 0)
+            at = atomicAdd(&counts[k], nh[k]);
+        at = __shfl(at, 0, WAVE);
+        if (lane < nh[k])
+            (k ? long_list : mid_list)[at + lane] = held[k];
+        nh[k] = 0;
+    };
     for (int r = blockIdx.x * wpb + threadIdx.x / WAVE; r < n;
          r += gridDim.x * wpb) {
     const int64_t b = row_ptr[r];
     const int64_t len = row_ptr[r + 1] - b;
-    if (pk && (len == 1 || len > 8 * WAVE))
-        for (int64_t i = lane; i < len; i += WAVE) {
-            const unsigned long long x = pk[b + i];
-            col[b + i] = (int32_t)(x >> 32);
-            dist[b + i] = __uint_as_float((uint32_t)x);
-        }
+    if (pk && len == 1 && lane == 0) {
+        const unsigned long long x = pk[b];
+        col[b] = (int32_t)(x >> 32);
+        dist[b] = __uint_as_float((uint32_t)x);
+    }
     if (len <= 1)
         continue;
     if (len > 8 * WAVE) {
-        if (lane == 0) {
-            if (len <= 4096)
-                mid_list[atomicAdd(&counts[0], 1)] = r;
-            else
-                long_list[atomicAdd(&counts[1], 1)] = r;
-        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if ((len > SORT_WAVE_MAX) == (k == 1)) {
+                if (lane == nh[k])
+                    held[k] = r;
+                if (++nh[k] == WAVE)
+                    flush(k);
+            }
         continue;
     }
     if (len > 4 * WAVE) {
@@ -1140,13 +1153,18 @@ k_sort_small(const int64_t *__restrict__ row_ptr, int n, int32_t *__restrict__ c
         dist[b + lane] = __uint_as_float((uint32_t)v);
     }
     }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (nh[k])
+            flush(k);
 }
 
-// Rows of 513..2048 entries (from the list of 513..4096): one wave per row,
-// the register sort with 16 or 32 entries per lane.
+// Listed rows of 513..SORT_WAVE_MAX entries: one wave per row, the register
+// sort with 16 or 32 entries per lane.
 __global__ void __launch_bounds__(256)
 k_sort_wave(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list,
-            int nl, int32_t *__restrict__ col, float *__restrict__ dist)
+            int nl, int32_t *__restrict__ col, float *__restrict__ dist,
+            const unsigned long long *__restrict__ pk)
 {
     __shared__ unsigned long long tr_s[256 / WAVE][WAVE * 33];  // up to 32 keys per lane
     const int lane = threadIdx.x & (WAVE - 1);
@@ -1156,151 +1174,166 @@ k_sort_wave(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ lis
         const int r = list[li];
         const int64_t b = row_ptr[r];
         const int len = (int)(row_ptr[r + 1] - b);
-        if (len > 32 * WAVE)
-            continue;  // the work-group sort's
         if (len > 16 * WAVE)
-            wave_sort_row<32>(col, dist, b, len, lane, nullptr, tr);
+            wave_sort_row<32>(col, dist, b, len, lane, pk, tr);
         else
-            wave_sort_row<16>(col, dist, b, len, lane, nullptr, tr);
+            wave_sort_row<16>(col, dist, b, len, lane, pk, tr);
     }
 }
 
-// Listed rows of lo+1 .. 1024 NW entries: one work-group of NW waves per
-// row, padded to N = 1024 NW.  Entry g = 1024 w + 64 v + lane lives in
-// register v of that lane of wave w: bitonic stages with strides below 64
-// exchange across lanes, strides up to 512 swap registers, and only the
-// stages with strides of 1024 and more go through LDS.
-template <int NW>
-__global__ void __launch_bounds__(NW * WAVE)
-k_sort_blk(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list,
-           int nl, int lo, int32_t *__restrict__ col, float *__restrict__ dist)
+// Longer listed rows, by counting: a row's columns are distinct, so a bit per
+// column of its span in LDS and the number of bits below give every entry's
+// place.  One work-group per row; WORDS 32-bit words of span at a time, with
+// the count of set bits before every eight of them.  Entries of rows up to
+// SB_V SB_T are held in registers (they are written where they were read);
+// longer ones are read again, from pk or from the copy made in scr.
+//
+// What bounds it: the LDS accesses, linear in the row and its span.  581K
+// rows, 6400 of 4097..16384 entries and 9 longer: 6.5 ms by bitonic sorts of
+// whole work-groups -> 0.8 ms.
+constexpr int SB_V = 8, SB_LONG = 1024;  // entries held per thread; threads of long rows
+template <int WORDS, int SB_T>
+__global__ void __launch_bounds__(SB_T)
+k_sort_bits(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list, int nl,
+            int32_t *__restrict__ col, float *__restrict__ dist,
+            const unsigned long long *__restrict__ pk, const int64_t *__restrict__ soff,
+            unsigned long long *__restrict__ scr)
 {
-    constexpr int V = 16, N = NW * V * WAVE;
-    __shared__ unsigned long long s[N];
-    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-    const int g0 = w * V * WAVE + lane;  // entry of register 0
+    static_assert(WORDS % 8 == 0, "counts of eight words");
+    __shared__ uint32_t bits[WORDS];
+    __shared__ uint32_t before[WORDS / 8];
+    __shared__ uint32_t wsum[SB_T / WAVE];
+    __shared__ int lo_s, hi_s;
+    const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
     for (int li = blockIdx.x; li < nl; li += gridDim.x) {
         const int r = list[li];
-        const int64_t b = row_ptr[r];
-        const int64_t len64 = row_ptr[r + 1] - b;
-        if (len64 <= lo || len64 > N)
-            continue;  // another kernel's (the same for the whole work-group)
-        const int len = (int)len64;
-        unsigned long long x[V];
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const int g = g0 + v * WAVE;
-            x[v] = g < len ? pack_entry(col[b + g], dist[b + g]) : ~0ull;
+        const int64_t b = row_ptr[r], len = row_ptr[r + 1] - b;
+        const bool reg = len <= SB_V * SB_T;
+        unsigned long long *src = pk || reg ? nullptr : scr + soff[li];
+        auto entry = [&](int64_t i) {
+            return pk ? pk[b + i] : pack_entry(col[b + i], dist[b + i]);
+        };
+        if (t == 0) {
+            lo_s = INT_MAX;
+            hi_s = 0;
         }
+        __syncthreads();
+        unsigned long long x[SB_V];
+        int lo = INT_MAX, hi = 0;
+        if (reg) {
 #pragma unroll
-        for (int k = 2; k <= N; k <<= 1) {
-#pragma unroll
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                if (j >= V * WAVE) {
-#pragma unroll
-                    for (int v = 0; v < V; ++v)
-                        s[g0 + v * WAVE] = x[v];
-                    __syncthreads();
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        const int g = g0 + v * WAVE;
-                        const unsigned long long o = s[g ^ j];
-                        const bool up = (g & k) == 0, lower = (g & j) == 0;
-                        x[v] = (lower == up) ? (o < x[v] ? o : x[v]) : (o > x[v] ? o : x[v]);
-                    }
-                    __syncthreads();  // s is written again by the next such stage
-                } else if (j >= WAVE) {
-                    const int jv = j / WAVE;
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        if (v & jv)
-                            continue;
-                        const bool up = ((g0 + v * WAVE) & k) == 0;
-                        const unsigned long long a = x[v], c = x[v | jv];
-                        if ((a > c) == up) {
-                            x[v] = c;
-                            x[v | jv] = a;
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        const unsigned long long o = __shfl_xor(x[v], j, WAVE);
-                        const bool up = ((g0 + v * WAVE) & k) == 0;
-                        const bool lower = (lane & j) == 0;
-                        x[v] = (lower == up) ? (o < x[v] ? o : x[v]) : (o > x[v] ? o : x[v]);
-                    }
+            for (int v = 0; v < SB_V; ++v) {
+                x[v] = v * SB_T + t < len ? entry(v * SB_T + t) : 0ull;
+                const int c = (int)(x[v] >> 32);
+                if (v * SB_T + t < len) {
+                    lo = min(lo, c);
+                    hi = max(hi, c);
                 }
             }
+        } else {
+            for (int64_t i = t; i < len; i += SB_T) {
+                const unsigned long long e = entry(i);
+                if (src)
+                    src[i] = e;  // read again by this thread only
+                const int c = (int)(e >> 32);
+                lo = min(lo, c);
+                hi = max(hi, c);
+            }
         }
+        lo = -wave_max(-lo);
+        hi = wave_max(hi);
+        if (lane == 0) {
+            atomicMin(&lo_s, lo);
+            atomicMax(&hi_s, hi);
+        }
+        __syncthreads();
+        const int wlo = lo_s >> 5, whi = hi_s >> 5;
+        auto each = [&](auto f) {
+            if (reg) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const int g = g0 + v * WAVE;
-            if (g < len) {
-                col[b + g] = (int32_t)(x[v] >> 32);
-                dist[b + g] = __uint_as_float((uint32_t)x[v]);
+                for (int v = 0; v < SB_V; ++v)
+                    if (v * SB_T + t < len)
+                        f(x[v]);
+            } else {
+                for (int64_t i = t; i < len; i += SB_T)
+                    f(src ? src[i] : pk[b + i]);
             }
-        }
-    }
-}
-
-constexpr int SORT_BLK_MAX = 16 * 16 * WAVE;  // longest row k_sort_blk<16> sorts
-
-// Longer rows: one work-group per row, bitonic sort in a global scratch
-// buffer (rare: only rows with more than 16384 neighbours).
-__global__ void __launch_bounds__(256)
-k_sort_long(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list,
-            const int64_t *__restrict__ soff, unsigned long long *__restrict__ scr,
-            int32_t *__restrict__ col, float *__restrict__ dist)
-{
-    const int r = list[blockIdx.x];
-    const int64_t b = row_ptr[r];
-    const int64_t len = row_ptr[r + 1] - b;
-    if (len <= SORT_BLK_MAX)
-        return;  // sorted in registers by k_sort_blk<16>
-    unsigned long long *s = scr + soff[blockIdx.x];
-    int64_t P2 = 1;
-    while (P2 < len)
-        P2 <<= 1;
-    for (int64_t i = threadIdx.x; i < P2; i += blockDim.x)
-        s[i] = i < len ? pack_entry(col[b + i], dist[b + i]) : ~0ull;
-    __syncthreads();
-    for (int64_t k = 2; k <= P2; k <<= 1) {
-        for (int64_t j = k >> 1; j > 0; j >>= 1) {
-            for (int64_t i = threadIdx.x; i < P2; i += blockDim.x) {
-                const int64_t l = i ^ j;
-                if (l > i) {
-                    const bool up = (i & k) == 0;
-                    unsigned long long x = s[i], y = s[l];
-                    if ((x > y) == up) {
-                        s[i] = y;
-                        s[l] = x;
-                    }
-                }
-            }
-            __threadfence_block();
+        };
+        int64_t at = b;  // of the span's first entry
+        for (int w0 = wlo; w0 <= whi; w0 += WORDS) {
+            const int words = min(WORDS, whi - w0 + 1), ng = (words + 7) / 8;
+            for (int i = t; i < 8 * ng; i += SB_T)
+                bits[i] = 0u;
             __syncthreads();
+            each([&](unsigned long long e) {
+                const int c = (int)(e >> 32), k = (c >> 5) - w0;
+                if (k >= 0 && k < words)
+                    atomicOr(&bits[k], 1u << (c & 31));
+            });
+            __syncthreads();
+            // every thread counts PG consecutive groups, then a scan
+            constexpr int PG = (WORDS / 8 + SB_T - 1) / SB_T;
+            uint32_t cnt[PG], sum = 0;
+#pragma unroll
+            for (int g = 0; g < PG; ++g) {
+                const int q = t * PG + g;
+                cnt[g] = 0;
+                if (q < ng)
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        cnt[g] += __popc(bits[8 * q + k]);
+                sum += cnt[g];
+            }
+            uint32_t incl = sum;
+#pragma unroll
+            for (int o = 1; o < WAVE; o <<= 1) {
+                const uint32_t y = __shfl_up(incl, o, WAVE);
+                if (lane >= o)
+                    incl += y;
+            }
+            if (lane == WAVE - 1)
+                wsum[w] = incl;
+            __syncthreads();
+            uint32_t run = incl - sum, all = 0;
+#pragma unroll
+            for (int k = 0; k < SB_T / WAVE; ++k) {
+                run += k < w ? wsum[k] : 0u;
+                all += wsum[k];
+            }
+#pragma unroll
+            for (int g = 0; g < PG; ++g) {
+                if (t * PG + g < ng)
+                    before[t * PG + g] = run;
+                run += cnt[g];
+            }
+            __syncthreads();
+            each([&](unsigned long long e) {
+                const int c = (int)(e >> 32), k = (c >> 5) - w0;
+                if (k < 0 || k >= words)
+                    return;
+                uint32_t p = before[k >> 3] + __popc(bits[k] & ((1u << (c & 31)) - 1u));
+                for (int q = k & ~7; q < k; ++q)
+                    p += __popc(bits[q]);
+                col[at + p] = c;
+                dist[at + p] = __uint_as_float((uint32_t)e);
+            });
+            at += all;
+            __syncthreads();  // the words, sums and bounds are rewritten
         }
-    }
-    for (int64_t i = threadIdx.x; i < len; i += blockDim.x) {
-        col[b + i] = (int32_t)(s[i] >> 32);
-        dist[b + i] = __uint_as_float((uint32_t)s[i]);
     }
 }
 
+// Scratch entries of every listed row: those read again and not packed.
 __global__ void k_long_sizes(const int64_t *__restrict__ row_ptr,
                              const int32_t *__restrict__ list, int nl,
-                             int64_t *__restrict__ p2)
+                             int64_t *__restrict__ size)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nl)
         return;
     const int r = list[i];
     const int64_t len = row_ptr[r + 1] - row_ptr[r];
-    int64_t P2 = 1;
-    while (P2 < len)
-        P2 <<= 1;
-    p2[i] = P2;
+    size[i] = len > SB_V * SB_LONG ? len : 0;
 }
 
 __global__ void k_cursor_init(const int64_t *__restrict__ row_ptr, int n,
@@ -1808,15 +1841,18 @@ __global__ void k_pair_bound(const int2 *__restrict__ inter, long long ni,
         atomicAdd(out, b);
 }
 
-// Sorts every CSR row by column (entries are (column, distance) pairs):
-// rows of up to 512 entries by one wave, up to 4096 by one wave or four,
-// up to 16384 by sixteen waves, longer rows in a global buffer.  pk: the
-// entries packed as (column << 32 | distance bits) in their slots, when the
-// fill wrote them so (col and dist are then written here); null: they are
-// in col and dist.
+// Sorts every CSR row by column (entries are (column, distance) pairs, a
+// row's columns within span of each other): rows of up to 512 entries by one
+// wave in registers, longer ones by a work-group's count, those of up to
+// SORT_WAVE_MAX only where the span is narrow (four work-groups per CU then;
+// 64 clouds x 16, 76K such rows: 2.6 -> 0.6 ms; at a span of 1M the count clears and
+// sums 31K words for every row, more than the register sort takes).  pk: the entries packed as
+// (column << 32 | distance bits) in their slots, when the fill wrote them so
+// (col and dist are then written here); null: they are in col and dist.
 // cc: two zeroed counts (null: taken here); err: a device flag to read along
 // with them into *herr (optional).
-void sort_csr_rows(const int64_t *row_ptr, int n, int32_t *col, float *dist,
+constexpr int SPAN_NARROW = 262144;
+void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, float *dist,
                    int64_t nnz, Scratch &S, const unsigned long long *pk, int32_t *cc,
                    const int *err, int *herr)
 {
@@ -1829,7 +1865,7 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int32_t *col, float *dist,
     if (nnz <= 0 && err)
         *herr = read_scalar(err, s);
     if (nnz > 0) {
-        FNN_LAUNCH(k_sort_small, dim3(grid_cap(n, 4, 16384)), dim3(256), 0, s,
+        FNN_LAUNCH(k_sort_small, dim3(grid_cap(n, 4, 4096)), dim3(256), 0, s,
                    row_ptr, n, col, dist, mid, lng, cc, pk);
         int32_t hcc[2];
         Readback rb(s);
@@ -1838,23 +1874,34 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int32_t *col, float *dist,
             rb.add(herr, err);
         rb.wait();
         if (hcc[0] > 0) {
-            FNN_LAUNCH(k_sort_wave, dim3(grid_cap(hcc[0], 4, 4096)), dim3(256), 0, s,
-                       row_ptr, mid, hcc[0], col, dist);
-            FNN_LAUNCH(k_sort_blk<4>, dim3(grid_cap(hcc[0], 1, 4096)), dim3(4 * WAVE), 0,
-                       s, row_ptr, mid, hcc[0], 32 * WAVE, col, dist);
+            // (at most SORT_WAVE_MAX entries: held by a work-group of 256)
+            if (span <= SPAN_NARROW)
+                FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, 256>),
+                           dim3(grid_cap(hcc[0], 1, 16 * num_cus())), dim3(256), 0, s, row_ptr,
+                           mid, hcc[0], col, dist, pk, nullptr, nullptr);
+            else
+                FNN_LAUNCH(k_sort_wave, dim3(grid_cap(hcc[0], 4, 4096)), dim3(256), 0, s,
+                           row_ptr, mid, hcc[0], col, dist, pk);
         }
         if (hcc[1] > 0) {
-            int64_t *p2 = S.get<int64_t>(hcc[1] + 1);
-            int64_t *soff = S.get<int64_t>(hcc[1] + 2);
-            FNN_LAUNCH(k_long_sizes, dim3(grid_for(hcc[1], 256)), dim3(256), 0, s,
-                       row_ptr, lng, hcc[1], p2);
-            scan_i64(p2, soff, hcc[1], S);
-            const int64_t tot = read_scalar(soff + hcc[1], s);
-            unsigned long long *scr = S.get<unsigned long long>(tot);
-            FNN_LAUNCH(k_sort_blk<16>, dim3(grid_cap(hcc[1], 1, 4096)), dim3(16 * WAVE), 0,
-                       s, row_ptr, lng, hcc[1], 64 * WAVE, col, dist);
-            FNN_LAUNCH(k_sort_long, dim3(hcc[1]), dim3(256), 0, s, row_ptr, lng,
-                       soff, scr, col, dist);
+            int64_t *soff = nullptr;
+            unsigned long long *scr = nullptr;
+            if (!pk) {
+                int64_t *size = S.get<int64_t>(hcc[1] + 1);
+                soff = S.get<int64_t>(hcc[1] + 2);
+                FNN_LAUNCH(k_long_sizes, dim3(grid_for(hcc[1], 256)), dim3(256), 0, s,
+                           row_ptr, lng, hcc[1], size);
+                scan_i64(size, soff, hcc[1], S);
+                const int64_t tot = read_scalar(soff + hcc[1], s);
+                scr = S.get<unsigned long long>(std::max<int64_t>(tot, 1));
+            }
+            const dim3 g(grid_cap(hcc[1], 1, 8 * num_cus()));
+            if (span <= SPAN_NARROW)
+                FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, SB_LONG>), g, dim3(SB_LONG), 0, s,
+                           row_ptr, lng, hcc[1], col, dist, pk, soff, scr);
+            else
+                FNN_LAUNCH((k_sort_bits<32768, SB_LONG>), g, dim3(SB_LONG), 0, s, row_ptr, lng,
+                           hcc[1], col, dist, pk, soff, scr);
         }
     }
 }
@@ -2480,9 +2527,15 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     }
 
     // ---- per-row sort ---------------------------------------------------
+    int64_t span = n;  // a row of a batch stays within its cloud
+    if (ncl > 1 && T->cross_a < 0) {
+        span = 0;
+        for (int c = 0; c < ncl; ++c)
+            span = std::max<int64_t>(span, T->cloud_off_h[c + 1] - T->cloud_off_h[c]);
+    }
     // (the fill's error flag is read with the sort's counts)
     int hbad = 0;
-    sort_csr_rows(C->row_ptr, nr, C->col, C->dist, nnz, S, packed, nlong, bad, &hbad);
+    sort_csr_rows(C->row_ptr, nr, span, C->col, C->dist, nnz, S, packed, nlong, bad, &hbad);
     tm.mark();  // 6
 
     // ---- trace targets, prediction error ---------------------------------
