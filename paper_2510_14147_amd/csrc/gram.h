@@ -211,6 +211,6 @@ inline void fp16_width(int dp, F &&f)
 // go to the survivor list (G.surv, G.nsurv).  Needs rows of at most 128
 // coordinates.
 void screen_tiles(const fnn_tree *T, const Pts &P, const GramArgs &G, const int2 *inter,
-                  long long ninter, const TileOut &o, hipStream_t s);
+                  long long ninter, hipStream_t s);
 
 }  // namespace fnn

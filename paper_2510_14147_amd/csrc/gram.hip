@@ -1677,17 +1677,18 @@ k_gram_direct(Pts P, GramArgs G, TileOut out)
 // What bounds it: the chain of loads of a pack pair (list, packs, rows) and
 // their latency; its products take a tenth of the time.  581K x 55, 7.0e9
 // pairs: 30.3 ms of tiles -> 6.1 here + 2.5 deciding 0.5 % of them; 64 clouds
-// x 16, 7.3e9 pairs: 20.9 -> 4.2 + 4.4 (1.0 %).
+// x 16, 7.3e9 pairs: 20.9 -> 3.6 + 4.4 (1.0 %).
+constexpr int SCREEN_BUF = 1024;  // survivors per wave in LDS (256: 4.3 ms for 3.6 at x 16)
 template <int M, int NKS>
 __global__ void __launch_bounds__(256, NKS >= 8 ? 2 : NKS >= 4 ? 3 : 4)  // unspilled
 k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
               long long ninter, const int32_t *__restrict__ q_cpos,
-              const float *__restrict__ q_rad, TileOut out)
+              const float *__restrict__ q_rad)
 {
     constexpr int KQ = 16 * NKS;
     __shared__ __align__(16) float cen_s[4][KQ];    // the frame's origin
     __shared__ __align__(16) float cterm_s[4][32];  // -(1 - c1) |b|^2 / 2
-    __shared__ int2 surv_s[4][SURV_BUF];
+    __shared__ int2 surv_s[4][SCREEN_BUF];
     const float *X = M == M_ANG ? P.xn : P.x;
     const int dp = P.dp;
     const int w = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
@@ -1696,7 +1697,6 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
     float *cen = cen_s[w], *cterm = cterm_s[w];
     int2 *sb = surv_s[w];
     unsigned fill = 0;
-    unsigned long long npairs = 0;
     const float omc1 = 1.f - mg.c1;
     for (long long it = (long long)blockIdx.x * 4 + w; it < ninter; it += (long long)gridDim.x * 4) {
         int A = __builtin_amdgcn_readfirstlane(inter[it].x);
@@ -1712,7 +1712,6 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
         const float e2 = G.pcl ? G.ct[G.pcl[a0]].e2f : G.e2f;
         const float sc = fp16_scale(3.f * q_rad[A] + sqrtf(e2));
         const float D2 = e2 * (sc * sc);
-        npairs += diag ? (unsigned long long)na * (na - 1) / 2 : (unsigned long long)na * nb;
         const float *C = X + (size_t)q_cpos[A] * dp;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         for (int k = lane; k < KQ; k += WAVE)
@@ -1822,12 +1821,12 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
                     pre += (unsigned)__popcll(m & ltmask) << b;
                     tot += (unsigned)__popcll(m) << b;
                 }
-                if (fill + tot > (unsigned)SURV_BUF) {
+                if (fill + tot > (unsigned)SCREEN_BUF) {
                     surv_flush(G, sb, fill);
                     fill = 0;
                 }
                 unsigned long long o = 0;  // slots in the list, if not in sb
-                const bool direct = tot > (unsigned)SURV_BUF;
+                const bool direct = tot > (unsigned)SCREEN_BUF;
                 if (direct) {
                     if (lane == 0)
                         o = atomicAdd(G.nsurv, (unsigned long long)tot);
@@ -1855,12 +1854,10 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
         }
     }
     surv_flush(G, sb, fill);
-    if (lane == 0 && npairs)
-        atomicAdd(&out.cnt[2], npairs);
 }
 
 void screen_tiles(const fnn_tree *T, const Pts &P, const GramArgs &G, const int2 *inter,
-                  long long ninter, const TileOut &o, hipStream_t s)
+                  long long ninter, hipStream_t s)
 {
     if (ninter <= 0)
         return;
@@ -1872,10 +1869,10 @@ void screen_tiles(const fnn_tree *T, const Pts &P, const GramArgs &G, const int2
     fp16_width(P.dp, [&](auto w) {
         if (P.metric == M_ANG)
             FNN_LAUNCH((k_tile_screen<M_ANG, decltype(w)::value>), g, dim3(256), 0, s, P, G, mg,
-                       inter, ninter, T->q_center_pos, T->q_radius, o);
+                       inter, ninter, T->q_center_pos, T->q_radius);
         else
             FNN_LAUNCH((k_tile_screen<M_L2, decltype(w)::value>), g, dim3(256), 0, s, P, G, mg,
-                       inter, ninter, T->q_center_pos, T->q_radius, o);
+                       inter, ninter, T->q_center_pos, T->q_radius);
     });
 }
 
