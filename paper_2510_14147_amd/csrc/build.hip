@@ -2078,24 +2078,41 @@ struct QtChunk {
     uint64_t open;  // lanes whose child opens a new pack
     uint64_t kid;   // lanes whose child is a query-tree kid (non-leaf or open)
 };
+// (a step per pack, found on the chunk's running sizes; a step per child is
+// 64 dependent scalar steps)
 __device__ __forceinline__ QtChunk qt_walk(int cnt, bool leaf, int sz, int P, int &run)
 {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const uint64_t valid = cnt >= WAVE ? ~0ull : ((1ull << cnt) - 1);
     const uint64_t leafm = __ballot(leaf);
+    int pre = leaf ? sz : 0;  // sizes up to and with this lane's
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const int y = __shfl_up(pre, o, WAVE);
+        if (lane >= o)
+            pre += y;
+    }
     uint64_t open = 0;
-    for (int j = 0; j < cnt; ++j) {
-        if (!((leafm >> j) & 1ull)) {
+    for (int j = 0; j < cnt;) {
+        const uint64_t from = ~0ull << j;
+        if (!((leafm >> j) & 1ull)) {  // to the next leaf
             run = -1;
+            const uint64_t m = leafm & from;
+            j = m ? __ffsll((unsigned long long)m) - 1 : cnt;
             continue;
         }
-        const int s = __builtin_amdgcn_readlane(sz, j);
-        if (run >= 0 && run + s <= P) {
-            run += s;
-        } else {
+        const int ex = j ? __builtin_amdgcn_readlane(pre, j - 1) : 0;
+        // lanes that cannot follow in the run's pack, or end it
+        uint64_t m = (__ballot(run < 0 || run + (pre - ex) > P) | ~leafm) & from;
+        if (m & (1ull << j)) {  // the child itself opens a pack
             open |= 1ull << j;
-            run = s;
+            run = 0;
+            m = (__ballot(pre - ex > P) | ~leafm) & (from << 1);
         }
+        const int e = m ? min(cnt, __ffsll((unsigned long long)m) - 1) : cnt;
+        run += __builtin_amdgcn_readlane(pre, e - 1) - ex;
+        j = e;
     }
-    const uint64_t valid = cnt >= WAVE ? ~0ull : ((1ull << cnt) - 1);
     return QtChunk{open, (~leafm & valid) | open};
 }
 
@@ -2117,12 +2134,21 @@ __global__ void k_qt_count(int nn, const int32_t *__restrict__ ccnt,
         P = 0;
     int packs = 0, kids = 0, run = -1;
     const int c0 = cc > 0 ? cbeg[v] : 0;
+    int nc = 1, nb = 0, ne = 0;  // the next chunk's, in flight
+    auto fetch = [&](int a) {
+        if (a + lane < cc) {
+            nc = ccnt[c0 + a + lane];
+            nb = pb[c0 + a + lane];
+            ne = pe[c0 + a + lane];
+        }
+    };
+    fetch(0);
     for (int a0 = 0; a0 < cc; a0 += WAVE) {
         const int cnt = min(WAVE, cc - a0);
-        const int u = c0 + a0 + lane;
         const bool in = lane < cnt;
-        const bool leaf = in && ccnt[u] == 0;
-        const int sz = in ? pe[u] - pb[u] : 0;
+        const bool leaf = in && nc == 0;
+        const int sz = in ? ne - nb : 0;
+        fetch(a0 + WAVE);
         const QtChunk q = qt_walk(cnt, leaf, sz, P, run);
         packs += __popcll(q.open);
         kids += __popcll(q.kid);
@@ -2172,12 +2198,24 @@ __global__ void k_qt_fill(int nn, const int32_t *__restrict__ ccnt,
     int kd0 = kidoff[v];
     int run = -1;
     const int c0 = cbeg[v];
+    int nc = 1, nb = 0, ne = 0, np = 0;  // the next chunk's, in flight
+    auto fetch = [&](int a) {
+        if (a + lane < cc) {
+            nc = ccnt[c0 + a + lane];
+            nb = pb[c0 + a + lane];
+            ne = pe[c0 + a + lane];
+            np = cpos[c0 + a + lane];
+        }
+    };
+    fetch(0);
+    int held = -1, held_e = 0;  // pack whose end the next chunk may move
     for (int a0 = 0; a0 < cc; a0 += WAVE) {
         const int cnt = min(WAVE, cc - a0);
         const int u = c0 + a0 + lane;
         const bool in = lane < cnt;
-        const bool leaf = in && ccnt[u] == 0;
-        const int pbk = in ? pb[u] : 0, pek = in ? pe[u] : 0;
+        const bool leaf = in && nc == 0;
+        const int pbk = in ? nb : 0, pek = in ? ne : 0, cp = np;
+        fetch(a0 + WAVE);
         const QtChunk q = qt_walk(cnt, leaf, pek - pbk, P, run);
         // this lane's pack (the last one opened at or before it) and slot
         const int pk = pk0 + __popcll(q.open & (below | (1ull << lane)));
@@ -2186,24 +2224,26 @@ __global__ void k_qt_fill(int nn, const int32_t *__restrict__ ccnt,
             q_kids[kd] = u;
         if ((q.open >> lane) & 1ull) {
             q_kids[kd] = pk;
-            q_cpos[pk] = cpos[u];
+            q_cpos[pk] = cp;
             q_pb[pk] = pbk;
             q_kbeg[pk] = 0;
             q_kcnt[pk] = 0;
             q_rad[pk] = 0.f;
         }
-        // the pack's end: written by its last leaf in this chunk (a run
-        // that goes on in the next chunk is written again there, after this
-        // store has completed)
-        const bool last =
-            lane == cnt - 1 || (lane < WAVE - 1 && ((q.kid >> (lane + 1)) & 1ull));
+        // a pack's end: written by its last leaf, the chunk's last one's when
+        // the next chunk does not go on with it
+        if (held >= 0 && (q.kid & 1ull) && lane == 0)
+            q_pe[held] = held_e;
+        const bool last = lane < WAVE - 1 && ((q.kid >> (lane + 1)) & 1ull);
         if (leaf && last)
             q_pe[pk] = pek;
+        held = __builtin_amdgcn_readlane(leaf ? pk : -1, cnt - 1);
+        held_e = __builtin_amdgcn_readlane(pek, cnt - 1);
         pk0 += __popcll(q.open);
         kd0 += __popcll(q.kid);
-        if (a0 + WAVE < cc)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     }
+    if (held >= 0 && lane == 0)
+        q_pe[held] = held_e;
 }
 
 // Radius of each pack: the largest key from its centre to its points.
