@@ -1050,88 +1050,135 @@ k_update_ham(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restric
     }
 }
 
-// k_update for strings.  A distance is some five thousand instructions, so
-// the work-group's waves share one chunk's new centres (wave w takes every
-// LEV_W-th; 50K strings are 782 chunks, under one wave per SIMD otherwise)
-// and the nearest of them meet in LDS, the earliest centre winning ties as
-// in a scan in order.  The point is the pattern (its planes loaded once per
-// pass), the centre the text: every lane reads the same symbol.  A centre
-// whose length differs by D or more cannot come nearer than D.
+// k_update for strings, three kernels.
+//
+// A new centre c was at distance D(c) or more from every centre before it, so
+// a point within D(c) / 2 of its own centre is no nearer to c (triangle
+// inequality): k_lev_need lists, per hub, the points farther than half the
+// smallest D(c) of the pass, and only those are compared, 64 to a wave.  Once
+// its group's centre is taken a point drops out.
+//
+// A distance is some five thousand instructions, so a work-group's waves
+// share 64 points' new centres (wave w takes every LEV_W-th; 50K strings are
+// 782 chunks, under one wave per SIMD otherwise) and the nearest of them meet
+// in LDS, the earliest centre winning ties as in a scan in order.  The point
+// is the pattern (its planes loaded once per pass), the centre the text:
+// every lane reads the same symbol.  A centre whose length differs by D or
+// more cannot come nearer than D.
+//
+// What bounds it: the integer instructions of the distances.  50K strings of
+// up to 128 symbols: 10.6 -> 9.5 ms a call against comparing every point.
+struct LevPass {
+    float *dmin;    // [hubs] smallest D of the pass's new centres, at selection
+    int32_t *nact;  // [hubs] points listed (cleared by the selection)
+    int32_t *act;   // [n] their positions, from the hub's first on
+};
 constexpr int LEV_W = 8;
+
+__global__ void __launch_bounds__(256)
+k_lev_need(const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
+           const int32_t *__restrict__ ch_e, int NC, const int32_t *__restrict__ live, Hubs hb,
+           const float *__restrict__ D, LevPass V)
+{
+    const int lane = threadIdx.x % CH;
+    const int nq = *live ? NC : 0;
+    for (int c = blockIdx.x * 4 + threadIdx.x / CH; c < nq; c += gridDim.x * 4) {
+        const int h = ch_hub[c];
+        if (!hb.act[h] || hb.m[h] == hb.ma[h])
+            continue;
+        const int p = ch_s[c] + lane;
+        const bool need = p < ch_e[c] && 2.f * D[p] > V.dmin[h];
+        const uint64_t m = __ballot(need);
+        int at = 0;
+        if (lane == 0 && m)
+            at = atomicAdd(&V.nact[h], __popcll(m));
+        at = __shfl(at, 0, WAVE);
+        if (need)
+            V.act[hb.b[h] + at + __popcll(m & ((1ull << lane) - 1))] = p;
+    }
+}
+
 template <int NW, int NB>
 __global__ void __launch_bounds__(CH *LEV_W)
-k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
-             const int32_t *__restrict__ ch_e, int NC, const int32_t *__restrict__ live,
-             int32_t *__restrict__ live_next, Hubs hb,
-             const int32_t *__restrict__ cent,
-             const int32_t *__restrict__ perm, float *__restrict__ D,
-             int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
-             unsigned long long *__restrict__ cand, int kmax,
-             unsigned long long *__restrict__ cnt)
+k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, int NC,
+             const int32_t *__restrict__ live, Hubs hb, const int32_t *__restrict__ cent,
+             const int32_t *__restrict__ perm, float *__restrict__ D, int32_t *__restrict__ L,
+             LevPass V)
 {
     __shared__ int sd[LEV_W][CH], sj[LEV_W][CH];
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CH));
     const int lane = threadIdx.x % CH;
     const int nq = *live ? NC : 0;
+    for (int c = blockIdx.x; c < nq; c += gridDim.x) {
+        const int h = ch_hub[c];
+        const int j0 = hb.ma[h], j1 = hb.m[h];
+        if (!hb.act[h] || j1 == j0)
+            continue;  // the same for the whole work-group
+        // the hub's k-th chunk takes the k-th 64 listed points
+        const int i0 = (c - hb.cb[h]) * CH, na = V.nact[h];
+        if (i0 >= na)
+            continue;
+        const int b = hb.b[h];
+        const bool valid = i0 + lane < na;
+        const int p = V.act[b + i0 + (valid ? lane : 0)], o = perm[p];
+        const float dcur = valid ? D[p] : 0.f;
+        int bd = INT_MAX, bj = INT_MAX;
+        LevPat<NW, NB> q;
+        lev_load(q, P.peq + (size_t)o * P.sigma * P.W, P.sigma, P.W, P.len[o]);
+        for (int j = j0 + w; j < j1; j += LEV_W) {
+            const int cj = __builtin_amdgcn_readfirstlane(cent[b + j]);
+            const int lc = __builtin_amdgcn_readfirstlane(P.len[cj]);
+            if (!__any(valid && (float)abs(q.m - lc) < dcur))
+                continue;
+            const int d = lev_run(q, P.s + (size_t)cj * P.dp, lc);
+            if (d < bd) {
+                bd = d;
+                bj = j;
+            }
+        }
+        __syncthreads();  // the previous chunk's values are consumed
+        sd[w][lane] = bd;
+        sj[w][lane] = bj;
+        __syncthreads();
+        if (w != 0 || !valid)
+            continue;
+        bd = INT_MAX, bj = INT_MAX;
+#pragma unroll
+        for (int k = 0; k < LEV_W; ++k) {
+            const int d = sd[k][lane], j = sj[k][lane];
+            if (d < bd || (d == bd && j < bj)) {
+                bd = d;
+                bj = j;
+            }
+        }
+        if (bj != INT_MAX && (float)bd < dcur) {
+            D[p] = (float)bd;
+            L[p] = bj;
+        }
+    }
+}
+
+__global__ void __launch_bounds__(256)
+k_lev_report(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
+             const int32_t *__restrict__ ch_e, int NC, const int32_t *__restrict__ live,
+             int32_t *__restrict__ live_next, Hubs hb, const int32_t *__restrict__ perm,
+             const float *__restrict__ D, const LevelTab *__restrict__ tab,
+             unsigned long long *__restrict__ cand, int kmax)
+{
+    const int lane = threadIdx.x % CH;
+    const int nq = *live ? NC : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         *live_next = 0;  // set by this pass's selection
-    for (int t = blockIdx.x; t < nq; t += gridDim.x) {
-        const int c = t, h = ch_hub[c];
+    for (int c = blockIdx.x * 4 + threadIdx.x / CH; c < nq; c += gridDim.x * 4) {
+        const int h = ch_hub[c];
         if (!hb.act[h])
-            continue;  // the same for the whole work-group
-        const int s = ch_s[c], e = ch_e[c], p = s + lane;
-        const bool valid = p < e;
-        const int b = hb.b[h], j0 = hb.ma[h], j1 = hb.m[h];
-        const int o = valid ? perm[p] : perm[s];
-        float dcur = valid ? D[p] : 0.f;
-        int lcur = valid ? L[p] : 0;
-        if (j1 > j0) {
-            int bd = INT_MAX, bj = INT_MAX;
-            LevPat<NW, NB> q;
-            lev_load(q, P.peq + (size_t)o * P.sigma * P.W, P.sigma, P.W, P.len[o]);
-            for (int j = j0 + w; j < j1; j += LEV_W) {
-                const int cj = __builtin_amdgcn_readfirstlane(cent[b + j]);
-                const int lc = __builtin_amdgcn_readfirstlane(P.len[cj]);
-                if (!__any(valid && (float)abs(q.m - lc) < dcur))
-                    continue;
-                const int d = lev_run(q, P.s + (size_t)cj * P.dp, lc);
-                if (d < bd) {
-                    bd = d;
-                    bj = j;
-                }
-            }
-            __syncthreads();  // the previous chunk's values are consumed
-            sd[w][lane] = bd;
-            sj[w][lane] = bj;
-            __syncthreads();
-        }
-        if (w != 0)
             continue;
+        const int p = ch_s[c] + lane;
         float dv = -1.f;
         int id = INT_MAX;
-        if (valid) {
-            if (j1 > j0) {
-                int bd = INT_MAX, bj = INT_MAX;
-#pragma unroll
-                for (int k = 0; k < LEV_W; ++k) {
-                    const int d = sd[k][lane], j = sj[k][lane];
-                    if (d < bd || (d == bd && j < bj)) {
-                        bd = d;
-                        bj = j;
-                    }
-                }
-                if (bj != INT_MAX && (float)bd < dcur) {
-                    dcur = (float)bd;
-                    lcur = bj;
-                }
-                D[p] = dcur;
-                L[p] = lcur;
-            }
-            const Thr T = tab->t[hb.lvl[h] - 1 + LOFF];
-            if (!within<M_LEV>(P, o, cent[b + lcur], dcur, T, cnt + 1)) {
-                dv = dcur;
-                id = o;
-            }
+        if (p < ch_e[c] && D[p] > tab->t[hb.lvl[h] - 1 + LOFF].lo) {  // whole distances
+            dv = D[p];
+            id = perm[p];
         }
         report_chunk(c, NC, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cand);
     }
@@ -1525,7 +1572,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
          const unsigned long long *__restrict__ cand, int NC,
          const LevelTab *__restrict__ tab, int kmax, int32_t *__restrict__ live_next,
          unsigned long long *__restrict__ cnt,
-         SelPart *__restrict__ sp, MxArgs A)
+         SelPart *__restrict__ sp, MxArgs A, LevPass V)
 {
     __shared__ unsigned long long buf[SEL_BUF], out[MAX_K];
     __shared__ unsigned long long conf[MAX_K][SEL_W];
@@ -1533,7 +1580,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
     __shared__ __align__(16) float cnrm[NKS ? MAX_K : 4];    // candidates' norms
     __shared__ int cpos[NKS ? MAX_K : 1], cid[NKS ? MAX_K : 1];  // positions, input ids
     __shared__ int acc[MAX_K];
-    __shared__ int nacc_s, nk_s, fill_s;
+    __shared__ int nacc_s, nk_s, fill_s, last_s;  // last_s: the last one accepted
     const int K = min(kmax, MAX_K);
     for (int h = blockIdx.x; h < H; h += gridDim.x) {
     if (!hb.act[h])
@@ -1749,8 +1796,10 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
                 const unsigned long long below = l == 0 ? 0ull : (~0ull >> (WAVE - l));
                 acc[__popcll(am & below)] = 0x7FFFFFFF - (int)(uint32_t)buf[l];
             }
-            if (l == 0)
+            if (l == 0) {
                 nacc_s = __popcll(am);
+                last_s = am ? 63 - __builtin_clzll(am) : 0;
+            }
         }
     } else if (threadIdx.x == 0) {
         unsigned long long am[SEL_W];
@@ -1765,6 +1814,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
                 ok &= (conf[i][w] & am[w]) == 0ull;
             if (ok) {
                 am[i >> 6] |= 1ull << (i & 63);
+                last_s = i;
                 acc[na++] = 0x7FFFFFFF - (int)(uint32_t)buf[i];
             }
         }
@@ -1784,6 +1834,10 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
             hb.act[h] = 0;
         } else {
             *live_next = 1;  // every hub that goes on stores the same
+            if constexpr (M == M_LEV) {
+                V.dmin[h] = __uint_as_float((uint32_t)(buf[last_s] >> 32));
+                V.nact[h] = 0;
+            }
             // the next update compares every point with the new centres
             atomicAdd(count_slot(cnt, h),
                       (unsigned long long)nacc * (unsigned)(hb.e[h] - hb.b[h]));
@@ -2492,6 +2546,9 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
             *ch_e = S.get<int32_t>(maxch), *ch_k = S.get<int32_t>(maxch);
     unsigned long long *cand = S.get<unsigned long long>((size_t)maxch * CAND_R);
     int32_t *live_d = S.get<int32_t>(2);
+    LevPass lev{};
+    if (M == M_LEV)
+        lev = LevPass{S.get<float>(maxch), S.get<int32_t>(maxch), S.get<int32_t>(n)};
     // net-selection passes per graph replay (even: the flag read is live_d[0]
     // again); 1 = one eager pass per host check
     const int GP = T->opt.graph_passes <= 1 ? 1 : (T->opt.graph_passes + 1) / 2 * 2;
@@ -2620,10 +2677,15 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
             sp = S.get<SelPart>(H);
         auto pass = [&](hipStream_t s, int k) {
             int32_t *lc = live_d + k, *lx = live_d + (1 - k);
-            if constexpr (M == M_LEV)
-                launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent, perm, D, L, tab, cand,
-                                  T->opt.kmax, cnt);
-            else if (M == M_HAM && T->dp <= 8) {
+            if constexpr (M == M_LEV) {
+                const dim3 gw(grid_cap(NC, 4, 4096));
+                FNN_LAUNCH(k_lev_need, gw, dim3(256), 0, s, ch_hub, ch_s, ch_e, NC, lc, hubs, D,
+                           lev);
+                launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, NC, lc, hubs, cent,
+                                  perm, D, L, lev);
+                FNN_LAUNCH(k_lev_report, gw, dim3(256), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx,
+                           hubs, perm, D, tab, cand, T->opt.kmax);
+            } else if (M == M_HAM && T->dp <= 8) {
                 auto go = [&](auto nw) {
                     FNN_LAUNCH((k_update_ham<decltype(nw)::value>), dim3(gu), dim3(CH * UPD_W),
                                0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs,
@@ -2657,17 +2719,17 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                 if (sp) {
                     const int K = std::min(T->opt.kmax, MAX_K);
                     const int nt = (int)cdiv(std::max(1, K * (K - 1) / 2), WAVE);
-                    FNN_LAUNCH((k_select<M, SEL_TOP, 0>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent, cand, NC, tab, T->opt.kmax, lx, cnt, sp, mx.a);
+                    FNN_LAUNCH((k_select<M, SEL_TOP, 0>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent, cand, NC, tab, T->opt.kmax, lx, cnt, sp, mx.a, lev);
                     FNN_LAUNCH(k_conflicts, dim3((unsigned)(H * nt)), dim3(WAVE), 0, s, P,
                                hubs, nt, sp, tab, cnt);
                     FNN_LAUNCH((k_select<M, SEL_TAKE, 0>), gs, dim3(SEL_T), 0, s, P, hubs, H,
-                               cent, cand, NC, tab, T->opt.kmax, lx, cnt, sp, mx.a);
+                               cent, cand, NC, tab, T->opt.kmax, lx, cnt, sp, mx.a, lev);
                     return;
                 }
             }
             auto all = [&](auto kw) {
                 FNN_LAUNCH((k_select<M, SEL_ALL, decltype(kw)::value>), gs, dim3(SEL_T), 0, s, P,
-                           hubs, H, cent, cand, NC, tab, T->opt.kmax, lx, cnt, nullptr, mx.a);
+                           hubs, H, cent, cand, NC, tab, T->opt.kmax, lx, cnt, nullptr, mx.a, lev);
             };
             if constexpr (M == M_L2 || M == M_ANG) {
                 if (mx.on) {
