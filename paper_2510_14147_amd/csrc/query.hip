@@ -1075,6 +1075,84 @@ __device__ __forceinline__ void wave_sort_row(int32_t *__restrict__ col,
     }
 }
 
+// The same for rows whose columns lie within SPAN32 of each other: 32-bit
+// keys of the column past the row's smallest and the entry's slot, so an
+// exchange is half the shuffles and a minimum and a maximum, and the distance
+// waits in LDS at its slot.  What bounds it: the exchanges.  1M rows of 507
+// entries on average: 11.1 -> 5.0 ms of sorts.
+constexpr int64_t SPAN32 = 1ll << 21;  // 11 bits of slot at 32 keys per lane
+template <int V>
+__device__ __forceinline__ void wave_sort_row32(int32_t *__restrict__ col,
+                                                float *__restrict__ dist, int64_t b, int len,
+                                                int lane,
+                                                const unsigned long long *__restrict__ pk,
+                                                uint32_t *tk)
+{
+    constexpr int SB = 6 + (V >= 2) + (V >= 4) + (V >= 8) + (V >= 16) + (V >= 32);
+    static_assert((WAVE * V) == 1 << SB && SB <= 11, "slot bits");
+    uint32_t *td = tk + WAVE * (V + 1);  // distances by slot; tk: keys, padded as above
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    uint32_t x[V];
+    int lo = INT_MAX;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int g = v * WAVE + lane;
+        int c = INT_MAX;
+        if (g < len) {
+            const unsigned long long e =
+                pk ? pk[b + g] : pack_entry(col[b + g], dist[b + g]);
+            c = (int)(e >> 32);
+            td[g] = (uint32_t)e;
+        }
+        x[v] = (uint32_t)c;
+        lo = min(lo, c);
+    }
+    lo = -wave_max(-lo);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int g = v * WAVE + lane;  // any order will do to start from
+        x[v] = g < len ? (x[v] - (uint32_t)lo) << SB | (uint32_t)g : ~0u;
+    }
+#pragma unroll
+    for (int k = 2; k <= WAVE * V; k <<= 1) {
+#pragma unroll
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            if (j < V) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    if (v & j)
+                        continue;
+                    const bool up = ((lane * V + v) & k) == 0;
+                    const uint32_t a = min(x[v], x[v | j]), c = max(x[v], x[v | j]);
+                    x[v] = up ? a : c;
+                    x[v | j] = up ? c : a;
+                }
+            } else {
+                const bool lower = (lane & (j / V)) == 0;
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const uint32_t o = __shfl_xor(x[v], j / V, WAVE);
+                    const bool up = ((lane * V + v) & k) == 0;
+                    x[v] = lower == up ? min(o, x[v]) : max(o, x[v]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+        tk[lane * (V + 1) + v] = x[v];
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int g = v * WAVE + lane;
+        if (g < len) {
+            const uint32_t y = tk[g + g / V];
+            col[b + g] = lo + (int)(y >> SB);
+            dist[b + g] = __uint_as_float(td[y & (WAVE * V - 1)]);
+        }
+    }
+}
+
 constexpr int SORT_WAVE_MAX = 32 * WAVE;  // longest row of k_sort_wave
 
 // Rows of at most 512 entries: one wave per row (register bitonic sort);
@@ -1082,6 +1160,7 @@ constexpr int SORT_WAVE_MAX = 32 * WAVE;  // longest row of k_sort_wave
 // add to the list's counter per row took 12 ns each, one after another: 1 ms
 // of 1.1 at 2.1M rows, 4 % of them long).  With pk non-null the entries are
 // read packed from pk (same slots).
+template <bool N32>
 __global__ void __launch_bounds__(256)
 k_sort_small(const int64_t *__restrict__ row_ptr, int n, int32_t *__restrict__ col,
              float *__restrict__ dist, int32_t *__restrict__ mid_list,
@@ -1124,6 +1203,18 @@ k_sort_small(const int64_t *__restrict__ row_ptr, int n, int32_t *__restrict__ c
             }
         continue;
     }
+    if constexpr (N32) {
+        uint32_t *tk = reinterpret_cast<uint32_t *>(tr);
+        if (len > 4 * WAVE)
+            wave_sort_row32<8>(col, dist, b, (int)len, lane, pk, tk);
+        else if (len > 2 * WAVE)
+            wave_sort_row32<4>(col, dist, b, (int)len, lane, pk, tk);
+        else if (len > WAVE)
+            wave_sort_row32<2>(col, dist, b, (int)len, lane, pk, tk);
+        else
+            wave_sort_row32<1>(col, dist, b, (int)len, lane, pk, tk);
+        continue;
+    }
     if (len > 4 * WAVE) {
         wave_sort_row<8>(col, dist, b, (int)len, lane, pk, tr);
         continue;
@@ -1159,14 +1250,18 @@ k_sort_small(const int64_t *__restrict__ row_ptr, int n, int32_t *__restrict__ c
             flush(k);
 }
 
-// Listed rows of 513..SORT_WAVE_MAX entries: one wave per row, the register
-// sort with 16 or 32 entries per lane.
+// Listed rows of 32 V + 1 .. 64 V entries: one wave per row, the register
+// sort with V entries per lane.  What bounds it: the row's loads, at the
+// waves per SIMD that V leaves (16: four; 32: two; one kernel for both held
+// rows of up to 1024 entries to two: 1M rows of 507 on average, 10.5 ms for
+// 8.4).
+template <int V, bool N32>
 __global__ void __launch_bounds__(256)
 k_sort_wave(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list,
             int nl, int32_t *__restrict__ col, float *__restrict__ dist,
             const unsigned long long *__restrict__ pk)
 {
-    __shared__ unsigned long long tr_s[256 / WAVE][WAVE * 33];  // up to 32 keys per lane
+    __shared__ unsigned long long tr_s[256 / WAVE][WAVE * (V + 1)];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wpb = blockDim.x / WAVE;
     unsigned long long *tr = tr_s[threadIdx.x / WAVE];
@@ -1174,10 +1269,12 @@ k_sort_wave(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ lis
         const int r = list[li];
         const int64_t b = row_ptr[r];
         const int len = (int)(row_ptr[r + 1] - b);
-        if (len > 16 * WAVE)
-            wave_sort_row<32>(col, dist, b, len, lane, pk, tr);
+        if (len <= V / 2 * WAVE || len > V * WAVE)
+            continue;
+        if constexpr (N32)
+            wave_sort_row32<V>(col, dist, b, len, lane, pk, reinterpret_cast<uint32_t *>(tr));
         else
-            wave_sort_row<16>(col, dist, b, len, lane, pk, tr);
+            wave_sort_row<V>(col, dist, b, len, lane, pk, tr);
     }
 }
 
@@ -1871,7 +1968,11 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, fl
     if (nnz <= 0 && err)
         *herr = read_scalar(err, s);
     if (nnz > 0) {
-        FNN_LAUNCH(k_sort_small, dim3(grid_cap(n, 4, 4096)), dim3(256), 0, s,
+        if (span <= SPAN32)
+            FNN_LAUNCH(k_sort_small<true>, dim3(grid_cap(n, 4, 4096)), dim3(256), 0, s,
+                   row_ptr, n, col, dist, mid, lng, cc, pk);
+        else
+            FNN_LAUNCH(k_sort_small<false>, dim3(grid_cap(n, 4, 4096)), dim3(256), 0, s,
                    row_ptr, n, col, dist, mid, lng, cc, pk);
         int32_t hcc[2];
         Readback rb(s);
@@ -1881,13 +1982,24 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, fl
         rb.wait();
         if (hcc[0] > 0) {
             // (at most SORT_WAVE_MAX entries: held by a work-group of 256)
-            if (span <= SPAN_NARROW)
+            if (span <= SPAN_NARROW) {
                 FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, 256>),
                            dim3(grid_cap(hcc[0], 1, 16 * num_cus())), dim3(256), 0, s, row_ptr,
                            mid, hcc[0], col, dist, pk, nullptr, nullptr);
-            else
-                FNN_LAUNCH(k_sort_wave, dim3(grid_cap(hcc[0], 4, 4096)), dim3(256), 0, s,
-                           row_ptr, mid, hcc[0], col, dist, pk);
+            } else {
+                auto wave = [&](auto v, auto n32) {
+                    FNN_LAUNCH((k_sort_wave<decltype(v)::value, decltype(n32)::value>),
+                               dim3(grid_cap(hcc[0], 4, 8192)), dim3(256), 0, s, row_ptr, mid,
+                               hcc[0], col, dist, pk);
+                };
+                if (span <= SPAN32) {
+                    wave(std::integral_constant<int, 16>{}, std::true_type{});
+                    wave(std::integral_constant<int, 32>{}, std::true_type{});
+                } else {
+                    wave(std::integral_constant<int, 16>{}, std::false_type{});
+                    wave(std::integral_constant<int, 32>{}, std::false_type{});
+                }
+            }
         }
         if (hcc[1] > 0) {
             int64_t *soff = nullptr;

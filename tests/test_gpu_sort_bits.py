@@ -1,6 +1,7 @@
 """Rows sorted by counting: lengths at its edges (2048 entries and below sort
 in registers of a wave, up to 8192 are held, longer ones read twice), columns
-within one span of 262144 and of 1048576 and across several, entries placed
+within one span of 262144 and of 1048576, across several, and beyond the
+2097152 of 32-bit sort keys, entries placed
 packed (the filter's) and unpacked (the plain tiles')."""
 import numpy as np
 import pytest
@@ -48,7 +49,7 @@ def _check(x, sizes, ids, **kw):
 
 @pytest.mark.parametrize("n", [40000, 262144, 262200, 1048600, 2200000])
 def test_spans(n):
-    sizes = [600, 1300, 2049, 2300, 4100]
+    sizes = [2, 40, 65, 66, 100, 129, 200, 257, 300, 513, 600, 1025, 1300, 2049, 2300, 4100]
     x, ids = _cliques(n, sizes, 3, n)
     _check(x, sizes, ids)
 
