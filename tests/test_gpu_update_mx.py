@@ -118,3 +118,29 @@ def test_batch(d):
         cmp = O.compare_csr(s - s[0], col[s[0]:s[-1]] - lo, dist[s[0]:s[-1]], *ref, rtol=1e-5)
         assert cmp["missing"] == 0 and cmp["extra"] == 0 and cmp["ok"], cmp
         lo += len(c)
+
+
+@pytest.mark.parametrize("kmax,d", [(64, 3), (200, 3), (64, 16)])
+def test_sliced_candidates(kmax, d):
+    """A hub of more than 16384 chunks (its candidates are cut per slice
+    first): the root's children are more than half its radius bound apart and
+    hold every point within that of their centres."""
+    import paper_2510_14147_amd as fnn
+    print(f"[case] kmax={kmax} d={d}", flush=True)
+    x = np.random.default_rng(kmax + d).random((1100000, d)).astype(np.float32)
+    t = fnn.fnn_tree_export(fnn.fnn_tree_build(x, "l2", kmax=kmax))
+    half = 2.0 ** (int(t["level"][0]) - 1)
+    ch = np.arange(t["child_begin"][0], t["child_begin"][0] + t["child_count"][0])
+    assert len(ch) > 1
+    c = x[t["center"][ch]].astype(np.float64)
+    dist = np.sqrt(((c[:, None] - c[None]) ** 2).sum(2))
+    np.fill_diagonal(dist, np.inf)
+    assert dist.min() > half
+    assert t["pt_begin"][ch[0]] == 0 and t["pt_end"][ch[-1]] == len(x)
+    assert np.array_equal(t["pt_begin"][ch[1:]], t["pt_end"][ch[:-1]])
+    assert np.array_equal(np.sort(t["order"]), np.arange(len(x)))
+    far = 0.0
+    for k, u in enumerate(ch):
+        p = x[t["order"][t["pt_begin"][u]:t["pt_end"][u]]].astype(np.float64)
+        far = max(far, float(np.sqrt(((p - c[k]) ** 2).sum(1)).max()))
+    assert far <= half
