@@ -2,6 +2,7 @@
 // filter): output sinks and the MFMA filter's arguments.
 #pragma once
 
+#include "lists.h"
 #include "tree.h"
 
 namespace fnn {

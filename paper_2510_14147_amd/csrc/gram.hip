@@ -48,8 +48,6 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
-constexpr int GP = 64;           // rows per pack (max) on the MFMA path
-constexpr int GW = 4;            // packs per group = waves per work-group
 constexpr int UNIT_MAX = 64;     // list entries per work unit (at most)
 // two waves per SIMD: the second wave hides the first one's LDS and MFMA
 // dependency stalls (one wave per SIMD with 512 registers measured 1.7x
@@ -2981,7 +2979,7 @@ double gram_pair_ms(int metric, int dp, double kmax)
 
 bool gram_rect_fits(int64_t na, int64_t nb)
 {
-    return cdiv(cdiv(na, GP), GW) * cdiv(nb, GP) < INT32_MAX;
+    return list_fits(cdiv(cdiv(na, GP), GW) * cdiv(nb, GP));
 }
 
 // Work list of a bichromatic rectangle (T->rect).
@@ -3054,19 +3052,16 @@ void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &
     // than GP, the work list is every (group g, B >= 4g) pair; the few pairs
     // the traversal pruned are evaluated too, which changes no edge.
     {
-        const int ngr = (npk + GW - 1) / GW;
         const long long allp = (long long)npk * (npk + 1) / 2;
-        long long mu = 0;  // entries: every (group, B >= its first pack)
-        for (int g = 0; g < ngr; ++g)
-            mu += npk - GW * g;
-        if (npk > 0 && (double)ninter >= 0.95 * (double)allp && mu < INT32_MAX) {
-            // one cloud: full packs of consecutive tree positions in place of
-            // the tree's (indexed from 0, not past the nodes)
-            const bool one = T->ncloud <= 1 && T->cross_a < 0;
+        // one cloud: full packs of consecutive tree positions in place of
+        // the tree's (indexed from 0, not past the nodes), whose number may
+        // be larger than the tree's (packs taller than GP) or smaller
+        const bool one = T->ncloud <= 1 && T->cross_a < 0;
+        const int np = one ? (int)cdiv(T->n, GP) : npk;
+        if (npk > 0 && (double)ninter >= 0.95 * (double)allp && dense_fits(np)) {
             if (one || gram_packs_fit(T, S)) {
-                int base = nn, np = npk;
+                int base = nn;
                 if (one) {
-                    np = (int)((T->n + GP - 1) / GP);
                     int32_t *vpb = S.get<int32_t>(np), *vpe = S.get<int32_t>(np);
                     FNN_LAUNCH(k_uniform_packs, dim3(grid_for(np, 256)), dim3(256), 0, s,
                                (int)T->n, np, vpb, vpe);
@@ -3074,11 +3069,8 @@ void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &
                     G.q_pb = vpb;
                     G.q_pe = vpe;
                     G.upk = (int)T->n;
-                    const int ng1 = (np + GW - 1) / GW;
-                    mu = 0;
-                    for (int g = 0; g < ng1; ++g)
-                        mu += np - GW * g;
                 }
+                const int64_t mu = dense_entries(np);
                 // units ordered by B run (runs aligned to RUN packs), then by
                 // group: the units of one run read the same B tiles.  The
                 // host only sums the per-run counts; the run and unit tables
