@@ -3112,6 +3112,8 @@ void gram_prepare(const fnn_tree *T, int prec, int proj, double eps, const Thr &
     }
 
     // ---- lists: canonical pairs, routed, unique per (group, B) ----------
+    if (!inter && ninter > 0)
+        fail(FNN_EINTERNAL, "a closed-form work list of %lld pack pairs does not fit", ninter);
     uint32_t *k1 = S.get<uint32_t>(ninter + 1), *v1 = S.get<uint32_t>(ninter + 1);
     int2 *rs = S.get<int2>(ninter + 1);
     unsigned long long *cnt = S.get<unsigned long long>(2);

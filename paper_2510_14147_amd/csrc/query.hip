@@ -2084,12 +2084,6 @@ struct Learned {
 
 const float *cost_model_device();
 
-// What a traversal costs beside the filter, milliseconds: launches and host
-// reads, per point (its levels' tests), and per pack pair it keeps
-// (expansion, two radix sorts, unique groups).  Measured: 20K to 60K points
-// in 20 clusters, 5 % kept, 0.4 to 0.7 ms; 200K points 1.3 to 2.1 ms; 988258
-// codes, 76.7M pairs kept, 30 ms.
-constexpr double TRAV_MS = 0.4, TRAV_POINT_MS = 4e-6, TRAV_PAIR_MS = 4.2e-7;
 // A bichromatic query's general path builds a tree over the queries and
 // joins two trees first: about 1.2 ms of launches and host reads more.
 constexpr double QUERY_TREE_MS = 1.2;
@@ -2227,28 +2221,21 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         return false;  // the caller builds a query tree instead
 
     // ---- traversal ------------------------------------------------------
-    // The filter may take every pair from a closed-form list instead of the
-    // traversal's (any pair set that contains the needed ones gives the
-    // exact graph): at once while the whole list costs no more than a
-    // traversal's launches and host reads, else where a seeded sample of
-    // pack pairs under the traversal's own test says that what it could
-    // prune is worth less than itself.
+    // (or every pair from the filter's closed-form list: dense_rule)
     int2 *inter = nullptr;
     long long ninter = 0;
     bool dense = rect;
     if (!rect && use_gram && ncl == 1 && !opt.trace && T->npacks > 0) {
-        const double pairs = 0.5 * n * (double)n, c = gram_pair_ms(M, T->dp, E.lo);
-        const double fixed = TRAV_MS + TRAV_POINT_MS * n;
-        dense = pairs * c <= fixed;
-        if (!dense) {
+        const double c = gram_pair_ms(M, T->dp, E.lo);
+        const Dense d = dense_rule(n, c);
+        dense = d == DENSE_YES;
+        if (d == DENSE_SAMPLE) {
             const int ns = 8192;
             unsigned long long *pc = S.get<unsigned long long>(1);
             fill(pc, 0ull, 1, s);
             FNN_LAUNCH((k_prune_sample<M>), dim3(ns / 256), dim3(256), 0, s, P, Q, pr,
                        (int)T->npacks, ns, pc);
-            const double gone = (double)read_scalar(pc, s) / ns;
-            const double kept = 0.5 * (1.0 - gone) * T->npacks * (double)T->npacks;
-            dense = gone * pairs * c <= fixed + TRAV_PAIR_MS * kept;
+            dense = dense_sampled(n, T->npacks, c, (double)read_scalar(pc, s) / ns);
             st.traverse_tests = ns;
         }
     }

@@ -1,6 +1,7 @@
 """Limits of the matrix filter's closed-form work lists (CPU only): the host
 arithmetic of csrc/lists.h, compiled by itself, against plain sums at both
-sides of 32-bit entry numbers.  No list of these sizes is made."""
+sides of 32-bit entry numbers, and the rule that takes such a list in place
+of a traversal.  No list of these sizes is made."""
 import ctypes
 import os
 import subprocess
@@ -15,6 +16,11 @@ using namespace fnn;
 extern "C" {
 long long entries(long long np) { return dense_entries(np); }
 int fits(long long np) { return dense_fits(np); }
+int rule(long long n, double c) { return dense_rule(n, c); }
+int sampled(long long n, long long np, double c, double gone)
+{
+    return dense_sampled(n, np, c, gone);
+}
 }
 """
 
@@ -29,6 +35,9 @@ def lists(tmp_path_factory):
     L = ctypes.CDLL(so)
     L.entries.restype = ctypes.c_longlong
     L.entries.argtypes = L.fits.argtypes = [ctypes.c_longlong]
+    L.rule.argtypes = [ctypes.c_longlong, ctypes.c_double]
+    L.sampled.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_double,
+                          ctypes.c_double]
     return L
 
 
@@ -45,3 +54,36 @@ def test_limit(lists):
     # rows in full packs, and the sizes beyond (10M and 2^31 - 1 rows)
     assert top == 131069
     assert not lists.fits(-(-10_000_000 // 64)) and not lists.fits(-(-(2**31 - 1) // 64))
+
+
+NO, YES, SAMPLE = 0, 1, 2
+PRICES = [4.6e-11, 5.7e-11, 8.5e-11, 1.15e-10, 2.5e-10]  # ms per screened pair
+
+
+@pytest.mark.parametrize("c", PRICES)
+def test_rule_never_takes_a_list_without_numbers(lists, c):
+    last = 131069 * 64
+    assert lists.rule(last, c) == SAMPLE
+    for n in (last + 1, 10_000_000, 100_000_000, 2**30, 2**31 - 1):
+        # what the tree prunes would be worth less than the traversal
+        assert lists.sampled(n, n // 40, c, 0.2) or n > 2**30
+        assert lists.rule(n, c) == NO, n
+
+
+@pytest.mark.parametrize("c", PRICES)
+def test_rule_counts_full_packs_not_the_tree_s(lists, c):
+    # one point to a pack: the tree's own packs have no list, full ones do
+    n = 140_000
+    assert not lists.fits(n) and lists.fits(-(-n // 64))
+    assert lists.rule(n, c) in (YES, SAMPLE)
+    # small sets take the list without a sample
+    assert lists.rule(1, c) == lists.rule(20_000, c) == YES
+    assert lists.rule(0, c) == NO
+
+
+@pytest.mark.parametrize("c", PRICES)
+def test_sample_decides_by_what_it_prunes(lists, c):
+    n, np_ = 1_000_000, 20_000
+    take = [lists.sampled(n, np_, c, g / 100) for g in range(101)]
+    assert take[0] and not take[100]
+    assert take == sorted(take, reverse=True)
