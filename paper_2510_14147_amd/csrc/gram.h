@@ -115,9 +115,10 @@ void edges_scatter(const int2 *edges, const float *edist, long long ne, bool bot
 // rows fill exactly); a rank past its row sets ERR_INDEX.
 void edges_place(const int2 *edges, const float *edist, const int2 *erank, long long ne,
                  bool both, const int64_t *row_ptr, const TileOut &o, hipStream_t s);
-// 2 c1 mean|x - mu|^2 / t2min for the BF16 filter (mu per cloud): how much
+// 2 c1 mean|x - mu|^2 / t2min for the filter's format (mu per cloud): how much
 // its rounding margin widens the test against the smallest squared
-// threshold; small values mean a selective filter.
+// threshold; up to MARGIN_MAX the filter is selective.
+constexpr double MARGIN_MAX = 0.5;
 // Per-query statistics of the rows the filter quantises, computed once by
 // the automatic precision rule and reused by the quantisation: the cloud
 // centres (column sums and 1 / sizes) and the largest |x - mu|.

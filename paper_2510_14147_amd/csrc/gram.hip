@@ -2818,7 +2818,9 @@ double gram_margin_of(double mean, double t2min, int prec, int dp, int d)
 {
     const double u32 = 1.0 / 16777216.0;
     const int kq = (int)cdiv(dp, 16) * 16;
-    const double u = prec == FNN_PREC_FP16 ? 1.0 / 2048.0 : 1.0 / 256.0;
+    const double u = prec == FNN_PREC_FP16   ? 1.0 / 2048.0
+                     : prec == FNN_PREC_BF16 ? 1.0 / 256.0
+                                             : 1.0 / 16.0;
     const double c1 = 2.25 * u + (4.0 * kq + 2.0 * d + 72.0) * u32;
     return t2min > 0 ? 2.0 * c1 * mean / t2min : HUGE_VAL;
 }

@@ -2210,7 +2210,7 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         if (M == M_HAM && T->dp <= 4)
             prec = FNN_PREC_I8;
         if ((M == M_L2 || M == M_ANG) && T->dim >= 16 && T->dp <= 128 &&
-            gram_margin_ratio(T, t2min, FNN_PREC_FP16, S, &gpre) <= 0.5)
+            gram_margin_ratio(T, t2min, FNN_PREC_FP16, S, &gpre) <= MARGIN_MAX)
             prec = FNN_PREC_FP16;
     }
     st.precision_used = prec;
@@ -2227,7 +2227,14 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     bool dense = rect;
     if (!rect && use_gram && ncl == 1 && !opt.trace && T->npacks > 0) {
         const double c = gram_pair_ms(M, T->dp, E.lo);
-        const Dense d = dense_rule(n, c);
+        // Hamming codes: exact.  Vectors: the automatic rule's choice is
+        // narrow; a format or a projection that the caller set may not be
+        bool wide = false;
+        if ((M == M_L2 || M == M_ANG) && T->dp <= 128)
+            wide = opt.proj > 0 ||
+                   (opt.precision != FNN_PREC_AUTO &&
+                    !(gram_margin_ratio(T, t2min, prec, S, &gpre) <= MARGIN_MAX));
+        const Dense d = dense_rule(n, T->npacks, c, wide);
         dense = d == DENSE_YES;
         if (d == DENSE_SAMPLE) {
             const int ns = 8192;
@@ -2235,7 +2242,8 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
             fill(pc, 0ull, 1, s);
             FNN_LAUNCH((k_prune_sample<M>), dim3(ns / 256), dim3(256), 0, s, P, Q, pr,
                        (int)T->npacks, ns, pc);
-            dense = dense_sampled(n, T->npacks, c, (double)read_scalar(pc, s) / ns);
+            dense = dense_sampled(n, T->npacks, c, wide, (double)read_scalar(pc, s) / ns) &&
+                    (!wide || gram_packs_fit(T, S));
             st.traverse_tests = ns;
         }
     }
@@ -2750,13 +2758,20 @@ bool query_screens_all(const fnn_tree *T, const void *q, int64_t nq, double eps,
     FNN_HIP(hipStreamSynchronize(s));
     float sum;
     memcpy(&sum, &h[1], sizeof sum);
-    // the automatic precision would most likely choose the plain tiles: half
-    // the mean squared distance of random pairs is the mean |x - mu|^2
-    if (vec && opt.precision == FNN_PREC_AUTO &&
-        !(gram_margin_of(0.5 * sum / ns, gram_t2(M, eps, E), FNN_PREC_FP16, T->dp, T->dim) <=
-          0.5))
-        return false;
     const double gone = (double)h[0] / ns, pairs = (double)T->n * (double)nq;
+    // half the mean squared distance of random pairs is the mean |x - mu|^2:
+    // with a wide margin the automatic precision would most likely choose the
+    // plain tiles, and a filter that the caller set passes too many pairs
+    // (dense_rule)
+    if (vec) {
+        const int prec = opt.precision == FNN_PREC_AUTO ? FNN_PREC_FP16 : opt.precision;
+        const bool wide = !(gram_margin_of(0.5 * sum / ns, gram_t2(M, eps, E), prec, T->dp,
+                                           T->dim) <= MARGIN_MAX);
+        if (wide && opt.precision == FNN_PREC_AUTO)
+            return false;
+        if (wide || opt.proj > 0)
+            return dense_sampled(T->n, T->npacks, 0.0, true, gone);
+    }
     const double kept = (1.0 - gone) * T->npacks * (nq / 40.0 + 1.0);
     return gone * pairs * gram_pair_ms(M, T->dp, E.lo) <=
            QUERY_TREE_MS + TRAV_MS + TRAV_POINT_MS * (double)nq + TRAV_PAIR_MS * kept;

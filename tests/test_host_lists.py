@@ -16,10 +16,15 @@ using namespace fnn;
 extern "C" {
 long long entries(long long np) { return dense_entries(np); }
 int fits(long long np) { return dense_fits(np); }
-int rule(long long n, double c) { return dense_rule(n, c); }
+int rule(long long n, double c) { return dense_rule(n, n / 40 + 1, c, false); }
 int sampled(long long n, long long np, double c, double gone)
 {
-    return dense_sampled(n, np, c, gone);
+    return dense_sampled(n, np, c, false, gone);
+}
+int wide_rule(long long n, long long np, double c) { return dense_rule(n, np, c, true); }
+int wide_sampled(long long n, long long np, double c, double gone)
+{
+    return dense_sampled(n, np, c, true, gone);
 }
 }
 """
@@ -36,8 +41,9 @@ def lists(tmp_path_factory):
     L.entries.restype = ctypes.c_longlong
     L.entries.argtypes = L.fits.argtypes = [ctypes.c_longlong]
     L.rule.argtypes = [ctypes.c_longlong, ctypes.c_double]
-    L.sampled.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_double,
-                          ctypes.c_double]
+    L.sampled.argtypes = L.wide_sampled.argtypes = [
+        ctypes.c_longlong, ctypes.c_longlong, ctypes.c_double, ctypes.c_double]
+    L.wide_rule.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_double]
     return L
 
 
@@ -87,3 +93,13 @@ def test_sample_decides_by_what_it_prunes(lists, c):
     take = [lists.sampled(n, np_, c, g / 100) for g in range(101)]
     assert take[0] and not take[100]
     assert take == sorted(take, reverse=True)
+
+
+@pytest.mark.parametrize("c", PRICES)
+def test_wide_margins_take_every_pair_only_where_none_is_prunable(lists, c):
+    for n in (1, 1000, 20_000, 1_000_000):
+        assert lists.wide_rule(n, 255, c) == NO
+        assert lists.wide_rule(n, 256, c) == SAMPLE
+        assert lists.wide_sampled(n, 256, c, 0.01)
+        assert not lists.wide_sampled(n, 256, c, 0.011)
+    assert lists.wide_rule(10_000_000, 200_000, c) == NO
