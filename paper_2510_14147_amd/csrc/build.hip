@@ -2132,8 +2132,11 @@ struct QtChunk {
     uint64_t open;  // lanes whose child opens a new pack
     uint64_t kid;   // lanes whose child is a query-tree kid (non-leaf or open)
 };
-// (a step per pack, found on the chunk's running sizes; a step per child is
-// 64 dependent scalar steps)
+// A step per pack of several children, found on the chunk's running sizes, and
+// per run of children that open a pack each because none fits with the next
+// (a step per child is 64 dependent scalar steps; a step per pack where every
+// child opens one, as the roots of a batch of small clouds do, took 3 times
+// as long: 4000 clouds of 40 points, whole build 0.81 ms by child, 1.28 by pack, 0.25 so; 40000 of 20: 5.7, 11.6, 1.1).
 __device__ __forceinline__ QtChunk qt_walk(int cnt, bool leaf, int sz, int P, int &run)
 {
     const int lane = threadIdx.x & (WAVE - 1);
@@ -2146,6 +2149,11 @@ __device__ __forceinline__ QtChunk qt_walk(int cnt, bool leaf, int sz, int P, in
         if (lane >= o)
             pre += y;
     }
+    // leaves that fit in one pack with the leaf after them (the next chunk's
+    // first is not known here: it sees this chunk's last run)
+    const int next = __shfl_down(pre, 1, WAVE) - pre;
+    const uint64_t fits =
+        leafm & (leafm >> 1) & __ballot(lane < WAVE - 1 && leaf && sz + next <= P);
     uint64_t open = 0;
     for (int j = 0; j < cnt;) {
         const uint64_t from = ~0ull << j;
@@ -2159,6 +2167,15 @@ __device__ __forceinline__ QtChunk qt_walk(int cnt, bool leaf, int sz, int P, in
         // lanes that cannot follow in the run's pack, or end it
         uint64_t m = (__ballot(run < 0 || run + (pre - ex) > P) | ~leafm) & from;
         if (m & (1ull << j)) {  // the child itself opens a pack
+            // and so does every one up to a leaf that fits with its next
+            const uint64_t stop = (fits | ~leafm) & from;
+            const int k = stop ? min(cnt, __ffsll((unsigned long long)stop) - 1) : cnt;
+            if (k > j) {
+                open |= from & (k < WAVE ? ~(~0ull << k) : ~0ull);
+                run = __builtin_amdgcn_readlane(sz, k - 1);
+                j = k;
+                continue;
+            }
             open |= 1ull << j;
             run = 0;
             m = (__ballot(pre - ex > P) | ~leafm) & (from << 1);
