@@ -2135,8 +2135,9 @@ struct QtChunk {
 // A step per pack of several children, found on the chunk's running sizes, and
 // per run of children that open a pack each because none fits with the next
 // (a step per child is 64 dependent scalar steps; a step per pack where every
-// child opens one, as the roots of a batch of small clouds do, took 3 times
-// as long: 4000 clouds of 40 points, whole build 0.81 ms by child, 1.28 by pack, 0.25 so; 40000 of 20: 5.7, 11.6, 1.1).
+// child opens one, as the roots of a batch of small clouds do, took longer
+// still: whole build of 4000 clouds of 40 points 0.81 ms by child, 1.28 by
+// pack, 0.25 so; 40000 of 20: 5.7, 11.6, 1.1).
 __device__ __forceinline__ QtChunk qt_walk(int cnt, bool leaf, int sz, int P, int &run)
 {
     const int lane = threadIdx.x & (WAVE - 1);

@@ -209,10 +209,11 @@ inline void fp16_width(int dp, F &&f)
         f(std::integral_constant<int, 8>{});
 }
 
-// Screens the point pairs of a list of pack pairs; those that may be edges
-// go to the survivor list (G.surv, G.nsurv).  Needs rows of at most 128
-// coordinates.
+// Screens the point pairs of a list of pack pairs, or of every step-th of
+// them; those that may be edges go to the survivor list (G.surv, G.nsurv:
+// counted past surv_cap too, until the count exceeds stop).  Needs rows of at
+// most 128 coordinates.
 void screen_tiles(const fnn_tree *T, const Pts &P, const GramArgs &G, const int2 *inter,
-                  long long ninter, hipStream_t s);
+                  long long ninter, int step, unsigned long long stop, hipStream_t s);
 
 }  // namespace fnn

@@ -1286,8 +1286,10 @@ constexpr int SURV_BUF = 256;  // survivors buffered per wave in LDS
 constexpr int BUF_RSRC_W3 = 0x00020000;
 
 // Appends a wave's n buffered survivors to the list: one atomic for their
-// slots, then coalesced stores.  Called with every lane of the wave active.
-__device__ __forceinline__ void surv_flush(const GramArgs &G, const int2 *sb, unsigned n)
+// slots, then coalesced stores.  Returns the list's length before them.
+// Called with every lane of the wave active.
+__device__ __forceinline__ unsigned long long surv_flush(const GramArgs &G, const int2 *sb,
+                                                         unsigned n)
 {
     const int lane = threadIdx.x & (WAVE - 1);
     // LDS writes of other lanes are read below: keep them in order
@@ -1302,6 +1304,7 @@ __device__ __forceinline__ void surv_flush(const GramArgs &G, const int2 *sb, un
             G.surv[q] = sb[i];
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    return b0;
 }
 
 // End of one 32-row x 64-column block of the narrow kernel: rows
@@ -1676,12 +1679,16 @@ k_gram_direct(Pts P, GramArgs G, TileOut out)
 // their latency; its products take a tenth of the time.  581K x 55, 7.0e9
 // pairs: 30.3 ms of tiles -> 6.1 here + 2.5 deciding 0.5 % of them; 64 clouds
 // x 16, 7.3e9 pairs: 20.9 -> 3.6 + 4.4 (1.0 %).
+//
+// step: every step-th pack pair of the list (a sample).  Where the list of
+// survivors has overflowed the tiles run instead, so a wave that sees it do
+// so past `stop` ends.
 constexpr int SCREEN_BUF = 1024;  // survivors per wave in LDS (256: 4.3 ms for 3.6 at x 16)
 template <int M, int NKS>
 __global__ void __launch_bounds__(256, NKS >= 8 ? 2 : NKS >= 4 ? 3 : 4)  // unspilled
 k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
-              long long ninter, const int32_t *__restrict__ q_cpos,
-              const float *__restrict__ q_rad)
+              long long ninter, int step, unsigned long long stop,
+              const int32_t *__restrict__ q_cpos, const float *__restrict__ q_rad)
 {
     constexpr int KQ = 16 * NKS;
     __shared__ __align__(16) float cen_s[4][KQ];    // the frame's origin
@@ -1695,8 +1702,10 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
     float *cen = cen_s[w], *cterm = cterm_s[w];
     int2 *sb = surv_s[w];
     unsigned fill = 0;
+    bool full = false;  // the same in every lane
     const float omc1 = 1.f - mg.c1;
-    for (long long it = (long long)blockIdx.x * 4 + w; it < ninter; it += (long long)gridDim.x * 4) {
+    for (long long it = ((long long)blockIdx.x * 4 + w) * step; it < ninter && !full;
+         it += (long long)gridDim.x * 4 * step) {
         int A = __builtin_amdgcn_readfirstlane(inter[it].x);
         int B = __builtin_amdgcn_readfirstlane(inter[it].y);
         const bool diag = A == B;
@@ -1740,13 +1749,13 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
             }
             return ss + __shfl_xor(ss, 32, WAVE);
         };
-        for (int ia = 0; ia < na; ia += 64) {
+        for (int ia = 0; ia < na && !full; ia += 64) {
             f16x8 Bf[2][NKS];
             float a2[2];
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
                 a2[cb] = frag(a0 + min(ia + cb * 32 + l32, na - 1), Bf[cb]);
-            for (int jb = diag ? ia : 0; jb < nb; jb += 32) {
+            for (int jb = diag ? ia : 0; jb < nb && !full; jb += 32) {
                 f16x8 Af[NKS];
                 const float n2 = frag(b0 + min(jb + l32, nb - 1), Af);
                 const float b2 = wave_max(n2);
@@ -1820,15 +1829,19 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
                     tot += (unsigned)__popcll(m) << b;
                 }
                 if (fill + tot > (unsigned)SCREEN_BUF) {
-                    surv_flush(G, sb, fill);
+                    full = surv_flush(G, sb, fill) + fill > stop;
                     fill = 0;
+                    if (full)
+                        break;
                 }
                 unsigned long long o = 0;  // slots in the list, if not in sb
                 const bool direct = tot > (unsigned)SCREEN_BUF;
                 if (direct) {
                     if (lane == 0)
                         o = atomicAdd(G.nsurv, (unsigned long long)tot);
-                    o = uniform_u64(o) + pre;
+                    o = uniform_u64(o);
+                    full = o + tot > stop;
+                    o += pre;
                 }
                 unsigned f = fill + pre;
                 while (todo) {
@@ -1855,7 +1868,7 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
 }
 
 void screen_tiles(const fnn_tree *T, const Pts &P, const GramArgs &G, const int2 *inter,
-                  long long ninter, hipStream_t s)
+                  long long ninter, int step, unsigned long long stop, hipStream_t s)
 {
     if (ninter <= 0)
         return;
@@ -1863,14 +1876,14 @@ void screen_tiles(const fnn_tree *T, const Pts &P, const GramArgs &G, const int2
     fp16_width(P.dp, [&](auto w) { kq = 16 * decltype(w)::value; });
     const Fp16Margin mg = fp16_margin(kq, P.dp, P.dim);
     // resident work-groups, a few rounds of each
-    const dim3 g(grid_cap(ninter, 4, 16 * num_cus()));
+    const dim3 g(grid_cap(cdiv(ninter, step), 4, 16 * num_cus()));
     fp16_width(P.dp, [&](auto w) {
         if (P.metric == M_ANG)
             FNN_LAUNCH((k_tile_screen<M_ANG, decltype(w)::value>), g, dim3(256), 0, s, P, G, mg,
-                       inter, ninter, T->q_center_pos, T->q_radius);
+                       inter, ninter, step, stop, T->q_center_pos, T->q_radius);
         else
             FNN_LAUNCH((k_tile_screen<M_L2, decltype(w)::value>), g, dim3(256), 0, s, P, G, mg,
-                       inter, ninter, T->q_center_pos, T->q_radius);
+                       inter, ninter, step, stop, T->q_center_pos, T->q_radius);
     });
 }
 
