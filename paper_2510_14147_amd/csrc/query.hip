@@ -1278,6 +1278,92 @@ k_sort_wave(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ lis
     }
 }
 
+// Listed rows of lo+1 .. 1024 NW entries (list entries below 0: none): one
+// work-group of NW waves per row, padded to N = 1024 NW.  Entry g = 1024 w +
+// 64 v + lane lives in register v of that lane of wave w: bitonic stages with
+// strides below 64 exchange across lanes, strides up to 512 swap registers,
+// and only the stages with strides of 1024 and more go through LDS.
+template <int NW, bool PK>
+__global__ void __launch_bounds__(NW * WAVE)
+k_sort_blk(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list,
+           int nl, int lo, int32_t *__restrict__ col, float *__restrict__ dist,
+           const unsigned long long *__restrict__ pk)
+{
+    constexpr int V = 16, N = NW * V * WAVE;
+    __shared__ unsigned long long s[N];
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    const int g0 = w * V * WAVE + lane;  // entry of register 0
+    for (int li = blockIdx.x; li < nl; li += gridDim.x) {
+        const int r = list[li];
+        if (r < 0)
+            continue;
+        const int64_t b = row_ptr[r];
+        const int64_t len64 = row_ptr[r + 1] - b;
+        if (len64 <= lo || len64 > N)
+            continue;  // another kernel's (the same for the whole work-group)
+        const int len = (int)len64;
+        unsigned long long x[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const int g = g0 + v * WAVE;
+            x[v] = g >= len ? ~0ull
+                   : PK     ? pk[b + g]
+                            : pack_entry(col[b + g], dist[b + g]);
+        }
+#pragma unroll
+        for (int k = 2; k <= N; k <<= 1) {
+#pragma unroll
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                if (j >= V * WAVE) {
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+                        s[g0 + v * WAVE] = x[v];
+                    __syncthreads();
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const int g = g0 + v * WAVE;
+                        const unsigned long long o = s[g ^ j];
+                        const bool up = (g & k) == 0, lower = (g & j) == 0;
+                        x[v] = (lower == up) ? (o < x[v] ? o : x[v]) : (o > x[v] ? o : x[v]);
+                    }
+                    __syncthreads();  // s is written again by the next such stage
+                } else if (j >= WAVE) {
+                    const int jv = j / WAVE;
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        if (v & jv)
+                            continue;
+                        const bool up = ((g0 + v * WAVE) & k) == 0;
+                        const unsigned long long a = x[v], c = x[v | jv];
+                        if ((a > c) == up) {
+                            x[v] = c;
+                            x[v | jv] = a;
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const unsigned long long o = __shfl_xor(x[v], j, WAVE);
+                        const bool up = ((g0 + v * WAVE) & k) == 0;
+                        const bool lower = (lane & j) == 0;
+                        x[v] = (lower == up) ? (o < x[v] ? o : x[v]) : (o > x[v] ? o : x[v]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const int g = g0 + v * WAVE;
+            if (g < len) {
+                col[b + g] = (int32_t)(x[v] >> 32);
+                dist[b + g] = __uint_as_float((uint32_t)x[v]);
+            }
+        }
+    }
+}
+
+constexpr int SORT_BLK_MAX = 16 * 16 * WAVE;  // longest row k_sort_blk<16> sorts
+
 // Longer listed rows, by counting: a row's columns are distinct, so a bit per
 // column of its span in LDS and the number of bits below give every entry's
 // place.  One work-group per row; WORDS 32-bit words of span at a time, with
@@ -1288,13 +1374,49 @@ k_sort_wave(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ lis
 // What bounds it: the LDS accesses, linear in the row and its span.  581K
 // rows, 6400 of 4097..16384 entries and 9 longer: 6.5 ms by bitonic sorts of
 // whole work-groups -> 0.8 ms.
+//
+// left: the rows that k_sort_far found too wide, sorted by k_sort_blk (-1:
+// sorted here; null: all are).
 constexpr int SB_V = 8, SB_LONG = 1024;  // entries held per thread; threads of long rows
+constexpr int SB_WIDE = 32768;           // words of a wide window (2^20 columns)
+
+// Listed rows whose columns lie too far apart to be counted, by the span of
+// 64 of their entries: left[i] = the row, else -1.  In windows of 2^20
+// columns, 40K rows of 2100 entries take 1.8, 2.5, 4.8 and 9.5 ms at 1, 2, 5
+// and 10 windows against 4.6 by k_sort_blk; of 4000 2.1, 2.8, 5.3 and 10.4
+// against 4.4; of 8000 3.6, 4.0, 6.7 and 13.0 against 24; 32K of 16000 12.7,
+// 9.7, 14.4 and 25.4 against 19.5.  Longer rows (40K of 40K entries: 44 to 76
+// ms, 1.1 s by a bitonic sort in memory) are always counted.
+__device__ __forceinline__ int bits_words(int64_t len)  // widest counted span
+{
+    return len <= 4096           ? SB_WIDE / 2 * 7
+           : len <= 8192         ? SB_WIDE * 16
+           : len <= SORT_BLK_MAX ? SB_WIDE * 6
+                                 : INT_MAX;
+}
+__global__ void __launch_bounds__(256)
+k_sort_far(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list, int nl,
+           const int32_t *__restrict__ col, const unsigned long long *__restrict__ pk,
+           int32_t *__restrict__ left)
+{
+    const int lane = threadIdx.x & (WAVE - 1), wpb = blockDim.x / WAVE;
+    for (int li = blockIdx.x * wpb + threadIdx.x / WAVE; li < nl; li += gridDim.x * wpb) {
+        const int r = list[li];
+        const int64_t b = row_ptr[r], len = row_ptr[r + 1] - b;
+        const int64_t i = b + (int64_t)lane * len / WAVE;
+        const int c = pk ? (int)(pk[i] >> 32) : col[i];
+        const int lo = -wave_max(-c), hi = wave_max(c);
+        if (lane == 0)
+            left[li] = (hi >> 5) - (lo >> 5) > bits_words(len) ? r : -1;
+    }
+}
+
 template <int WORDS, int SB_T>
 __global__ void __launch_bounds__(SB_T)
 k_sort_bits(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list, int nl,
             int32_t *__restrict__ col, float *__restrict__ dist,
             const unsigned long long *__restrict__ pk, const int64_t *__restrict__ soff,
-            unsigned long long *__restrict__ scr)
+            unsigned long long *__restrict__ scr, const int32_t *__restrict__ left)
 {
     static_assert(WORDS % 8 == 0, "counts of eight words");
     __shared__ uint32_t bits[WORDS];
@@ -1303,6 +1425,8 @@ k_sort_bits(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ lis
     __shared__ int lo_s, hi_s;
     const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
     for (int li = blockIdx.x; li < nl; li += gridDim.x) {
+        if (left && left[li] >= 0)
+            continue;
         const int r = list[li];
         const int64_t b = row_ptr[r], len = row_ptr[r + 1] - b;
         const bool reg = len <= SB_V * SB_T;
@@ -1946,7 +2070,8 @@ __global__ void k_pair_bound(const int2 *__restrict__ inter, long long ni,
 
 // Sorts every CSR row by column (entries are (column, distance) pairs, a
 // row's columns within span of each other): rows of up to 512 entries by one
-// wave in registers, longer ones by a work-group's count, those of up to
+// wave in registers, longer ones by a work-group's count (or, spread over
+// many millions of columns, in a work-group's registers), those of up to
 // SORT_WAVE_MAX only where the span is narrow (four work-groups per CU then;
 // 64 clouds x 16, 76K such rows: 2.6 -> 0.6 ms; at a span of 1M the count clears and
 // sums 31K words for every row, more than the register sort takes).  pk: the entries packed as
@@ -1985,7 +2110,7 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, fl
             if (span <= SPAN_NARROW) {
                 FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, 256>),
                            dim3(grid_cap(hcc[0], 1, 16 * num_cus())), dim3(256), 0, s, row_ptr,
-                           mid, hcc[0], col, dist, pk, nullptr, nullptr);
+                           mid, hcc[0], col, dist, pk, nullptr, nullptr, nullptr);
             } else {
                 auto wave = [&](auto v, auto n32) {
                     FNN_LAUNCH((k_sort_wave<decltype(v)::value, decltype(n32)::value>),
@@ -2016,10 +2141,30 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, fl
             const dim3 g(grid_cap(hcc[1], 1, 8 * num_cus()));
             if (span <= SPAN_NARROW)
                 FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, SB_LONG>), g, dim3(SB_LONG), 0, s,
-                           row_ptr, lng, hcc[1], col, dist, pk, soff, scr);
-            else
-                FNN_LAUNCH((k_sort_bits<32768, SB_LONG>), g, dim3(SB_LONG), 0, s, row_ptr, lng,
-                           hcc[1], col, dist, pk, soff, scr);
+                           row_ptr, lng, hcc[1], col, dist, pk, soff, scr, nullptr);
+            else {
+                // (a span of three windows: none is too wide)
+                int32_t *left = nullptr;
+                if (span > 3ll * 32 * SB_WIDE) {
+                    left = S.get<int32_t>(hcc[1]);
+                    FNN_LAUNCH(k_sort_far, dim3(grid_cap(hcc[1], 4, 8192)), dim3(256), 0, s,
+                               row_ptr, lng, hcc[1], col, pk, left);
+                }
+                FNN_LAUNCH((k_sort_bits<SB_WIDE, SB_LONG>), g, dim3(SB_LONG), 0, s, row_ptr,
+                           lng, hcc[1], col, dist, pk, soff, scr, left);
+                auto blk = [&](auto packed) {
+                    constexpr bool PK = decltype(packed)::value;
+                    const dim3 gb(grid_cap(hcc[1], 1, 4096));
+                    FNN_LAUNCH((k_sort_blk<4, PK>), gb, dim3(4 * WAVE), 0, s, row_ptr, left,
+                               hcc[1], 32 * WAVE, col, dist, pk);
+                    FNN_LAUNCH((k_sort_blk<16, PK>), gb, dim3(16 * WAVE), 0, s, row_ptr, left,
+                               hcc[1], 64 * WAVE, col, dist, pk);
+                };
+                if (left && pk)
+                    blk(std::true_type{});
+                else if (left)
+                    blk(std::false_type{});
+            }
         }
     }
 }
