@@ -109,6 +109,13 @@ void survivors_launch(int metric, const Pts &P, const GramArgs &G,
 // listed in both directions, each entry written into its first id's row.
 void edges_scatter(const int2 *edges, const float *edist, long long ne, bool both,
                    const TileOut &o, hipStream_t s);
+// Survivors of the exact filter (Hamming codes: edges already) as they are,
+// for the device that cannot hold a second list of them: per-row degrees and
+// their count in out.cnt, then the CSR by cursors with the distances computed
+// again.
+void ham_degrees(const GramArgs &G, long long ns, const TileOut &o, hipStream_t s);
+void ham_scatter(const Pts &P, const GramArgs &G, long long ns, const TileOut &o,
+                 hipStream_t s);
 // Decided survivors into the CSR without cursors: edge i goes to slots
 // row_ptr[a] + ranks[i].x of row a and (both) row_ptr[b] + ranks[i].y of row
 // b, the ranks its degree counters returned (each in [0, degree), so the

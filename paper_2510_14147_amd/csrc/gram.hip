@@ -2467,6 +2467,72 @@ void edges_scatter(const int2 *edges, const float *edist, long long ne, bool bot
                edist, ne, both, o);
 }
 
+// The rows of a Hamming survivor: input ids (x: -1 for an unused slot), the
+// query's row first where only it exists (row0).
+__device__ __forceinline__ int2 ham_rows(const GramArgs &G, long long i)
+{
+    const int2 e = G.surv[i];
+    if (e.x < 0)
+        return make_int2(-1, -1);
+    const int a = G.perm[e.x], b = G.perm[e.y & 0x7FFFFFFF];
+    return G.row0 >= 0 ? make_int2(max(a, b) - G.row0, min(a, b)) : make_int2(a, b);
+}
+
+__global__ void k_ham_degrees(GramArgs G, long long ns, TileOut out)
+{
+    unsigned long long c = 0;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < ns;
+         i += (long long)gridDim.x * blockDim.x) {
+        const int2 r = ham_rows(G, i);
+        if (r.x < 0)
+            continue;
+        ++c;
+        atomicAdd(&out.deg[r.x], 1);
+        if (G.row0 < 0)
+            atomicAdd(&out.deg[r.y], 1);
+    }
+    c = wave_sum(c);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && c)
+        atomicAdd(&out.cnt[3], c);
+}
+
+__global__ void k_ham_scatter(Pts P, GramArgs G, long long ns, TileOut out)
+{
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < ns;
+         i += (long long)gridDim.x * blockDim.x) {
+        const int2 r = ham_rows(G, i);
+        const unsigned long long s1 = claim_run(out.cursor, r.x);
+        if (r.x < 0)
+            continue;
+        const int2 e = G.surv[i];
+        const float d = key32<M_HAM>(P, e.x, e.y & 0x7FFFFFFF);
+        const unsigned long long s2 = G.row0 < 0 ? atomicAdd(&out.cursor[r.y], 1ull) : s1;
+        if (s1 < out.nnz && s2 < out.nnz) {
+            if (G.row0 < 0) {
+                out.col[s2] = r.x;
+                out.dist[s2] = d;
+            }
+            out.col[s1] = r.y;
+            out.dist[s1] = d;
+        } else {
+            atomicOr(out.err, ERR_INDEX);
+        }
+    }
+}
+
+void ham_degrees(const GramArgs &G, long long ns, const TileOut &o, hipStream_t s)
+{
+    if (ns > 0)
+        FNN_LAUNCH(k_ham_degrees, dim3(grid_cap(ns, 256, 4096)), dim3(256), 0, s, G, ns, o);
+}
+
+void ham_scatter(const Pts &P, const GramArgs &G, long long ns, const TileOut &o,
+                 hipStream_t s)
+{
+    if (ns > 0)
+        FNN_LAUNCH(k_ham_scatter, dim3(grid_cap(ns, 256, 4096)), dim3(256), 0, s, P, G, ns, o);
+}
+
 template <int M, int PREC, int NKS>
 static void launch_gram_k(bool fill_pass, const Pts &P, const GramArgs &G,
                           const TileOut &o, hipStream_t s)

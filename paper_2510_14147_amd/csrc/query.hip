@@ -2291,7 +2291,8 @@ static float prune_eps(int metric, double eps, const Thr &E)
 template <int M>
 static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                            const Options &opt, fnn_csr *C, fnn_stats &st,
-                           Scratch &S, float **trace_feat, float **trace_targ)
+                           Scratch &S, float **trace_feat, float **trace_targ,
+                           bool lean = false)
 {
     fnn_tree *T = const_cast<fnn_tree *>(Tc);  // lazily built caches only
     if (T->cross_a >= 0 && (opt.sched == FNN_SCHED_LEARNED || opt.trace))
@@ -2479,8 +2480,13 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         float *gedist = nullptr;
         long long ngedges = 0;
         // survivors decided exactly; slot per survivor: holes where it is no
-        // edge
+        // edge.  (lean: the exact filter's survivors are taken as they are)
         auto decide = [&](long long got) {
+            ngedges = got;
+            if (lean) {
+                ham_degrees(G, got, o, s);
+                return;
+            }
             // with no plain tiles in the query every CSR entry
             // comes from a survivor: keep the ranks its degree
             // counters return and place it without cursors
@@ -2498,7 +2504,6 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                 G.erank = S.get<int2>(got + 1);
             // slot per survivor: holes where it is no edge
             survivors_launch(M, P, G, got, gedges, gedist, o, s);
-            ngedges = got;
         };
         if (use_gram) {
             unsigned long long *ns = S.get<unsigned long long>(2);
@@ -2677,7 +2682,9 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
             FNN_LAUNCH(k_cursor_init, dim3(grid_for(nr, 256)), dim3(256), 0, s,
                        C->row_ptr, nr, o.cursor);
             if (nnz > 0) {
-                if (gedges)
+                if (lean)
+                    ham_scatter(P, G, ngedges, o, s);
+                else if (gedges)
                     edges_scatter(gedges, gedist, ngedges, !rect, o, s);
                 if (listed)
                     edges_scatter(o.elist, o.edist, nlisted, false, o, s);
@@ -2878,8 +2885,31 @@ bool eps_graph(const fnn_tree *T, const double *eps, const Options &opt,
         return eps_graph_impl<M_L2>(T, eps, opt, C, st, S, tf, tt);
     case M_ANG:
         return eps_graph_impl<M_ANG>(T, eps, opt, C, st, S, tf, tt);
-    case M_HAM:
-        return eps_graph_impl<M_HAM>(T, eps, opt, C, st, S, tf, tt);
+    case M_HAM: {
+        // The exact filter's survivors are decided into a list of their own,
+        // with ranks and packed words (20 to 36 more bytes each) for the
+        // placement.  Where the device cannot hold these the call runs again
+        // with the survivors alone, 8 bytes each, and row cursors.
+        const fnn_stats st0 = st;
+        try {
+            Scratch A(S.stream());
+            return eps_graph_impl<M_HAM>(T, eps, opt, C, st, A, tf, tt);
+        } catch (const Error &e) {
+            if (e.code != FNN_ENOMEM || opt.validate || T->dp > 4 ||
+                (opt.precision != FNN_PREC_I8 && opt.precision != FNN_PREC_AUTO))
+                throw;
+        }
+        for (void *p : {(void *)C->row_ptr, (void *)C->col, (void *)C->dist, (void *)*tf,
+                        (void *)*tt})
+            if (p)
+                out_free(p);
+        C->row_ptr = nullptr;
+        C->col = nullptr;
+        C->dist = nullptr;
+        *tf = *tt = nullptr;
+        st = st0;
+        return eps_graph_impl<M_HAM>(T, eps, opt, C, st, S, tf, tt, true);
+    }
     default:
         return eps_graph_impl<M_LEV>(T, eps, opt, C, st, S, tf, tt);
     }
