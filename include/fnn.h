@@ -162,12 +162,17 @@ typedef struct fnn_stats {
     int64_t packs;            /* query tile blocks                           */
     int64_t rounds;           /* build levels processed                      */
     int64_t netsel_passes;    /* net-selection passes over all hubs          */
-    int64_t build_dist_evals; /* metric evaluations in the build             */
+    int64_t build_dist_evals; /* metric evaluations in the build (not the    */
+                              /* pairs that an FP16 screen, for rows of 16   */
+                              /* to 128 floats, or the triangle inequality,  */
+                              /* for strings, decides without one)           */
     int64_t traverse_tests;   /* node-pair tests in the traversal            */
     int64_t interactions;     /* block pairs sent to leaf tiles              */
-    int64_t tile_pairs;       /* point pairs evaluated in leaf tiles (once   */
-                              /* per unordered pair, per pass)               */
-    int64_t filter_pairs;     /* pairs screened by the MFMA filter           */
+    int64_t tile_pairs;       /* point pairs evaluated in leaf tiles or as   */
+                              /* survivors (once per unordered pair, per     */
+                              /* pass)                                       */
+    int64_t filter_pairs;     /* pairs screened by the MFMA filter, or by    */
+                              /* that of long lists of plain tiles           */
     int64_t filter_survivors; /* pairs the filter passed to FP32             */
     int64_t fp64_rechecks;    /* borderline pairs decided in FP64            */
     int64_t edges;            /* nnz (ordered pairs)                          */

@@ -524,10 +524,19 @@ __device__ __forceinline__ unsigned long long *count_slot(unsigned long long *cn
 {
     return cnt + (size_t)(i % CNT_SLOTS) * CNT_LINE;
 }
+// Updates that do not compute every distance count theirs per wave of the
+// launch (launches follow one another, so each adds to its own word): with the
+// slots above, 0.4 us of a pass over 9078 chunks.
+constexpr int EVAL_GRID = 4096, EVAL_WAVES = 8 * EVAL_GRID;
 __global__ void __launch_bounds__(CNT_SLOTS)
-k_count_sum(const unsigned long long *__restrict__ cnt, unsigned long long *__restrict__ out)
+k_count_sum(const unsigned long long *__restrict__ cnt,
+            const unsigned long long *__restrict__ evs, int nev,
+            unsigned long long *__restrict__ out)
 {
     unsigned long long a = cnt[threadIdx.x * CNT_LINE], b = cnt[threadIdx.x * CNT_LINE + 1];
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nev; i += CNT_SLOTS)
+        a += evs[i];
     a = wave_sum(a);
     b = wave_sum(b);
     if ((threadIdx.x & (WAVE - 1)) == 0) {
@@ -804,14 +813,14 @@ __device__ __forceinline__ float mx_key(const float *__restrict__ a,
 }
 
 template <int M, int NKS>
-__global__ void __launch_bounds__(CH *UPD_W, NKS >= 4 ? 3 : 4)  // unspilled
+__global__ void __launch_bounds__(CH *UPD_W, NKS >= 4 ? 3 : 4)  // (next to) unspilled
 k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
             const int32_t *__restrict__ ch_e, int NC, const int32_t *__restrict__ live,
             int32_t *__restrict__ live_next, Hubs hb,
             const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
             float *__restrict__ D, int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
             unsigned long long *__restrict__ cand, int kmax,
-            unsigned long long *__restrict__ cnt, MxArgs A)
+            unsigned long long *__restrict__ cnt, unsigned long long *__restrict__ evs, MxArgs A)
 {
     constexpr int KQ = 16 * NKS;
     __shared__ __align__(16) float cterm_s[UPD_W][CH];  // -(1 - c1) |b|^2 / 2; -FLT_MAX: none
@@ -824,6 +833,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
     if (blockIdx.x == 0 && threadIdx.x == 0)
         *live_next = 0;  // set by this pass's selection
     const float omc1 = 1.f - A.m.c1;
+    unsigned evals = 0;  // keys computed (the same in every lane)
     // no wave waits for another: a new centre is a point of the hub, so its
     // FP16 row is read from the level's copy like the points' own
     for (int t = blockIdx.x * UPD_W + w; t < nq; t += gridDim.x * UPD_W) {
@@ -912,7 +922,8 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                 }
                 float bk[2] = {FLT_MAX, FLT_MAX};
                 int bj[2] = {INT_MAX, INT_MAX};
-                while (__ballot(mask != 0u)) {
+                while (const uint64_t left = __ballot(mask != 0u)) {
+                    evals = __builtin_amdgcn_readfirstlane(evals + (unsigned)__popcll(left));
                     const bool on = mask != 0u;
                     const int bit = on ? __ffs(mask) - 1 : 0;
                     mask &= mask - 1u;
@@ -967,6 +978,8 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
         }
         report_chunk(c, NC, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cand);
     }
+    if (lane == 0 && evals)
+        evs[blockIdx.x * UPD_W + w] += evals;
 }
 
 // k_update for codes of up to 64 NW bits.  A wave owns a chunk: every lane
@@ -1074,6 +1087,7 @@ struct LevPass {
     int32_t *act;   // [n] their positions, from the hub's first on
 };
 constexpr int LEV_W = 8;
+static_assert(std::max(UPD_W, LEV_W) * EVAL_GRID <= EVAL_WAVES, "a count per wave");
 
 __global__ void __launch_bounds__(256)
 k_lev_need(const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ ch_s,
@@ -1103,12 +1117,13 @@ __global__ void __launch_bounds__(CH *LEV_W)
 k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, int NC,
              const int32_t *__restrict__ live, Hubs hb, const int32_t *__restrict__ cent,
              const int32_t *__restrict__ perm, float *__restrict__ D, int32_t *__restrict__ L,
-             LevPass V)
+             unsigned long long *__restrict__ evs, LevPass V)
 {
     __shared__ int sd[LEV_W][CH], sj[LEV_W][CH];
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CH));
     const int lane = threadIdx.x % CH;
     const int nq = *live ? NC : 0;
+    unsigned evals = 0;  // distances computed (the same in every lane)
     for (int c = blockIdx.x; c < nq; c += gridDim.x) {
         const int h = ch_hub[c];
         const int j0 = hb.ma[h], j1 = hb.m[h];
@@ -1131,6 +1146,7 @@ k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, int NC,
             if (!__any(valid && (float)abs(q.m - lc) < dcur))
                 continue;
             const int d = lev_run(q, P.s + (size_t)cj * P.dp, lc);
+            evals += min(CH, na - i0);
             if (d < bd) {
                 bd = d;
                 bj = j;
@@ -1156,6 +1172,8 @@ k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, int NC,
             L[p] = bj;
         }
     }
+    if (lane == 0 && evals)
+        evs[blockIdx.x * LEV_W + w] += evals;
 }
 
 __global__ void __launch_bounds__(256)
@@ -1590,7 +1608,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
     const Thr T = tab->t[hb.lvl[h] - 1 + LOFF];
 
     int nk;
-    unsigned long long tests = 0;
+    unsigned tests = 0;
     if constexpr (PH == SEL_TAKE) {
         nk = sp[h].nk;
         for (int i = threadIdx.x; i < nk; i += SEL_T)
@@ -1666,6 +1684,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
                 bool y = d2 + e < tl * (1.f - 1e-6f);
                 const bool in = j < i && i < nk;
                 if (in && !y && !(d2 - e > th * (1.f + 1e-6f))) {
+                    ++tests;
                     const int a = cid[i], c = cid[j];
                     y = within<M>(P, a, c, key32<M>(P, a, c), T, cnt + 1);
                 }
@@ -1675,8 +1694,6 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
                         (uint32_t)(m >> (32 * hi));
             }
         }
-        if (threadIdx.x == 0)
-            tests = (unsigned long long)nk * (nk - 1) / 2;
     } else {
     // Vector rows of up to SEL_CR candidates are staged in LDS first (rows
     // padded by 4 floats: neighbouring rows start in different banks) and
@@ -1826,7 +1843,8 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
         cent[b + m0 + a] = acc[a];
     tests = wave_sum(tests);
     if ((threadIdx.x & (WAVE - 1)) == 0 && tests)
-        atomicAdd(count_slot(cnt, h * (SEL_T / WAVE) + threadIdx.x / WAVE), tests);
+        atomicAdd(count_slot(cnt, h * (SEL_T / WAVE) + threadIdx.x / WAVE),
+                  (unsigned long long)tests);
     if (threadIdx.x == 0) {
         hb.ma[h] = m0;
         hb.m[h] = m0 + nacc;
@@ -1839,8 +1857,10 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
                 V.nact[h] = 0;
             }
             // the next update compares every point with the new centres
-            atomicAdd(count_slot(cnt, h),
-                      (unsigned long long)nacc * (unsigned)(hb.e[h] - hb.b[h]));
+            // (k_update_mx and k_update_lev count those they compute)
+            if (NKS == 0 && M != M_LEV)
+                atomicAdd(count_slot(cnt, h),
+                          (unsigned long long)nacc * (unsigned)(hb.e[h] - hb.b[h]));
         }
     }
     __syncthreads();
@@ -2518,8 +2538,11 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     const int n = (int)T->n;
     int *err = S.get<int>(1);
     fill(err, 0, 1, st);
-    unsigned long long *cnt = S.get<unsigned long long>(CNT_SLOTS * CNT_LINE + 2);
-    fill(cnt, 0ull, CNT_SLOTS * CNT_LINE + 2, st);
+    constexpr int NCNT = CNT_SLOTS * CNT_LINE + 2;
+    unsigned long long *cnt = S.get<unsigned long long>(NCNT + EVAL_WAVES);
+    fill(cnt, 0ull, NCNT + EVAL_WAVES, st);
+    unsigned long long *evs = cnt + NCNT;
+    int nev = 0;  // words of it in use
 
     hipEvent_t ev0, ev1;
     FNN_HIP(hipEventCreate(&ev0));
@@ -2677,7 +2700,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
         // so passes can run ahead of the host: G passes are recorded into a
         // graph once per level and replayed until no hub does.
         fill(live_d, 1, 1, st);
-        const unsigned gu = grid_cap(NC, UPD_W, 4096);
+        const unsigned gu = grid_cap(NC, UPD_W, EVAL_GRID);
         const size_t upd_lds =
             (M == M_L2 || M == M_ANG) && T->dp <= UPD_D ? sizeof(float) * UPD_K * (T->dp + 4)
                                                         : 16;
@@ -2699,8 +2722,10 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                 const dim3 gw(grid_cap(NC, 4, 4096));
                 FNN_LAUNCH(k_lev_need, gw, dim3(256), 0, s, ch_hub, ch_s, ch_e, NC, lc, hubs, D,
                            lev);
-                launch_update_lev(dim3(grid_cap(NC, 1, 4096)), s, P, ch_hub, NC, lc, hubs, cent,
-                                  perm, D, L, lev);
+                const unsigned gl = grid_cap(NC, 1, EVAL_GRID);
+                nev = std::max(nev, (int)gl * LEV_W);
+                launch_update_lev(dim3(gl), s, P, ch_hub, NC, lc, hubs, cent, perm, D, L, evs,
+                                  lev);
                 FNN_LAUNCH(k_lev_report, gw, dim3(256), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx,
                            hubs, perm, D, tab, cand, T->opt.kmax);
             } else if (M == M_HAM && T->dp <= 8) {
@@ -2720,8 +2745,11 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                     if constexpr (M == M_L2 || M == M_ANG)
                         fp16_width(T->dp, [&](auto kw) {
                             FNN_LAUNCH((k_update_mx<M, decltype(kw)::value>), dim3(gu),
-                                       dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent, perm, D, L, tab, cand, T->opt.kmax, cnt, mx.a);
+                                       dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx,
+                                       hubs, cent, perm, D, L, tab, cand, T->opt.kmax, cnt, evs,
+                                       mx.a);
                         });
+                    nev = std::max(nev, (int)gu * UPD_W);
                 } else {
                     FNN_LAUNCH((k_update<M>), dim3(gu), dim3(CH * UPD_W), upd_lds, s, P,
                                ch_hub, ch_s, ch_e, NC, lc, lx, hubs, cent,
@@ -2945,7 +2973,8 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     FNN_HIP(hipEventRecord(ev1, st));
     unsigned long long hc[2];
     int herr = 0;
-    FNN_LAUNCH(k_count_sum, dim3(1), dim3(CNT_SLOTS), 0, st, cnt, cnt + CNT_SLOTS * CNT_LINE);
+    FNN_LAUNCH(k_count_sum, dim3(1), dim3(CNT_SLOTS), 0, st, cnt, evs, nev,
+               cnt + CNT_SLOTS * CNT_LINE);
     Readback(st).add(hc, cnt + CNT_SLOTS * CNT_LINE, 2).add(&herr, err).wait();
     float ms = 0.f;
     FNN_HIP(hipEventElapsedTime(&ms, ev0, ev1));
