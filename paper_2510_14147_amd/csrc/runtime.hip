@@ -94,6 +94,10 @@ LaunchCount &launch_count()
     return c;
 }
 
+// One recording at a time: the recording stream is shared by the device's
+// threads (a second recording on it fails, and its launches would mix).
+static std::mutex g_rec_mu;
+
 GraphRun::~GraphRun()
 {
     if (capturing)
@@ -101,6 +105,7 @@ GraphRun::~GraphRun()
     if (capturing) {  // an error left the recording open: close and drop it
         hipGraph_t g = nullptr;
         (void)hipStreamEndCapture(cs, &g);
+        g_rec_mu.unlock();
         if (g)
             (void)hipGraphDestroy(g);
     }
@@ -113,7 +118,9 @@ GraphRun::~GraphRun()
 void GraphRun::begin()
 {
     cs = capture_stream();
+    std::unique_lock<std::mutex> lk(g_rec_mu);
     FNN_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+    lk.release();  // held until the recording ends
     capturing = true;
     launch_count().capturing = true;
 }
@@ -122,6 +129,7 @@ void GraphRun::end()
 {
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(cs, &g);
+    g_rec_mu.unlock();
     capturing = false;
     launch_count().capturing = false;
     if (e != hipSuccess || !g)
