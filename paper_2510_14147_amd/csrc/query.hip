@@ -1375,8 +1375,8 @@ constexpr int SORT_BLK_MAX = 16 * 16 * WAVE;  // longest row k_sort_blk<16> sort
 // rows, 6400 of 4097..16384 entries and 9 longer: 6.5 ms by bitonic sorts of
 // whole work-groups -> 0.8 ms.
 //
-// left: the rows that k_sort_far found too wide, sorted by k_sort_blk (-1:
-// sorted here; null: all are).
+// LEFT: the rows that k_sort_far found too wide are k_sort_blk's (left[i] =
+// -1: sorted here).
 constexpr int SB_V = 8, SB_LONG = 1024;  // entries held per thread; threads of long rows
 constexpr int SB_WIDE = 32768;           // words of a wide window (2^20 columns)
 
@@ -1411,7 +1411,7 @@ k_sort_far(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list
     }
 }
 
-template <int WORDS, int SB_T>
+template <int WORDS, int SB_T, bool LEFT>
 __global__ void __launch_bounds__(SB_T)
 k_sort_bits(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ list, int nl,
             int32_t *__restrict__ col, float *__restrict__ dist,
@@ -1425,7 +1425,7 @@ k_sort_bits(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ lis
     __shared__ int lo_s, hi_s;
     const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
     for (int li = blockIdx.x; li < nl; li += gridDim.x) {
-        if (left && left[li] >= 0)
+        if (LEFT && left[li] >= 0)
             continue;
         const int r = list[li];
         const int64_t b = row_ptr[r], len = row_ptr[r + 1] - b;
@@ -2108,7 +2108,7 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, fl
         if (hcc[0] > 0) {
             // (at most SORT_WAVE_MAX entries: held by a work-group of 256)
             if (span <= SPAN_NARROW) {
-                FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, 256>),
+                FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, 256, false>),
                            dim3(grid_cap(hcc[0], 1, 16 * num_cus())), dim3(256), 0, s, row_ptr,
                            mid, hcc[0], col, dist, pk, nullptr, nullptr, nullptr);
             } else {
@@ -2140,7 +2140,7 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, fl
             }
             const dim3 g(grid_cap(hcc[1], 1, 8 * num_cus()));
             if (span <= SPAN_NARROW)
-                FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, SB_LONG>), g, dim3(SB_LONG), 0, s,
+                FNN_LAUNCH((k_sort_bits<SPAN_NARROW / 32, SB_LONG, false>), g, dim3(SB_LONG), 0, s,
                            row_ptr, lng, hcc[1], col, dist, pk, soff, scr, nullptr);
             else {
                 // (a span of three windows: none is too wide)
@@ -2150,8 +2150,12 @@ void sort_csr_rows(const int64_t *row_ptr, int n, int64_t span, int32_t *col, fl
                     FNN_LAUNCH(k_sort_far, dim3(grid_cap(hcc[1], 4, 8192)), dim3(256), 0, s,
                                row_ptr, lng, hcc[1], col, pk, left);
                 }
-                FNN_LAUNCH((k_sort_bits<SB_WIDE, SB_LONG>), g, dim3(SB_LONG), 0, s, row_ptr,
-                           lng, hcc[1], col, dist, pk, soff, scr, left);
+                if (left)
+                    FNN_LAUNCH((k_sort_bits<SB_WIDE, SB_LONG, true>), g, dim3(SB_LONG), 0, s,
+                               row_ptr, lng, hcc[1], col, dist, pk, soff, scr, left);
+                else
+                    FNN_LAUNCH((k_sort_bits<SB_WIDE, SB_LONG, false>), g, dim3(SB_LONG), 0, s,
+                               row_ptr, lng, hcc[1], col, dist, pk, soff, scr, left);
                 auto blk = [&](auto packed) {
                     constexpr bool PK = decltype(packed)::value;
                     const dim3 gb(grid_cap(hcc[1], 1, 4096));
@@ -2249,7 +2253,7 @@ constexpr double QUERY_TREE_MS = 1.2;
 constexpr unsigned long long SCREEN_MIN = 30000000ull;
 constexpr unsigned long long SCREEN_RATIO = 32;
 constexpr unsigned long long SCREEN_PROBE = 400000000ull;
-constexpr long long SCREEN_SAMPLE = 8192;
+constexpr long long SCREEN_SAMPLE = 2048;
 
 // Device view of a tree's points (tree order).
 static Pts tree_points(const fnn_tree *T)
@@ -2588,8 +2592,8 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                     bound / SCREEN_RATIO, freeb / 16 / sizeof(int2));
                 if (opt.list_cap > 0)
                     cap = opt.list_cap;
-                unsigned long long *ns = S.get<unsigned long long>(1);
-                fill(ns, 0ull, 1, s);
+                unsigned long long *ns = S.get<unsigned long long>(2);  // [1]: the sample's
+                fill(ns, 0ull, 2, s);
                 G.surv = S.get<int2>(cap);
                 G.surv_cap = cap;
                 G.nsurv = ns;
@@ -2606,9 +2610,9 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                 if (bound >= SCREEN_PROBE && step >= 16) {
                     GramArgs probe = G;
                     probe.surv_cap = 0;  // counted only
+                    probe.nsurv = ns + 1;
                     screen_tiles(T, P, probe, plain, nplain, step, ~0ull, s);
-                    got = (long long)((double)read_scalar(ns, s) * step * 0.8);
-                    fill(ns, 0ull, 1, s);
+                    got = (long long)((double)read_scalar(ns + 1, s) * step * 0.8);
                 }
                 if (got <= cap) {
                     screen_tiles(T, P, G, plain, nplain, 1, (unsigned long long)cap, s);
