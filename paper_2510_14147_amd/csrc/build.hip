@@ -503,8 +503,6 @@ __device__ __forceinline__ void upd_lane(const float *__restrict__ X, int o, flo
         }
 }
 
-// The chunk's R farthest uncovered points (dv, id of each lane; dv < 0:
-// covered), farthest first.  Called by a whole wave.
 // Sort key of a chunk candidate: farther first, then the smaller input id
 // (0 = no candidate).
 __device__ __forceinline__ unsigned long long cand_key(float d, int id)
@@ -525,14 +523,19 @@ __device__ __forceinline__ unsigned long long *count_slot(unsigned long long *cn
     return cnt + (size_t)(i % CNT_SLOTS) * CNT_LINE;
 }
 // Updates that do not compute every distance count theirs per wave of the
-// launch (launches follow one another, so each adds to its own word): with the
-// slots above, 0.4 us of a pass over 9078 chunks.
+// launch: with the slots above, 0.4 us of a pass over 9078 chunks.  (An add
+// whose result nobody reads: the wave does not wait for its word.)
 constexpr int EVAL_GRID = 4096, EVAL_WAVES = 8 * EVAL_GRID;
-__global__ void __launch_bounds__(CNT_SLOTS)
-k_count_sum(const unsigned long long *__restrict__ cnt,
-            const unsigned long long *__restrict__ evs, int nev,
-            unsigned long long *__restrict__ out)
+constexpr int CNT_WORDS = CNT_SLOTS * CNT_LINE + 2 + EVAL_WAVES;  // slots, sums, waves
+__device__ __forceinline__ unsigned long long *eval_words(unsigned long long *cnt)
 {
+    return cnt + CNT_SLOTS * CNT_LINE + 2;
+}
+__global__ void __launch_bounds__(CNT_SLOTS)
+k_count_sum(unsigned long long *__restrict__ cnt, int nev)
+{
+    unsigned long long *out = cnt + CNT_SLOTS * CNT_LINE;
+    const unsigned long long *evs = eval_words(cnt);
     unsigned long long a = cnt[threadIdx.x * CNT_LINE], b = cnt[threadIdx.x * CNT_LINE + 1];
 #pragma unroll 4
     for (int i = threadIdx.x; i < nev; i += CNT_SLOTS)
@@ -545,6 +548,8 @@ k_count_sum(const unsigned long long *__restrict__ cnt,
     }
 }
 
+// The chunk's R farthest uncovered points (dv, id of each lane; dv < 0:
+// covered), farthest first.  Called by a whole wave.
 __device__ __forceinline__ void report_chunk(int c, int NC, int R, float dv, int id,
                                              unsigned long long *__restrict__ cand)
 {
@@ -578,7 +583,8 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
          int32_t *__restrict__ live_next, Hubs hb,
          const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
          float *__restrict__ D, int32_t *__restrict__ L,
-         const LevelTab *__restrict__ tab, unsigned long long *__restrict__ cand, int kmax, unsigned long long *__restrict__ cnt)
+         const LevelTab *__restrict__ tab, unsigned long long *__restrict__ cand, int kmax,
+         unsigned long long *__restrict__ cnt)
 {
     // staged centres: UPD_K rows of the point stride (sized at launch, so
     // low-dimensional inputs keep many work-groups resident), shared by the
@@ -820,7 +826,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
             const int32_t *__restrict__ cent, const int32_t *__restrict__ perm,
             float *__restrict__ D, int32_t *__restrict__ L, const LevelTab *__restrict__ tab,
             unsigned long long *__restrict__ cand, int kmax,
-            unsigned long long *__restrict__ cnt, unsigned long long *__restrict__ evs, MxArgs A)
+            unsigned long long *__restrict__ cnt, MxArgs A)
 {
     constexpr int KQ = 16 * NKS;
     __shared__ __align__(16) float cterm_s[UPD_W][CH];  // -(1 - c1) |b|^2 / 2; -FLT_MAX: none
@@ -832,8 +838,6 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
     const int nq = *live ? NC : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         *live_next = 0;  // set by this pass's selection
-    const float omc1 = 1.f - A.m.c1;
-    unsigned evals = 0;  // keys computed (the same in every lane)
     // no wave waits for another: a new centre is a point of the hub, so its
     // FP16 row is read from the level's copy like the points' own
     for (int t = blockIdx.x * UPD_W + w; t < nq; t += gridDim.x * UPD_W) {
@@ -870,7 +874,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                     const float n2 = cid >= 0 ? A.nrm[cp] : 0.f;
                     b2 = wave_max(n2);
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                    cterm[lane] = cid >= 0 ? -0.5f * omc1 * n2 : -FLT_MAX;
+                    cterm[lane] = cid >= 0 ? -0.5f * (1.f - A.m.c1) * n2 : -FLT_MAX;
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 }
                 const _Float16 *cr = A.q + (size_t)__shfl(cp, u + l32, WAVE) * KQ + 8 * hi;
@@ -908,7 +912,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                     for (int q = 1; q < 16; ++q)
                         mx = fmaxf(mx, acc[cb][q]);
                     mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-                    const float lo = 0.5f * (omc1 * a2[cb] - D2 - A.m.add) -
+                    const float lo = 0.5f * ((1.f - A.m.c1) * a2[cb] - D2 - A.m.add) -
                                      A.m.keyrel * (mag + D2);
                     if (__ballot(s + pi < e && mx >= lo) == 0ull)
                         continue;  // no point of this block can come nearer
@@ -922,6 +926,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                 }
                 float bk[2] = {FLT_MAX, FLT_MAX};
                 int bj[2] = {INT_MAX, INT_MAX};
+                unsigned evals = 0;  // keys computed
                 while (const uint64_t left = __ballot(mask != 0u)) {
                     evals = __builtin_amdgcn_readfirstlane(evals + (unsigned)__popcll(left));
                     const bool on = mask != 0u;
@@ -941,6 +946,9 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                             }
                     }
                 }
+                if (lane == 0 && evals)
+                    atomicAdd(&eval_words(cnt)[blockIdx.x * UPD_W + w],
+                              (unsigned long long)evals);
                 // the two halves of a column, then column i to lane i
                 float mk = FLT_MAX;
                 int mj = INT_MAX;
@@ -978,8 +986,6 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
         }
         report_chunk(c, NC, cand_per_chunk(hb.ce[h] - hb.cb[h], kmax), dv, id, cand);
     }
-    if (lane == 0 && evals)
-        evs[blockIdx.x * UPD_W + w] += evals;
 }
 
 // k_update for codes of up to 64 NW bits.  A wave owns a chunk: every lane
@@ -1117,7 +1123,7 @@ __global__ void __launch_bounds__(CH *LEV_W)
 k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, int NC,
              const int32_t *__restrict__ live, Hubs hb, const int32_t *__restrict__ cent,
              const int32_t *__restrict__ perm, float *__restrict__ D, int32_t *__restrict__ L,
-             unsigned long long *__restrict__ evs, LevPass V)
+             unsigned long long *__restrict__ cnt, LevPass V)
 {
     __shared__ int sd[LEV_W][CH], sj[LEV_W][CH];
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CH));
@@ -1173,7 +1179,7 @@ k_update_lev(Pts P, const int32_t *__restrict__ ch_hub, int NC,
         }
     }
     if (lane == 0 && evals)
-        evs[blockIdx.x * LEV_W + w] += evals;
+        atomicAdd(&eval_words(cnt)[blockIdx.x * LEV_W + w], (unsigned long long)evals);
 }
 
 __global__ void __launch_bounds__(256)
@@ -2538,11 +2544,9 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     const int n = (int)T->n;
     int *err = S.get<int>(1);
     fill(err, 0, 1, st);
-    constexpr int NCNT = CNT_SLOTS * CNT_LINE + 2;
-    unsigned long long *cnt = S.get<unsigned long long>(NCNT + EVAL_WAVES);
-    fill(cnt, 0ull, NCNT + EVAL_WAVES, st);
-    unsigned long long *evs = cnt + NCNT;
-    int nev = 0;  // words of it in use
+    unsigned long long *cnt = S.get<unsigned long long>(CNT_WORDS);
+    fill(cnt, 0ull, CNT_WORDS, st);
+    int nev = 0;  // waves' words in use
 
     hipEvent_t ev0, ev1;
     FNN_HIP(hipEventCreate(&ev0));
@@ -2724,7 +2728,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                            lev);
                 const unsigned gl = grid_cap(NC, 1, EVAL_GRID);
                 nev = std::max(nev, (int)gl * LEV_W);
-                launch_update_lev(dim3(gl), s, P, ch_hub, NC, lc, hubs, cent, perm, D, L, evs,
+                launch_update_lev(dim3(gl), s, P, ch_hub, NC, lc, hubs, cent, perm, D, L, cnt,
                                   lev);
                 FNN_LAUNCH(k_lev_report, gw, dim3(256), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx,
                            hubs, perm, D, tab, cand, T->opt.kmax);
@@ -2746,7 +2750,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                         fp16_width(T->dp, [&](auto kw) {
                             FNN_LAUNCH((k_update_mx<M, decltype(kw)::value>), dim3(gu),
                                        dim3(CH * UPD_W), 0, s, P, ch_hub, ch_s, ch_e, NC, lc, lx,
-                                       hubs, cent, perm, D, L, tab, cand, T->opt.kmax, cnt, evs,
+                                       hubs, cent, perm, D, L, tab, cand, T->opt.kmax, cnt,
                                        mx.a);
                         });
                     nev = std::max(nev, (int)gu * UPD_W);
@@ -2765,7 +2769,8 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
                 if (sp) {
                     const int K = std::min(T->opt.kmax, MAX_K);
                     const int nt = (int)cdiv(std::max(1, K * (K - 1) / 2), WAVE);
-                    FNN_LAUNCH((k_select<M, SEL_TOP, 0>), gs, dim3(SEL_T), 0, s, P, hubs, H, cent, cand, NC, tab, T->opt.kmax, lx, cnt, sp, mx.a, lev);
+                    FNN_LAUNCH((k_select<M, SEL_TOP, 0>), gs, dim3(SEL_T), 0, s, P, hubs, H,
+                               cent, cand, NC, tab, T->opt.kmax, lx, cnt, sp, mx.a, lev);
                     FNN_LAUNCH(k_conflicts, dim3((unsigned)(H * nt)), dim3(WAVE), 0, s, P,
                                hubs, nt, sp, tab, cnt);
                     FNN_LAUNCH((k_select<M, SEL_TAKE, 0>), gs, dim3(SEL_T), 0, s, P, hubs, H,
@@ -2973,8 +2978,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
     FNN_HIP(hipEventRecord(ev1, st));
     unsigned long long hc[2];
     int herr = 0;
-    FNN_LAUNCH(k_count_sum, dim3(1), dim3(CNT_SLOTS), 0, st, cnt, evs, nev,
-               cnt + CNT_SLOTS * CNT_LINE);
+    FNN_LAUNCH(k_count_sum, dim3(1), dim3(CNT_SLOTS), 0, st, cnt, nev);
     Readback(st).add(hc, cnt + CNT_SLOTS * CNT_LINE, 2).add(&herr, err).wait();
     float ms = 0.f;
     FNN_HIP(hipEventElapsedTime(&ms, ev0, ev1));
