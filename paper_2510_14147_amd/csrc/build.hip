@@ -728,10 +728,6 @@ k_update(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__ 
 // through LDS for eight waves, two barriers a batch, 7.2 and 17.8 ms).  Three
 // waves per SIMD for rows above 32 floats: four spill the point operands and
 // took 8.0 and 20.2 ms.
-typedef __attribute__((ext_vector_type(8))) _Float16 mx_f16x8;
-typedef __attribute__((ext_vector_type(4))) _Float16 mx_f16x4;
-typedef __attribute__((ext_vector_type(16))) float mx_f32x16;
-
 struct MxArgs {
     const _Float16 *q;       // [n][16 NKS], by position
     const float *nrm;        // [n] |.|^2, scaled
@@ -775,8 +771,8 @@ k_mx_rows(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict__
                             v2 = (a.z - b.z) * sc, v3 = (a.w - b.w) * sc;
                 ss = fmaf(v0, v0, fmaf(v1, v1, fmaf(v2, v2, fmaf(v3, v3, ss))));
                 if (in)
-                    *reinterpret_cast<mx_f16x4 *>(q + (size_t)(s + r) * KQ + k) =
-                        (mx_f16x4){(_Float16)v0, (_Float16)v1, (_Float16)v2, (_Float16)v3};
+                    *reinterpret_cast<f16x4 *>(q + (size_t)(s + r) * KQ + k) =
+                        (f16x4){(_Float16)v0, (_Float16)v1, (_Float16)v2, (_Float16)v3};
             }
             ss += __shfl_xor(ss, 1, WAVE);
             ss += __shfl_xor(ss, 2, WAVE);
@@ -853,7 +849,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
         if (j1 > j0) {
             const float sc = fp16_scale(A.radius[hb.node[h]]);
             // this chunk's points: columns 32 cb + l32, k 16 ks + 8 hi ..
-            mx_f16x8 B[2][NKS];
+            f16x8 B[2][NKS];
             float a2[2];
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
@@ -861,7 +857,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                 a2[cb] = A.nrm[pp];
 #pragma unroll
                 for (int ks = 0; ks < NKS; ++ks)
-                    B[cb][ks] = *reinterpret_cast<const mx_f16x8 *>(A.q + (size_t)pp * KQ +
+                    B[cb][ks] = *reinterpret_cast<const f16x8 *>(A.q + (size_t)pp * KQ +
                                                                     16 * ks + 8 * hi);
             }
             int cid = -1, cp = 0;  // lane's of 64 centres: input id, position
@@ -874,11 +870,11 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                     const float n2 = cid >= 0 ? A.nrm[cp] : 0.f;
                     b2 = wave_max(n2);
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                    cterm[lane] = cid >= 0 ? -0.5f * (1.f - A.m.c1) * n2 : -FLT_MAX;
+                    cterm[lane] = cid >= 0 ? screen_term(A.m, n2) : -FLT_MAX;
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 }
                 const _Float16 *cr = A.q + (size_t)__shfl(cp, u + l32, WAVE) * KQ + 8 * hi;
-                mx_f32x16 acc[2];
+                f32x16 acc[2];
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
                     const float4 v =
@@ -893,7 +889,7 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                 }
 #pragma unroll
                 for (int ks = 0; ks < NKS; ++ks) {
-                    const mx_f16x8 a = *reinterpret_cast<const mx_f16x8 *>(cr + 16 * ks);
+                    const f16x8 a = *reinterpret_cast<const f16x8 *>(cr + 16 * ks);
 #pragma unroll
                     for (int cb = 0; cb < 2; ++cb)
                         acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, B[cb][ks], acc[cb],
@@ -912,12 +908,10 @@ k_update_mx(Pts P, const int32_t *__restrict__ ch_hub, const int32_t *__restrict
                     for (int q = 1; q < 16; ++q)
                         mx = fmaxf(mx, acc[cb][q]);
                     mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-                    const float lo = 0.5f * ((1.f - A.m.c1) * a2[cb] - D2 - A.m.add) -
-                                     A.m.keyrel * (mag + D2);
+                    const float lo = screen_floor(A.m, a2[cb], b2, D2);
                     if (__ballot(s + pi < e && mx >= lo) == 0ull)
                         continue;  // no point of this block can come nearer
-                    const float thr =
-                        fmaxf(lo, mx - (A.m.c1 + A.m.keyrel) * mag - A.m.add);
+                    const float thr = fmaxf(lo, screen_rival(A.m, mx, mag));
                     unsigned k = 0;
 #pragma unroll
                     for (int q = 0; q < 16; ++q)
@@ -1673,12 +1667,12 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
                 bj -= ++bi;
             const _Float16 *ra = A.q + (size_t)cpos[32 * bi + l32] * KQ + 8 * hi;
             const _Float16 *rb = A.q + (size_t)cpos[32 * bj + l32] * KQ + 8 * hi;
-            mx_f32x16 acc = {};
+            f32x16 acc = {};
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                    *reinterpret_cast<const mx_f16x8 *>(ra + 16 * ks),
-                    *reinterpret_cast<const mx_f16x8 *>(rb + 16 * ks), acc, 0, 0, 0);
+                    *reinterpret_cast<const f16x8 *>(ra + 16 * ks),
+                    *reinterpret_cast<const f16x8 *>(rb + 16 * ks), acc, 0, 0, 0);
             const int j = 32 * bj + l32;
             const float nj = cnrm[j];
             const float tl = T.lo * s2, th = T.hi * s2;
@@ -1686,7 +1680,7 @@ k_select(Pts P, Hubs hb, int H, int32_t *__restrict__ cent,
             for (int q = 0; q < 16; ++q) {
                 const int i = 32 * bi + 8 * (q >> 2) + 4 * hi + (q & 3);
                 const float mag = cnrm[i] + nj, d2 = mag - 2.f * acc[q];
-                const float e = (A.m.c1 + 2.f * A.m.keyrel) * mag + A.m.add;
+                const float e = screen_slack(A.m, mag);
                 bool y = d2 + e < tl * (1.f - 1e-6f);
                 const bool in = j < i && i < nk;
                 if (in && !y && !(d2 - e > th * (1.f + 1e-6f))) {

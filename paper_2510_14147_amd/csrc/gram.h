@@ -7,6 +7,10 @@
 
 namespace fnn {
 
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
 struct TileOut {
     int32_t *deg;                 // count pass
     unsigned long long *cursor;   // fill pass: next free slot of each row
@@ -199,6 +203,30 @@ inline Fp16Margin fp16_margin(int kq, int dp, int dim)
     m.add = (float)(4.02 * eta * sqrt((double)kq) + 2.0 * kq * eta * eta);
     m.keyrel = (float)((8.0 * (dp + 8) + 64.0) * u32);
     return m;
+}
+
+// Every screen tests through these, in scaled units.  Its accumulators are v =
+// g - (1 - c1) |b|^2 / 2, g the product of the rounded rows (they start at
+// screen_term).
+__device__ __forceinline__ float screen_term(const Fp16Margin &m, float b2)
+{
+    return -0.5f * (1.f - m.c1) * b2;
+}
+// Below it no |a - b|^2 is at most D2 (|b|^2 <= b2), by the FP32 key either.
+__device__ __forceinline__ float screen_floor(const Fp16Margin &m, float a2, float b2, float D2)
+{
+    return 0.5f * ((1.f - m.c1) * a2 - D2 - m.add) - m.keyrel * (a2 + b2 + D2);
+}
+// Below it b is farther from a than the row of the largest v (mag >= |a|^2 +
+// |b|^2 of both).
+__device__ __forceinline__ float screen_rival(const Fp16Margin &m, float vmax, float mag)
+{
+    return vmax - (m.c1 + m.keyrel) * mag - m.add;
+}
+// How far |a|^2 + |b|^2 - 2 g and the FP32 key are from |a - b|^2 together.
+__device__ __forceinline__ float screen_slack(const Fp16Margin &m, float mag)
+{
+    return (m.c1 + 2.f * m.keyrel) * mag + m.add;
 }
 
 // f(NKS) for the narrowest product width 16 NKS that holds dp <= 128

@@ -44,8 +44,6 @@
 namespace fnn {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
 constexpr int UNIT_MAX = 64;     // list entries per work unit (at most)
@@ -910,8 +908,8 @@ __device__ __forceinline__ void pad_surv(const GramArgs &G, unsigned long long c
 // End of one 64-row x 32-column block (column block cb) of a wave's tile:
 // the pairs that pass the filter (all valid pairs with their pass flag when
 // validating) go to the survivor list through the wave's reserved slots
-// [cpos, cend); npairs counts the screened pairs.  mx is the lane's largest accumulator (scaled) and ay
-// its column term.
+// [cpos, cend); npairs counts the screened pairs.  mx is the lane's largest
+// accumulator (scaled) and ay its column term.
 template <int PREC, typename V, typename ACC>
 __device__ __forceinline__ void block_finish(const GramArgs &G, const ACC (&accb)[2], V ay,
                                              V mx, int cb, int na, int nb, bool self,
@@ -1703,7 +1701,6 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
     int2 *sb = surv_s[w];
     unsigned fill = 0;
     bool full = false;  // the same in every lane
-    const float omc1 = 1.f - mg.c1;
     for (long long it = ((long long)blockIdx.x * 4 + w) * step; it < ninter && !full;
          it += (long long)gridDim.x * 4 * step) {
         int A = __builtin_amdgcn_readfirstlane(inter[it].x);
@@ -1761,7 +1758,7 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
                 const float b2 = wave_max(n2);
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 if (hi == 0)
-                    cterm[l32] = jb + l32 < nb ? -0.5f * omc1 * n2 : -FLT_MAX;
+                    cterm[l32] = jb + l32 < nb ? screen_term(mg, n2) : -FLT_MAX;
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 f32x16 acc[2];
 #pragma unroll
@@ -1790,9 +1787,7 @@ k_tile_screen(Pts P, GramArgs G, Fp16Margin mg, const int2 *__restrict__ inter,
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb) {
                     const int ca = ia + cb * 32 + l32;
-                    const float mag = a2[cb] + b2;
-                    const float lo = 0.5f * (omc1 * a2[cb] - D2 - mg.add) -
-                                     mg.keyrel * (mag + D2);
+                    const float lo = screen_floor(mg, a2[cb], b2, D2);
                     float mx = acc[cb][0];
 #pragma unroll
                     for (int q = 1; q < 16; ++q)
