@@ -14,6 +14,8 @@ namespace fnn {
 extern thread_local hipStream_t g_stream;
 void set_alloc_hook(fnn_alloc_fn a, fnn_free_fn f, void *ctx);
 void build_tree(fnn_tree *T, const void *points, Scratch &S);
+// Whether a build of such rows keeps an FP16 copy of them for its updates.
+bool mx_rows(int metric, int dp);
 fnn_tree *forest_pair(const fnn_tree *A, const fnn_tree *B, Scratch &S);
 // False only for a bichromatic rectangle (T->rect) whose automatic precision
 // is none of the filters': nothing was computed.
@@ -202,6 +204,8 @@ static int tree_build_any(const void *points, int64_t n, const int64_t *offsets,
         return set_err(FNN_EINVAL, "out is NULL");
     *out = nullptr;
     fnn_tree *T = nullptr;
+    bool plain = false;  // a second try, without the updates' FP16 copy
+again:
     try {
         if (!points)
             fail(FNN_EINVAL, "points is NULL");
@@ -244,6 +248,7 @@ static int tree_build_any(const void *points, int64_t n, const int64_t *offsets,
         }
         T->ncloud = (int)T->cloud_src.size();
         T->dp = row_stride(metric, dim);
+        T->plain_updates = plain;
         LaunchDelta ld;
         {
             Scratch S(current_stream());
@@ -253,8 +258,12 @@ static int tree_build_any(const void *points, int64_t n, const int64_t *offsets,
         *out = T;
         return FNN_OK;
     } catch (const Error &e) {
+        const bool retry = e.code == FNN_ENOMEM && !plain && T && mx_rows(metric, T->dp);
         delete T;
-        return set_err(e.code, e.msg);
+        T = nullptr;
+        if (!retry)
+            return set_err(e.code, e.msg);
+        plain = true;
     } catch (const std::bad_alloc &) {
         delete T;
         return set_err(FNN_ENOMEM, "host allocation failed");
@@ -262,6 +271,7 @@ static int tree_build_any(const void *points, int64_t n, const int64_t *offsets,
         delete T;
         return set_err(FNN_EINTERNAL, "unexpected exception");
     }
+    goto again;
 }
 
 int fnn_tree_build_ex(const void *points, int64_t n, int32_t dim,

@@ -1487,7 +1487,8 @@ __device__ __forceinline__ size_t cand_at(int q, int nch, int NC)
 // streams its candidates whole.
 constexpr int SEL_SL = 8;                // slices per hub at most
 // (one work-group takes 15.6K candidates in 55 us; slices of 2K and up took
-// 30 us and their own launch before a selection of 45 us)
+// 30 us and their own launch before a selection of 45 us, and of fewer
+// candidates the slices take no less; beyond, they are sliced as before)
 constexpr int SEL_PRE = 16384;
 __device__ __forceinline__ void sel_slices(int ncand, int &nsl, int &len)
 {
@@ -2461,6 +2462,11 @@ Pts ingest_input(fnn_tree *T, const void *points, Scratch &S)
     }
 }
 
+bool mx_rows(int metric, int dp)
+{
+    return (metric == M_L2 || metric == M_ANG) && dp >= 16 && dp <= UPD_D;
+}
+
 // The screened update's copies and launches for rows of 16..128 floats.
 struct MxLevel {
     bool on = false;
@@ -2470,10 +2476,11 @@ struct MxLevel {
     MxArgs a{};
 
     // Rows below 16 floats keep the scan (a product would be mostly padding),
-    // as do sets whose copy does not fit easily.
+    // as do sets whose copy does not fit easily (memory that the caller's
+    // allocator keeps for itself counts as taken).
     void init(const Pts &P, const NodeArrays &nd, Scratch &S)
     {
-        if ((P.metric != M_L2 && P.metric != M_ANG) || P.dp < 16 || P.dp > UPD_D)
+        if (!mx_rows(P.metric, P.dp))
             return;
         int kq = 128;
         fp16_width(P.dp, [&](auto k) { kq = 16 * decltype(k)::value; });
@@ -2665,7 +2672,7 @@ static void build_impl(fnn_tree *T, const void *points, Scratch &S)
 
     MxLevel mx;
     if constexpr (M == M_L2 || M == M_ANG)
-        if (H > 0)
+        if (H > 0 && !T->plain_updates)
             mx.init(P, nd, S);
     int32_t *most = S.get<int32_t>(NLEV + 1);  // largest hub of every round
     fill(most, 0, NLEV + 1, st);

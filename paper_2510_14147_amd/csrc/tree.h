@@ -102,6 +102,9 @@ struct fnn_tree {
     // vertices
     int64_t rect = -1;
 
+    // built without the updates' FP16 copy (it did not fit)
+    bool plain_updates = false;
+
     int depth = 0;
     fnn_stats stats{};
     std::vector<void *> owned;
