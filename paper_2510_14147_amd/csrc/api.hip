@@ -412,7 +412,7 @@ static bool query_all_pairs(const fnn_tree *tree, const void *queries, int64_t n
     if (B)
         free_box(B);
     delete F;
-    return true;
+    return *rc != FNN_ENOMEM;  // the general path may need less
 }
 
 int fnn_eps_query(const fnn_tree *tree, const void *queries, int64_t nq, double eps,

@@ -2295,8 +2295,7 @@ static float prune_eps(int metric, double eps, const Thr &E)
 template <int M>
 static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
                            const Options &opt, fnn_csr *C, fnn_stats &st,
-                           Scratch &S, float **trace_feat, float **trace_targ,
-                           bool lean = false)
+                           Scratch &S, float **trace_feat, float **trace_targ, bool lean)
 {
     fnn_tree *T = const_cast<fnn_tree *>(Tc);  // lazily built caches only
     if (T->cross_a >= 0 && (opt.sched == FNN_SCHED_LEARNED || opt.trace))
@@ -2390,8 +2389,8 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         const double c = gram_pair_ms(M, T->dp, E.lo);
         // Hamming codes: exact.  Vectors: the automatic rule's choice is
         // narrow; a format or a projection that the caller set may not be
-        bool wide = false;
-        if ((M == M_L2 || M == M_ANG) && T->dp <= 128)
+        bool wide = lean;
+        if (!lean && (M == M_L2 || M == M_ANG) && T->dp <= 128)
             wide = opt.proj > 0 ||
                    (opt.precision != FNN_PREC_AUTO &&
                     !(gram_margin_ratio(T, t2min, prec, S, &gpre) <= MARGIN_MAX));
@@ -2485,9 +2484,10 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         long long ngedges = 0;
         // survivors decided exactly; slot per survivor: holes where it is no
         // edge.  (lean: the exact filter's survivors are taken as they are)
+        const bool lean_ham = lean && M == M_HAM && use_gram && !opt.validate;
         auto decide = [&](long long got) {
             ngedges = got;
-            if (lean) {
+            if (lean_ham) {
                 ham_degrees(G, got, o, s);
                 return;
             }
@@ -2585,7 +2585,7 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
         // only the pairs that may be edges computed.  More of them than the
         // list takes: the tiles run instead.
         if constexpr (M == M_L2 || M == M_ANG) {
-            if (!use_gram && T->dp >= 16 && T->dp <= 128 && bound >= SCREEN_MIN) {
+            if (!use_gram && !lean && T->dp >= 16 && T->dp <= 128 && bound >= SCREEN_MIN) {
                 size_t freeb = 0, totb = 0;
                 FNN_HIP(hipMemGetInfo(&freeb, &totb));
                 long long cap = (long long)std::min<unsigned long long>(
@@ -2686,7 +2686,7 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
             FNN_LAUNCH(k_cursor_init, dim3(grid_for(nr, 256)), dim3(256), 0, s,
                        C->row_ptr, nr, o.cursor);
             if (nnz > 0) {
-                if (lean)
+                if (lean_ham)
                     ham_scatter(P, G, ngedges, o, s);
                 else if (gedges)
                     edges_scatter(gedges, gedist, ngedges, !rect, o, s);
@@ -2881,42 +2881,42 @@ static bool eps_graph_impl(const fnn_tree *Tc, const double *epsv,
     return true;
 }
 
+// The faster routes take more memory than those they stand in for: a second
+// list of the exact filter's survivors with ranks and packed words (20 to 36
+// bytes more for an edge between codes), the survivor list of screened tiles,
+// every pair's list in place of the traversal's.  Where the device, or the
+// caller's allocator, cannot hold them the call runs again without (lean).
 bool eps_graph(const fnn_tree *T, const double *eps, const Options &opt,
                fnn_csr *C, fnn_stats &st, Scratch &S, float **tf, float **tt)
 {
-    switch (T->metric) {
-    case M_L2:
-        return eps_graph_impl<M_L2>(T, eps, opt, C, st, S, tf, tt);
-    case M_ANG:
-        return eps_graph_impl<M_ANG>(T, eps, opt, C, st, S, tf, tt);
-    case M_HAM: {
-        // The exact filter's survivors are decided into a list of their own,
-        // with ranks and packed words (20 to 36 more bytes each) for the
-        // placement.  Where the device cannot hold these the call runs again
-        // with the survivors alone, 8 bytes each, and row cursors.
-        const fnn_stats st0 = st;
-        try {
-            Scratch A(S.stream());
-            return eps_graph_impl<M_HAM>(T, eps, opt, C, st, A, tf, tt);
-        } catch (const Error &e) {
-            if (e.code != FNN_ENOMEM || opt.validate || T->dp > 4 ||
-                (opt.precision != FNN_PREC_I8 && opt.precision != FNN_PREC_AUTO))
-                throw;
+    auto run = [&](Scratch &A, bool lean) {
+        switch (T->metric) {
+        case M_L2:
+            return eps_graph_impl<M_L2>(T, eps, opt, C, st, A, tf, tt, lean);
+        case M_ANG:
+            return eps_graph_impl<M_ANG>(T, eps, opt, C, st, A, tf, tt, lean);
+        case M_HAM:
+            return eps_graph_impl<M_HAM>(T, eps, opt, C, st, A, tf, tt, lean);
+        default:
+            return eps_graph_impl<M_LEV>(T, eps, opt, C, st, A, tf, tt, lean);
         }
-        for (void *p : {(void *)C->row_ptr, (void *)C->col, (void *)C->dist, (void *)*tf,
-                        (void *)*tt})
-            if (p)
-                out_free(p);
-        C->row_ptr = nullptr;
-        C->col = nullptr;
-        C->dist = nullptr;
-        *tf = *tt = nullptr;
-        st = st0;
-        return eps_graph_impl<M_HAM>(T, eps, opt, C, st, S, tf, tt, true);
+    };
+    const fnn_stats st0 = st;
+    try {
+        Scratch A(S.stream());
+        return run(A, false);
+    } catch (const Error &e) {
+        if (e.code != FNN_ENOMEM || T->metric == M_LEV)
+            throw;
     }
-    default:
-        return eps_graph_impl<M_LEV>(T, eps, opt, C, st, S, tf, tt);
-    }
+    for (void *p : {(void *)C->row_ptr, (void *)C->col, (void *)C->dist, (void *)*tf, (void *)*tt})
+        out_free(p);
+    C->row_ptr = nullptr;
+    C->col = nullptr;
+    C->dist = nullptr;
+    *tf = *tt = nullptr;
+    st = st0;
+    return run(S, true);
 }
 
 bool query_screens_all(const fnn_tree *T, const void *q, int64_t nq, double eps,
