@@ -61,12 +61,16 @@ enum {
 
 /* Leaf-tile arithmetic of the query. */
 typedef enum {
-    FNN_PREC_FP32 = 0,   /* direct-difference FP32 tiles (the plain path);    */
-                         /* long lists are screened first: same results        */
+    FNN_PREC_FP32 = 0,   /* direct-difference FP32 tiles (the plain path).    */
+                         /* Of long lists (3e7 pairs of 16 to 128 floats) the  */
+                         /* pairs that FP16 products rule out beyond their     */
+                         /* rounding are skipped, and the others computed as   */
+                         /* in a tile: the same result bit for bit             */
     FNN_PREC_BF16 = 1,   /* MFMA BF16 Gram filter, FP32 recompute of survivors */
     FNN_PREC_FP8 = 2,    /* MFMA FP8 (E4M3) Gram filter, FP32 recompute        */
     FNN_PREC_I8 = 3,     /* Hamming codes of <= 256 bits: exact MFMA Gram of   */
-                         /* the bits as +-1 (s.t = K - 2 d over K bits)       */
+                         /* the bits as +-1 (s.t = K - 2 d over K bits; +-1    */
+                         /* in 4-bit floats, sums in FP32, all exact)          */
     FNN_PREC_AUTO = 4,   /* chosen per query: I8 for Hamming codes of <= 256  */
                          /* bits; FP16 for L2 / angular with 16 <= dim <= 128 */
                          /* when the filter's margin is small against eps^2   */
@@ -111,7 +115,9 @@ typedef struct fnn_options {
                           /* over device-resident frontier queues (a level  */
                           /* that may not fit stops them; eager levels      */
                           /* finish).  Default 4, rounded up to even; 1 =   */
-                          /* one eager pass / level per host check          */
+                          /* one eager pass / level per host check.  A      */
+                          /* build level's first passes, and by default the */
+                          /* first traversal levels, run eagerly            */
     int32_t proj;         /* BF16 / FP8 filter on the K leading principal    */
                           /* coordinates (a conservative bound: |Q^T(x-y)|   */
                           /* <= ||Q|| |x-y|): 0 = K the smallest multiple of */
@@ -120,7 +126,9 @@ typedef struct fnn_options {
                           /* -1 = none; 16..128 in steps of 16 = that K;     */
                           /* else EINVAL                                     */
     int32_t list_cap;     /* initial capacity (entries) of the MFMA filter's */
-                          /* survivor list, of the plain tiles' edge list   */
+                          /* survivor list, of that of screened plain tiles */
+                          /* (one that overflows: the tiles run instead),   */
+                          /* of the plain tiles' edge list                  */
                           /* and of the traversal's replayed frontier and   */
                           /* interaction buffers; 0 = automatic (default).  */
                           /* A list that overflows is redone: the filter    */
@@ -227,12 +235,14 @@ int fnn_eps_graph_ex(const fnn_tree *tree, double eps,
  * device pointer, nq rows in the tree's metric layout and dim, caller-owned,
  * only read during the call.  The queries get a cover tree of their own
  * (built with `opt`); Algorithm 3 then runs on the pair of trees, visiting
- * only pairs across them.  *out: CSR with nq rows (query order), columns =
+ * only pairs across them.  Where an MFMA filter applies and a sample says
+ * that the tree would prune too little, it screens every pair instead,
+ * without a query tree.  *out: CSR with nq rows (query order), columns =
  * the tree's input indices, ascending, dist as in fnn_eps_graph; the same
  * exactness.  The tree must hold one cloud (FNN_EUNSUPPORTED for a batch);
  * the learned schedule and traces are not available (FNN_EUNSUPPORTED);
  * eps must be finite and > 0 (FNN_EINVAL).  Stats (fnn_get_stats on the
- * CSR) count the query tree's build as well. */
+ * CSR) count the query tree's build as well, where there is one. */
 int fnn_eps_query(const fnn_tree *tree, const void *queries, int64_t nq, double eps,
                   const fnn_options *opt, fnn_csr **out);
 
